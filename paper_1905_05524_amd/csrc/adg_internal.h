@@ -16,9 +16,6 @@
 namespace adg {
 
 constexpr int kMaxN = 8;          // nodes per direction supported (order 7)
-// the predictor runs a wavefront per time level while that puts at most this
-// many wavefronts on the chip (three per SIMD): cells * n <= kLevelsWaves
-constexpr int kLevelsWaves = 3072;
 constexpr int kWave = 64;         // CDNA wavefront size
 
 // Basis tables for n nodes, passed by value as a kernel argument so that every
@@ -39,11 +36,12 @@ struct Tab {
 //   Rk[3][n][n]  restriction (w_q/3) phi_m((k+xi_q)/3)/w_m at [k][m][q],
 //   D[n][n], Pt[n][n] (time matrix transposed: Pt[b][a] = P[a][b]), Dw[n][n],
 //   even-odd forms of D and Dw (see EvenOdd below),
-//   LU[n*n+n]: the time matrix K1 = L U (unit lower L, no pivoting: for
+//   LU[n*n]: the time matrix K1 = L U (unit lower L, no pivoting: for
 //   Gauss-Legendre nodes the factors stay bounded, |U_ii| >= 1 up to n = 8)
-//   stored in the order the in-place solve of K1 y = W r reads it: for each
-//   row i, w_i then L[i][0..i-1]; then for each row i from n-1 down to 0,
-//   1/U_ii then U[i][i+1..n-1]/U_ii.
+//   stored in the order the in-place solve of K1 y = W r reads it, with the
+//   weights moved into the factors (the forward substitution works on
+//   z_i / w_i): for each row i > 0, L[i][j] w_j / w_i for j < i; then for each
+//   row i from n-1 down to 0, w_i / U_ii then U[i][i+1..n-1] / U_ii.
 struct GTab {
   static constexpr int XI = 0, W = 1, L0 = 2, L1 = 3, E0 = 4, E1 = 5;
   static __host__ __device__ inline int pk(int n) { return 6 * n; }
@@ -55,7 +53,7 @@ struct GTab {
   static __host__ __device__ inline int eo_d(int n) { return 6 * n + 9 * n * n; }
   static __host__ __device__ inline int eo_dw(int n) { return 6 * n + 9 * n * n + eo_size(n); }
   static __host__ __device__ inline int lu(int n) { return 6 * n + 9 * n * n + 2 * eo_size(n); }
-  static __host__ __device__ inline int size(int n) { return 7 * n + 10 * n * n + 2 * eo_size(n); }
+  static __host__ __device__ inline int size(int n) { return 6 * n + 10 * n * n + 2 * eo_size(n); }
 };
 
 // Even-odd form of an n x n matrix T with T[n-1-i][n-1-m] = -T[i][m] (the
@@ -98,13 +96,9 @@ struct Group {
   double* clock = nullptr;    // [S][4]
   // launch shape: cells per wavefront, wavefronts per workgroup
   int cpw = 1, wpb = 1;
-  // predictor kernel: -1 automatic (the time-level predictor while cells * n
-  // <= kLevelsWaves, or over four wavefronts per cell while cells * 4 <=
-  // kLevelsWaves), 0 one wavefront per cell, 1 the time-level predictor
+  // predictor kernel: -1 automatic (by order and cells, pick() in
+  // predict.hip), 0 chosen by the launch shape, 1 four wavefronts per cell
   int lv = -1;
-  // wavefronts per cell of the time-level predictor: 2 or 4 spread the n
-  // time nodes over that many wavefronts (when fewer than n), else n
-  int lw = 0;
   // handle-owned scratch of the TV statistics over many cells: per-workgroup
   // partials (count, mean, M2) and the thresholds (kTvPartDoubles doubles)
   double* d_part = nullptr;
@@ -117,9 +111,6 @@ struct Group {
 // TV statistics over many cells: at most kStatParts per-workgroup partials
 constexpr int kStatParts = 512;
 constexpr int kTvPartDoubles = 3 * kStatParts + 3;
-
-// wavefronts per cell the time-level predictor of g launches
-inline int level_waves(const Group& g) { return (g.lw == 2 || g.lw == 4) && g.lw < g.n ? g.lw : g.n; }
 
 // Host copies of the basis of one order.
 struct HostBasis {
@@ -345,49 +336,6 @@ __device__ inline double recip(double x) {
   r = fma(r, e, r);
   e = fma(-x, r, 1.0);
   return fma(r, e, r);
-}
-
-// Flux (hyperbolic + viscous) in x and z and the gravity source of the
-// vertical momentum at one node (eqs. equation-set, eos, temperature,
-// stress-tensor, heat-conduction-coeff, momentum-equation-split).
-// q: conserved state; gx, gz: its gradients in reference coordinates, i.e.
-// h times the physical ones.  Every gradient enters the flux linearly through
-// the stress and the heat flux, so the 1/h is carried by mu_h = mu / h and
-// kappa_h = kappa / h, and the hydrostatic term of the vertical pressure
-// gradient by gh = g h (0 without gravity).  rb, pb: background density and
-// pressure at the node height z.
-__device__ inline void flux_source(const Phys& ph, const double q[4], const double gx[4],
-                                   const double gz[4], double z, double rb, double pb, double mu_h,
-                                   double kappa_h, double gh, double Fx[4], double Fz[4], double& Sw) {
-  const double rho = q[0], mx = q[1], mz = q[2], E = q[3];
-  const double ir = recip(rho);
-  const double u = mx * ir, w = mz * ir;
-  // branch-free in the gravity switch: geff = gh = 0 and rb = pb = 0 without it
-  const double gzz = ph.geff * z;
-  const double p = ph.gm1 * (E - 0.5 * (mx * u + mz * w) - rho * gzz);
-  const double pm = p - pb;
-  const double T = p * ir * ph.iR;
-  const double dux = (gx[1] - u * gx[0]) * ir, duz = (gz[1] - u * gz[0]) * ir;
-  const double dwx = (gx[2] - w * gx[0]) * ir, dwz = (gz[2] - w * gz[0]) * ir;
-  const double hv2 = 0.5 * (u * u + w * w) + gzz;
-  const double dpx = ph.gm1 * (gx[3] - hv2 * gx[0] - rho * (u * dux + w * dwx));
-  const double dpz = ph.gm1 * (gz[3] - hv2 * gz[0] - rho * (u * duz + w * dwz) - rho * gh);
-  const double dTx = (dpx - ph.R * T * gx[0]) * ir * ph.iR;
-  const double dTz = (dpz - ph.R * T * gz[0]) * ir * ph.iR;
-  const double div = dux + dwz;
-  const double sxx = mu_h * ((2.0 / 3.0) * div - 2.0 * dux);
-  const double szz = mu_h * ((2.0 / 3.0) * div - 2.0 * dwz);
-  const double sxz = -mu_h * (duz + dwx);
-  const double H = E + p;
-  Fx[0] = mx;
-  Fx[1] = mx * u + pm + sxx;
-  Fx[2] = mz * u + sxz;
-  Fx[3] = u * H + u * sxx + w * sxz - kappa_h * dTx;
-  Fz[0] = mz;
-  Fz[1] = mx * w + sxz;
-  Fz[2] = mz * w + pm + szz;
-  Fz[3] = w * H + u * sxz + w * szz - kappa_h * dTz;
-  Sw = -ph.geff * (rho - rb);
 }
 
 // max over the 64 lanes of a wavefront (butterfly, fixed order)

@@ -27,8 +27,9 @@ __device__ inline void wave_sync_a() {
 }
 
 // --------------------------------------------------------- pointwise VJP
-// Reverse of flux_source: given adjoints aFx, aFz of the fluxes and aSw of
-// the gravity source, returns the adjoints of the state and its gradients.
+// Reverse of the predictor's flux and gravity source at one node: given
+// adjoints aFx, aFz of the fluxes and aSw of the source, returns the adjoints
+// of the state and its (physical) gradients.
 __device__ inline void flux_source_vjp(const Phys& ph, const double q[4], const double gx[4],
                                        const double gz[4], double z, double rb, const double aFx[4],
                                        const double aFz[4], double aSw, double aq[4], double agx[4],
@@ -662,7 +663,7 @@ __global__ __launch_bounds__(kWave) void k_loss_adj(Phys ph, const double* Q, co
 }
 
 // --------------------------------------------------------------- launchers
-int launch_predictor_any(const Group& g, double* store, hipStream_t s);
+int launch_predictor(const Group& g, double* store, hipStream_t s);
 int launch_corrector(const Group& g, hipStream_t s);
 
 template <int n>
@@ -679,7 +680,7 @@ int launch_step_adjoint(const Group& g, const double* Qn, const double* lam_in, 
     Group gf = g;
     gf.Q = const_cast<double*>(Qn);
     gf.FD = const_cast<double*>(fd);
-    int rc = launch_predictor_any(gf, store, s);
+    int rc = launch_predictor(gf, store, s);
     if (rc) return rc;
   }
   AdjArgs a;

@@ -9,7 +9,7 @@
 
 namespace adg {
 
-int launch_predictor(const Group& g, hipStream_t s);
+int launch_predictor(const Group& g, double* store, hipStream_t s);
 int launch_corrector(const Group& g, hipStream_t s);
 int launch_cell_dt(const Group& g, hipStream_t s);
 int launch_clock(double* clock, const double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
@@ -24,8 +24,6 @@ int launch_regrid(int n, int C, const int* ops, const double* Qold, double* Qnew
                   hipStream_t s);
 int launch_step_adjoint(const Group& g, const double* Qn, const double* lam_in, double* lam_out, double* store,
                         const double* fd, bool recompute, double* lamFD, hipStream_t s);
-int launch_predictor_store(const Group& g, double* store, hipStream_t s);
-int launch_predictor_levels(const Group& g, double* store, hipStream_t s);
 int launch_ic_theta(const Group& g, const double* thp, hipStream_t s);
 int launch_ic_theta_adj(const Group& g, const double* thp, const double* lam, double* grad, hipStream_t s);
 int launch_loss(const Group& g, double* part, double* out, hipStream_t s);
@@ -35,25 +33,6 @@ int regrid_plan(const std::vector<int>& lev, const std::vector<int>& ci, const s
                 std::vector<int>& nci, std::vector<int>& ncj, std::vector<int>& ops);
 
 static thread_local std::string g_err;
-
-// Predictor of a group with the kernel its launch mode selects: the
-// time-level predictor (lv = 1 with the group's wavefronts per cell), or
-// automatically one wavefront per time level while cells * n <= kLevelsWaves,
-// the levels over four wavefronts per cell while cells * 4 <= kLevelsWaves
-// (n > 4), else one wavefront per cell with the group's launch shape; with a
-// store, the Picard iterates are kept (adjoint).
-int launch_predictor_any(const Group& g, double* store, hipStream_t s) {
-  if (g.lv == 1) return launch_predictor_levels(g, store, s);
-  if (g.lv < 0) {
-    const long cn = (long)g.C * g.n;
-    if (cn <= kLevelsWaves || (g.n > 4 && 4L * g.C <= kLevelsWaves)) {
-      Group t = g;
-      t.lw = cn <= kLevelsWaves ? 0 : 4;
-      return launch_predictor_levels(t, store, s);
-    }
-  }
-  return store ? launch_predictor_store(g, store, s) : launch_predictor(g, s);
-}
 
 // Corrector of one mesh, then its clock: with a frozen time step the
 // corrector's first workgroup advances t and the step count itself (no clock
@@ -216,12 +195,10 @@ void build_basis(int n, HostBasis& B) {
     }
     double* t = B.gtab.data() + GTab::lu(n);
     int o = 0;
-    for (int i = 0; i < n; ++i) {
-      t[o++] = (double)w[i];
-      for (int j = 0; j < i; ++j) t[o++] = (double)Lm[i * n + j];
-    }
+    for (int i = 1; i < n; ++i)
+      for (int j = 0; j < i; ++j) t[o++] = (double)(Lm[i * n + j] * w[j] / w[i]);
     for (int i = n - 1; i >= 0; --i) {
-      t[o++] = (double)(1.0L / Um[i * n + i]);
+      t[o++] = (double)(w[i] / Um[i * n + i]);
       for (int j = i + 1; j < n; ++j) t[o++] = (double)(Um[i * n + j] / Um[i * n + i]);
     }
   }
@@ -476,39 +453,38 @@ static int autotune_group(Group& g, hipStream_t s, int reps, float* best_ms) {
   if (g.C == 0) return ADG_OK;
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return fail(ADG_EHIP, "event");
-  // candidates: (lv, lw, cpw, wpb); lv = 1 is the time-level predictor with
-  // lw = n, 2 or 4 wavefronts per cell (its corrector shape is the default one)
-  const int cpws[3] = {1, 2, 4}, wpbs[3] = {1, 2, 4}, lws[3] = {0, 2, 4};
-  int bl = g.lv, blw = g.lw, bc = g.cpw, bw = g.wpb;
+  // candidates: (lv, cpw, wpb); lv = 1 is the predictor with four wavefronts
+  // per cell (its corrector shape is the default one)
+  const int cpws[3] = {1, 2, 4}, wpbs[3] = {1, 2, 4};
+  int bl = g.lv, bc = g.cpw, bw = g.wpb;
   float best = 1e30f;
-  for (int k = -3; k < 9; ++k) {
+  for (int k = -1; k < 9; ++k) {
     Group t = g;
     if (k < 0) {
-      t.lv = 1; t.lw = lws[k + 3]; t.cpw = 1; t.wpb = 1;
-      if (t.lw && t.lw >= g.n) continue;   // the same kernel as lw = n
+      t.lv = 1; t.cpw = 1; t.wpb = 1;
     } else {
       t.lv = 0; t.cpw = cpws[k / 3]; t.wpb = wpbs[k % 3];
       if (t.cpw > max_cpw(g.n)) continue;
     }
     Group tc = t;
     tc.Q = t.Qs;   // corrector reads Q*, writes in place: state untouched
-    int rc = launch_predictor_any(t, nullptr, s);   // warm-up
+    int rc = launch_predictor(t, nullptr, s);   // warm-up
     if (!rc) rc = launch_corrector(tc, s);
     if (rc) { (void)hipEventDestroy(e0); (void)hipEventDestroy(e1); return rc; }
     (void)hipEventRecord(e0, s);
     for (int r = 0; r < reps; ++r) {
-      launch_predictor_any(t, nullptr, s);
+      launch_predictor(t, nullptr, s);
       launch_corrector(tc, s);
     }
     (void)hipEventRecord(e1, s);
     (void)hipEventSynchronize(e1);
     float ms = 0.0f;
     (void)hipEventElapsedTime(&ms, e0, e1);
-    if (ms < best) { best = ms; bl = t.lv; blw = t.lw; bc = t.cpw; bw = t.wpb; }
+    if (ms < best) { best = ms; bl = t.lv; bc = t.cpw; bw = t.wpb; }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  g.lv = bl; g.lw = blw; g.cpw = bc; g.wpb = bw;
+  g.lv = bl; g.cpw = bc; g.wpb = bw;
   if (best_ms) *best_ms = best / reps;
   return check_launch("autotune");
 }
@@ -622,7 +598,7 @@ int adg_compute_dt(adg_mesh* m, void* stream) {
 int adg_predictor(adg_mesh* m, void* stream) {
   int rc = need_state(m);
   if (rc) return rc;
-  return launch_predictor_any(m->g, nullptr, (hipStream_t)stream);
+  return launch_predictor(m->g, nullptr, (hipStream_t)stream);
 }
 
 int adg_corrector(adg_mesh* m, void* stream) {
@@ -849,7 +825,7 @@ int adg_step_keep(adg_mesh* m, double* store, double* fd, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   Group gf = m->g;
   gf.FD = fd;   // the corrector reads the kept face data
-  rc = launch_predictor_any(gf, store, s);
+  rc = launch_predictor(gf, store, s);
   if (rc) return rc;
   return launch_corrector_clock(gf, m->clock, s);
 }
@@ -867,7 +843,7 @@ int adg_step_to(adg_mesh* m, double* Q_out, double* store, double* fd, void* str
   hipStream_t s = (hipStream_t)stream;
   Group gp = m->g;
   if (fd) gp.FD = fd;   // the corrector reads the kept face data
-  rc = launch_predictor_any(gp, store, s);
+  rc = launch_predictor(gp, store, s);
   if (rc) return rc;
   Group gc = gp;
   gc.Q = Q_out;         // the corrector writes Q^{n+1} here; it reads only Q* and the face data
@@ -924,10 +900,10 @@ int adg_loss_theta_adjoint(adg_mesh* m, const double* loss, const double* grad_l
 
 int adg_set_launch(adg_mesh* m, int cells_per_wave, int waves_per_block) {
   if (!m) return fail(ADG_EINVAL, "null handle");
-  if (cells_per_wave == 0) {   // time-level predictor: n (1), 2 or 4 wavefronts per cell
+  if (cells_per_wave == 0) {   // four wavefronts per cell
     if (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4)
       return fail(ADG_EINVAL, "waves_per_block must be 1, 2 or 4 with cells_per_wave 0");
-    m->g.lv = 1; m->g.lw = waves_per_block == 1 ? 0 : waves_per_block; m->g.cpw = 1; m->g.wpb = 1;
+    m->g.lv = 1; m->g.cpw = 1; m->g.wpb = 1;
     return ADG_OK;
   }
   if ((cells_per_wave != 1 && cells_per_wave != 2 && cells_per_wave != 4) || cells_per_wave > max_cpw(m->g.n))
@@ -945,7 +921,7 @@ int adg_autotune(adg_mesh* m, int reps, void* stream, int* cells_per_wave, int* 
   rc = autotune_group(m->g, (hipStream_t)stream, reps, nullptr);
   if (rc) return rc;
   if (cells_per_wave) *cells_per_wave = m->g.lv == 1 ? 0 : m->g.cpw;
-  if (waves_per_block) *waves_per_block = m->g.lv == 1 ? (level_waves(m->g) == m->g.n ? 1 : m->g.lw) : m->g.wpb;
+  if (waves_per_block) *waves_per_block = m->g.lv == 1 ? 1 : m->g.wpb;
   return ADG_OK;
 }
 
@@ -1015,7 +991,7 @@ static int batch_enqueue_step(adg_batch* b, hipStream_t s) {
     hipStream_t gs = b->streams[g];
     if (hipStreamWaitEvent(gs, b->events[0], 0) != hipSuccess) return fail(ADG_EHIP, "stream wait");
     int rc = b->mode == 1 ? launch_predictor_queue(b->groups[g], b->d_queue + 2 * g, b->queue_waves[g], gs)
-                          : launch_predictor_any(b->groups[g], nullptr, gs);
+                          : launch_predictor(b->groups[g], nullptr, gs);
     if (!rc) rc = launch_corrector(b->groups[g], gs);
     if (rc) return rc;
     if (hipEventRecord(b->events[1 + g], gs) != hipSuccess) return fail(ADG_EHIP, "event record");
@@ -1250,7 +1226,7 @@ int adg_batch_autotune(adg_batch* b, int reps, void* stream, int* cells_per_wave
     if (cells_per_wave) cells_per_wave[gi] = b->groups[gi].lv == 1 ? 0 : b->groups[gi].cpw;
     if (waves_per_block) {
       const Group& gg = b->groups[gi];
-      waves_per_block[gi] = gg.lv == 1 ? (level_waves(gg) == gg.n ? 1 : gg.lw) : gg.wpb;
+      waves_per_block[gi] = gg.lv == 1 ? 1 : gg.wpb;
     }
   }
   if (b->exec) { (void)hipGraphExecDestroy(b->exec); b->exec = nullptr; }
@@ -1299,10 +1275,10 @@ int adg_batch_set_launch(adg_batch* b, int group, int cells_per_wave, int waves_
   if (!b) return fail(ADG_EINVAL, "null batch");
   if (group < 0 || group >= (int)b->groups.size()) return fail(ADG_EINVAL, "group out of range");
   Group& g = b->groups[group];
-  if (cells_per_wave == 0) {   // time-level predictor: n (1), 2 or 4 wavefronts per cell
+  if (cells_per_wave == 0) {   // four wavefronts per cell
     if (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4)
       return fail(ADG_EINVAL, "waves_per_block must be 1, 2 or 4 with cells_per_wave 0");
-    g.lv = 1; g.lw = waves_per_block == 1 ? 0 : waves_per_block; g.cpw = 1; g.wpb = 1;
+    g.lv = 1; g.cpw = 1; g.wpb = 1;
   } else {
     if ((cells_per_wave != 1 && cells_per_wave != 2 && cells_per_wave != 4) || cells_per_wave > max_cpw(g.n))
       return fail(ADG_EINVAL, "cells_per_wave must be 0, 1, 2 or 4 with cells_per_wave * n^2 <= 64");

@@ -456,10 +456,7 @@ __global__ __launch_bounds__(kThreads3, 3) void k_pred3_w64(Phys ph, Tab<4> tb, 
     const double* lu = a.gtab + GTab::lu(n);
     int o = 0;
 #pragma unroll
-    for (int ii = 0; ii < n; ++ii) {
-      const double wi = lu[o++];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) X[ii][v] *= wi;
+    for (int ii = 1; ii < n; ++ii) {
 #pragma unroll
       for (int jj = 0; jj < ii; ++jj) {
         const double l = lu[o++];

@@ -38,7 +38,7 @@ int static_scratch_address(int dev, void** ptr) {
   return ADG_OK;
 }
 
-int launch_predictor_any(const Group& g, double* store, hipStream_t s);
+int launch_predictor(const Group& g, double* store, hipStream_t s);
 int launch_corrector(const Group& g, hipStream_t s);
 int launch_corrector_clock(Group g, double* clock, hipStream_t s);
 
@@ -69,7 +69,7 @@ extern "C" int adg_step_static(adg_mesh* m, double* Q, double* clock, void* stre
   g.dtc = reinterpret_cast<double*>(ws + m->off_dtc);
   g.clock = clock;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int rc = launch_predictor_any(g, nullptr, s);
+  int rc = launch_predictor(g, nullptr, s);
   if (rc) return rc;
   return launch_corrector_clock(g, clock, s);
 }

@@ -1,0 +1,66 @@
+"""The predictor's kernels at the edges of their packings and of the rule that
+picks among them: strips of cells one below, at and one above a workgroup's
+cells (so that the last workgroup is ragged), single cells, and both sides of
+every cell count at which the default changes kernel.  Against the oracle at
+the bars of one step, and every launch shape against every other bit for bit
+(the kernels share the arithmetic of each value)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import oracle as O  # noqa: E402
+from paper_1905_05524_amd import adg  # noqa: E402
+from paper_1905_05524_amd import inputs as I  # noqa: E402
+from tests import parity as P  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# cells per workgroup of the packings: 16, 7, 4, 2 or 5, 3, 1, 1
+EDGES = {1: (1, 15, 17), 2: (1, 6, 8), 3: (3, 5), 4: (1, 4, 6, 11), 5: (2, 4, 7), 6: (1, 2), 7: (1, 3)}
+RULE = [(1, 384), (1, 385), (4, 385), (4, 4097), (5, 768), (5, 769), (5, 2048), (5, 2049), (7, 769)]
+
+
+def strip(N, C, flow):
+    if flow == "wave":
+        w = I.mms_small(N=N, nx=C, mu=0.02)
+        w["mesh"].update(nx=C, nz=1, Lx=1.0, Lz=1.0 / C)
+        kind = "mms"
+    else:
+        w = I.bubble(C, N)
+        w["mesh"].update(nx=C, nz=1, Lx=1000.0, Lz=1000.0 / C)
+        kind = "bubbles"
+    Q = O.ic(w["phys"], w["mesh"], kind, w["bubbles"])
+    return w, (Q if flow == "wave" else I.perturb(Q, seed=N))
+
+
+def step(w, Q, dt, shape=None):
+    m = adg.Mesh(w["phys"], w["mesh"], fixed_dt=True)
+    if shape is not None:
+        m.set_launch(*shape)
+    m.set_state(Q, t=0.1, dt=dt)
+    m.step()
+    torch.cuda.synchronize()
+    return m.Q.clone()
+
+
+@pytest.mark.parametrize("flow", ["air", "wave"])
+@pytest.mark.parametrize("N,C", [(N, C) for N, cs in EDGES.items() for C in cs])
+def test_ragged_workgroups(N, C, flow):
+    w, Q = strip(N, C, flow)
+    dt = 0.5 * O.dt(w["phys"], w["mesh"], Q)
+    ref = O.step(w["phys"], w["mesh"], Q, 0.1, dt)
+    base = step(w, Q, dt)
+    P.assert_step(base.cpu().numpy(), ref, Q, what=f"N={N} C={C}")
+    n = N + 1
+    for shape in ((0, 1), (1, 1), (1, 2), (2, 1), (4, 1)):
+        if max(shape[0], 1) * n * n <= 64:
+            assert torch.equal(step(w, Q, dt, shape), base), shape
+
+
+@pytest.mark.parametrize("N,C", RULE)
+def test_both_sides_of_the_kernel_rule(N, C):
+    w, Q = strip(N, C, "air")
+    dt = 0.5 * O.dt(w["phys"], w["mesh"], Q)
+    got = step(w, Q, dt)
+    P.assert_step(got.cpu().numpy(), O.step(w["phys"], w["mesh"], Q, 0.1, dt), Q, what=f"N={N} C={C}")
+    assert torch.equal(got, step(w, Q, dt, (1, 1)))
