@@ -18,6 +18,7 @@ struct Args3 {
   double* dtc;          // [C] CFL candidates
   const double* clock;  // (t, dt, -, steps)
   const double* gtab;   // GTab layout
+  const double* bg;     // [nz][n][2] background density and pressure of the node rows
   int nx, ny, nz, C, iters;
   int wall;             // bit f set: domain face f is a wall
   double x0, y0, z0, h;
@@ -32,6 +33,8 @@ struct Bubbles3 {
 
 int launch_pred3(const Phys& ph, const HostBasis& B, const Args3& a, hipStream_t s);
 int launch_corr3(const Phys& ph, int n, const Args3& a, hipStream_t s);
+// fills bg (Args3) on the device
+int launch_background3(const Phys& ph, int n, const Args3& a, double* bg, hipStream_t s);
 int launch_dt3(const Phys& ph, int n, const Args3& a, hipStream_t s);
 int launch_init3(const Phys& ph, int n, const Args3& a, int kind, const Bubbles3& B, double t0, double* Q,
                  hipStream_t s);
@@ -47,7 +50,8 @@ struct adg3_mesh {
   adg::HostBasis basis;
   adg::Phys ph{};
   int n = 0, C = 0, iters = 0;
-  double* d_gtab = nullptr;
+  double* d_gtab = nullptr;   // basis tables, then the background table
+  double* d_bg = nullptr;     // within d_gtab
   // bound (caller-owned)
   double* Q = nullptr;
   void* ws = nullptr;

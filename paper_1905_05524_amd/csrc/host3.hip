@@ -32,7 +32,7 @@ static Args3 args_of(const adg3_mesh* m) {
   a.Qs = ws ? reinterpret_cast<double*>(ws + m->off_qs) : nullptr;
   a.FD = ws ? reinterpret_cast<double*>(ws + m->off_fd) : nullptr;
   a.dtc = ws ? reinterpret_cast<double*>(ws + m->off_dtc) : nullptr;
-  a.clock = m->clock; a.gtab = m->d_gtab;
+  a.clock = m->clock; a.gtab = m->d_gtab; a.bg = m->d_bg;
   a.nx = m->desc.nx; a.ny = m->desc.ny; a.nz = m->desc.nz; a.C = m->C; a.iters = m->iters;
   a.wall = 0;
   for (int f = 0; f < 6; ++f)
@@ -71,11 +71,20 @@ int adg3_init_mesh(const adg_params* prm, const adg3_mesh_desc* mesh, adg3_mesh*
   m->ph = make_phys(*prm);
   build_basis(m->n, m->basis);
   const size_t tb = sizeof(double) * m->basis.gtab.size();
-  if (hipMalloc(&m->d_gtab, tb) != hipSuccess) { delete m; return fail(ADG_ENOMEM, "device allocation failed"); }
+  const size_t bb = sizeof(double) * 2 * (size_t)mesh->nz * m->n;
+  if (hipMalloc(&m->d_gtab, tb + bb) != hipSuccess) { delete m; return fail(ADG_ENOMEM, "device allocation failed"); }
+  m->d_bg = m->d_gtab + m->basis.gtab.size();
   if (hipMemcpy(m->d_gtab, m->basis.gtab.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(m->d_gtab);
     delete m;
     return fail(ADG_EHIP, "upload failed");
+  }
+  // the table is complete before any stream can use the handle
+  rc = launch_background3(m->ph, m->n, args_of(m), m->d_bg, nullptr);
+  if (rc || hipStreamSynchronize(nullptr) != hipSuccess) {
+    (void)hipFree(m->d_gtab);
+    delete m;
+    return rc ? rc : fail(ADG_EHIP, "background table failed");
   }
   const size_t C = (size_t)m->C, nd = (size_t)m->n * m->n * m->n, nn = (size_t)m->n * m->n;
   size_t off = 0;

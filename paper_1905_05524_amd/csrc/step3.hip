@@ -3,16 +3,19 @@
 // (periodic and wall faces) and the CFL candidate of every cell, initial
 // states and the health check.
 //
-// Work decomposition.  A workgroup of kThreads3 threads holds CB cells; the
+// Work decomposition of the corrector, the time step and the predictor of
+// orders other than N = 3.  A workgroup of kThreads3 threads holds CB cells; the
 // thread t owns spatial node t % nd (nd = n^3) of cell slot t / nd, so a
 // cell's nodes are consecutive lanes.  For n = 2 and n = 4 every cell lies in
 // one wavefront and the LDS hand-offs between its nodes need only a
 // wavefront barrier; otherwise cells straddle wavefronts and the workgroup
 // synchronises.  Threads past CB * nd (when nd does not divide the
 // workgroup) mirror the threads of slot 0: same cell, same node, hence the
-// same values written to the same LDS addresses, and no global stores.  Tensor-product contractions along x, y and z read n values of an
-// LDS slice per output; the space-time iterate of a node (n time levels x 5
-// variables) stays in registers.
+// same values written to the same LDS addresses, and no global stores.
+// Tensor-product contractions along x, y and z read n values of an LDS slice
+// per output; the space-time iterate of a node (n time levels x 5 variables)
+// stays in registers.  The predictor of N = 3 (k_pred3_w64) keeps that layout
+// with one wavefront per cell and contracts with matrix instructions.
 #include "adg3_internal.h"
 
 namespace adg {
@@ -41,53 +44,68 @@ __device__ inline double pressure3(const Phys& ph, const double q[5], double z) 
   return ph.gm1 * (q[4] - 0.5 * (q[1] * q[1] + q[2] * q[2] + q[3] * q[3]) / q[0] - geo);
 }
 
-// Flux along x, y, z and the gravity source of the vertical momentum at one
-// node: the equation set of Section 2 in three dimensions (eqs. equation-set,
-// eos, temperature, stress-tensor, heat-conduction-coeff,
-// momentum-equation-split).  g[d]: gradient of the conserved state along d in
-// reference coordinates (h times the physical one); the 1/h of the viscous
-// and heat fluxes is carried by mu_h = mu/h and kappa_h = kappa/h, the
-// hydrostatic part of the vertical pressure gradient by gh = g h (0 without
-// gravity).  rb, pb: background density and pressure at the node height z.
-__device__ inline void flux_source3(const Phys& ph, const double q[5], const double g[3][5], double z, double rb,
-                                    double pb, double mu_h, double kappa_h, double gh, double F[3][5],
-                                    double& Sw) {
+// Per-launch and per-lane constants of the flux: the 1/h of the viscous and
+// heat fluxes (gradients are in reference coordinates, h times the physical
+// ones) sits in mu, mu2, mu23, kap and gh.
+struct FluxC3 {
+  double gm1, hgm1, mu, mu2, mu23, kap, gh;   // gm1, gm1/2, mu/h, 2 mu/h, (2/3) mu/h, kappa/(h R), g h
+  double gz, pb;                              // g z and background pressure at the node
+};
+__device__ inline FluxC3 flux_consts3(const Phys& ph, double h) {
+  FluxC3 c;
+  c.gm1 = ph.gm1;
+  c.hgm1 = 0.5 * ph.gm1;
+  c.mu = ph.mu / h;
+  c.mu2 = 2.0 * c.mu;
+  c.mu23 = (2.0 / 3.0) * c.mu;
+  c.kap = ph.kappa / h * ph.iR;
+  c.gh = ph.geff * h;
+  c.gz = 0.0;
+  c.pb = 0.0;
+  return c;
+}
+
+// Momentum and energy fluxes F[d][0..3] along x, y, z at one node: the
+// equation set of Section 2 in three dimensions (eqs. equation-set, eos,
+// temperature, stress-tensor, heat-conduction-coeff,
+// momentum-equation-split).  q: state, g[d]: its gradient along d in
+// reference coordinates.  The mass fluxes are the momenta and are left out;
+// a[c][d] = rho du_c/dx_d, so that the divisions by rho collect in ir, and the
+// off-diagonal fluxes m_a u_b + sigma_ab are symmetric and formed once.
+__device__ inline void flux_xyz(const FluxC3& k, const double q[5], const double g[3][5], double F[3][4]) {
   const double rho = q[0], E = q[4];
   const double ir = recip(rho);
   const double u[3] = {q[1] * ir, q[2] * ir, q[3] * ir};
-  const double gzz = ph.geff * z;
-  const double p = ph.gm1 * (E - 0.5 * (q[1] * u[0] + q[2] * u[1] + q[3] * u[2]) - rho * gzz);
-  const double pm = p - pb;
-  const double T = p * ir * ph.iR;
-  double du[3][3];   // du[a][d] = d u_a / d x_d (reference coordinates)
+  const double ke = fma(q[1], u[0], fma(q[2], u[1], q[3] * u[2]));   // rho |v|^2
+  const double p = fma(-k.hgm1, ke, k.gm1 * fma(-k.gz, rho, E));
+  const double pm = p - k.pb, pir = p * ir;                          // pir = R T
+  double a[3][3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+  for (int c = 0; c < 3; ++c)
 #pragma unroll
-    for (int d = 0; d < 3; ++d) du[a][d] = (g[d][1 + a] - u[a] * g[d][0]) * ir;
-  const double hv2 = 0.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) + gzz;
-  double dT[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    double dp = ph.gm1 * (g[d][4] - hv2 * g[d][0] - rho * (u[0] * du[0][d] + u[1] * du[1][d] + u[2] * du[2][d]));
-    if (d == 2) dp -= ph.gm1 * rho * gh;
-    dT[d] = (dp - ph.R * T * g[d][0]) * ir * ph.iR;
-  }
-  const double div = du[0][0] + du[1][1] + du[2][2];
-  double sig[3][3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-      sig[a][b] = mu_h * ((a == b ? (2.0 / 3.0) * div : 0.0) - (du[a][b] + du[b][a]));
-  const double H = E + p;
+    for (int d = 0; d < 3; ++d) a[c][d] = fma(-u[c], g[d][0], g[d][1 + c]);
+  const double hv = fma(0.5 * ir, ke, k.gz);
+  double Qd[3];                                                      // gm1 dp' - R T drho: heat flux along d
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    F[d][0] = q[1 + d];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) F[d][1 + a] = q[1 + a] * u[d] + (a == d ? pm : 0.0) + sig[a][d];
-    F[d][4] = u[d] * H + (u[0] * sig[0][d] + u[1] * sig[1][d] + u[2] * sig[2][d]) - kappa_h * dT[d];
+    double dp = fma(-u[2], a[2][d], fma(-u[1], a[1][d], fma(-u[0], a[0][d], fma(-hv, g[d][0], g[d][4]))));
+    if (d == 2) dp = fma(-k.gh, rho, dp);
+    Qd[d] = fma(-pir, g[d][0], k.gm1 * dp);
   }
-  Sw = -ph.geff * (rho - rb);
+  const double m = k.mu * ir, m2 = k.mu2 * ir;
+  const double t = (k.mu23 * ir) * ((a[0][0] + a[1][1]) + a[2][2]);
+  const double s01 = -m * (a[0][1] + a[1][0]), s02 = -m * (a[0][2] + a[2][0]), s12 = -m * (a[1][2] + a[2][1]);
+  const double kk = k.kap * ir, H = E + p;
+  const double s0 = fma(-m2, a[0][0], t), s1 = fma(-m2, a[1][1], t), s2 = fma(-m2, a[2][2], t);
+  F[0][0] = fma(q[1], u[0], pm + s0);
+  F[1][1] = fma(q[2], u[1], pm + s1);
+  F[2][2] = fma(q[3], u[2], pm + s2);
+  F[0][1] = F[1][0] = fma(q[1], u[1], s01);
+  F[0][2] = F[2][0] = fma(q[1], u[2], s02);
+  F[1][2] = F[2][1] = fma(q[2], u[2], s12);
+  F[0][3] = fma(-kk, Qd[0], fma(u[2], s02, fma(u[1], s01, u[0] * (H + s0))));
+  F[1][3] = fma(-kk, Qd[1], fma(u[2], s12, fma(u[0], s01, u[1] * (H + s1))));
+  F[2][3] = fma(-kk, Qd[2], fma(u[1], s12, fma(u[0], s02, u[2] * (H + s2))));
 }
 
 // largest wave speed along d and the viscous speed at a face node
@@ -124,13 +142,25 @@ __device__ inline void wall_ghost3(const Phys& ph, int d, double zf, const doubl
   Fg[4] = 2.0 * qbg - Fi[4];
 }
 
+// Background density and pressure at the node rows of every layer of cells,
+// once per handle: the predictor would spend a tenth of its instructions on
+// the power function (250 of 2,500 to 4,500 per node at n = 2 to 4).
+__global__ void k_background3(Phys ph, Args3 a, int n, double* bg) {
+  const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= (long long)a.nz * n) return;
+  const int ck = (int)(g / n), k = (int)(g % n);
+  double rb, pb;
+  background(ph, (a.z0 + ck * a.h) + a.h * a.gtab[GTab::XI * n + k], rb, pb);
+  bg[2 * g] = rb;
+  bg[2 * g + 1] = pb;
+}
+
 // ---------------------------------------------------------------- predictor
 // Gradient of the slice src ([5][nd] in LDS) at node (k, j, i) along x, y, z
 // with the derivative-matrix rows of the node, then the flux and source.
 template <int n>
-__device__ inline void grad_flux3(const Phys& ph, const double* src, int i, int j, int k, const double Di[n],
-                                  const double Dj[n], const double Dk[n], const double q[5], double z, double rb,
-                                  double pb, double mu_h, double kappa_h, double gh, double F[3][5], double& Sw) {
+__device__ inline void grad_flux3(const FluxC3& fc, const double* src, int i, int j, int k, const double Di[n],
+                                  const double Dj[n], const double Dk[n], const double q[5], double F[3][5]) {
   constexpr int nn = n * n, nd = nn * n;
   double g[3][5];
 #pragma unroll
@@ -145,7 +175,14 @@ __device__ inline void grad_flux3(const Phys& ph, const double* src, int i, int 
     }
     g[0][v] = gx; g[1][v] = gy; g[2][v] = gz;
   }
-  flux_source3(ph, q, g, z, rb, pb, mu_h, kappa_h, gh, F, Sw);
+  double F4[3][4];
+  flux_xyz(fc, q, g, F4);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    F[d][0] = q[1 + d];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) F[d][1 + v] = F4[d][v];
+  }
 }
 
 // sum over the three directions of the contraction of the flux components
@@ -212,9 +249,10 @@ __global__ __launch_bounds__(kThreads3) void k_pred3(Phys ph, Tab<n> tb, Args3 a
   const double h = a.h;
   const int ck = c / (a.nx * a.ny);
   const double z = (a.z0 + ck * h) + h * a.gtab[GTab::XI * n + k];
-  double rb, pb;
-  background(ph, z, rb, pb);
-  const double mu_h = ph.mu / h, kappa_h = ph.kappa / h, gh = ph.geff * h;
+  const double rb = a.bg[2 * (ck * n + k)];
+  FluxC3 fc = flux_consts3(ph, h);
+  fc.gz = ph.geff * z;
+  fc.pb = a.bg[2 * (ck * n + k) + 1];
   const double dt = a.clock[1], sdt = -dt / h;
   double Di[n], Dj[n], Dk[n];
 #pragma unroll
@@ -245,8 +283,9 @@ __global__ __launch_bounds__(kThreads3) void k_pred3(Phys ph, Tab<n> tb, Args3 a
 #pragma unroll
       for (int v = 0; v < 5; ++v) sq[v * nd + r] = X[b][v];
       sync3<WL>();
-      double F[3][5], Sw;
-      grad_flux3<n>(ph, sq, i, j, k, Di, Dj, Dk, X[b], z, rb, pb, mu_h, kappa_h, gh, F, Sw);
+      double F[3][5];
+      const double Sw = -ph.geff * (X[b][0] - rb);
+      grad_flux3<n>(fc, sq, i, j, k, Di, Dj, Dk, X[b], F);
 #pragma unroll
       for (int d = 0; d < 3; ++d)
 #pragma unroll
@@ -282,8 +321,9 @@ __global__ __launch_bounds__(kThreads3) void k_pred3(Phys ph, Tab<n> tb, Args3 a
 #pragma unroll
     for (int v = 0; v < 5; ++v) buf[v * nd + r] = X[b][v];
     sync3<WL>();
-    double F[3][5], Sw;
-    grad_flux3<n>(ph, buf, i, j, k, Di, Dj, Dk, X[b], z, rb, pb, mu_h, kappa_h, gh, F, Sw);
+    double F[3][5];
+    const double Sw = -ph.geff * (X[b][0] - rb);
+    grad_flux3<n>(fc, buf, i, j, k, Di, Dj, Dk, X[b], F);
     const double w = tb.w[b];
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
@@ -323,111 +363,86 @@ __global__ __launch_bounds__(kThreads3) void k_pred3(Phys ph, Tab<n> tb, Args3 a
 }
 
 // ------------------------------------------------ predictor, n = 4 (N = 3)
-// One cell per wavefront, lane l = 16 k + 4 j + i.  The contractions along x
-// and y run on the lanes of a quad (x) and of a 16-lane row (y) through the
-// DPP network: rotation r brings each lane the value of the node r steps
-// further along the line, multiplied by the matching entry of the lane's
-// derivative-matrix row.  Only the z contractions go through LDS (one slice
-// of 5 variables, read 4 values per output), so an LDS round trip per time
-// level moves 10 writes and 40 reads per lane instead of 20 and 120.
+// One cell per wavefront, lane l = 16 k + 4 j + i, the four time levels of a
+// node in registers.  Lines of four nodes are what one 4 x 4 x 4 matrix
+// instruction (four blocks, here the four rows j) contracts: along z
+// directly (the lane bits of k are the contracted ones), along x after a
+// transposition of every x-z plane, itself a product with the identity
+// (exact).  A matrix instruction takes the time of four vector FMAs, so a z
+// contraction costs what its FMAs would and an x contraction twice that, with
+// no lane exchange; the y contractions go through LDS (one slice of the
+// variables, three values read per output beside the lane's own).
+// Bound by the FP64 issue rate: per cell 3,390 vector and 451 matrix
+// instructions (8,820 vector ones when the x and z operands moved through the
+// DPP network, six moves per contraction, and the background's power function
+// ran per lane).  25^3 cells, 4 iterations: 172 us, 238 us before.  Three
+// waves per SIMD: at four (128 registers) the sweep spills, 187 us.
 
-// lane exchange of a double through the DPP network (two 32-bit moves; every
-// lane of a quad or row has a source, so no lane keeps an old value)
-template <int ctrl>
-__device__ inline double dpp_d(double x) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), ctrl, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), ctrl, 0xF, 0xF, true);
-  return __hiloint2double(hi, lo);
+// D[i][j] = sum_k A[i][k] B[k][j] + C[i][j] in every block b, with A in lane
+// 16 k + 4 b + i, B in lane 16 k + 4 b + j, C and D in lane 16 i + 4 b + j
+__device__ inline double mm4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
-// quad_perm control word: lane i of every quad reads lane (i + r) & 3
-template <int r>
-constexpr int quad_rot() {
-  return ((0 + r) & 3) | (((1 + r) & 3) << 2) | (((2 + r) & 3) << 4) | (((3 + r) & 3) << 6);
-}
-constexpr int kRowRor = 0x120;   // row_ror:s control word base (rotation by s lanes within a row of 16)
-
-// sum_r c[r] x(node r steps along x), the r = 0 term the lane's own value
-__device__ inline double cx4(const double c[4], double x) {
-  double s = c[0] * x;
-  s = fma(c[1], dpp_d<quad_rot<1>()>(x), s);
-  s = fma(c[2], dpp_d<quad_rot<2>()>(x), s);
-  s = fma(c[3], dpp_d<quad_rot<3>()>(x), s);
-  return s;
-}
-// the same along y (rows of 16 lanes hold the 4 x 4 nodes of one z level)
-__device__ inline double cy4(const double c[4], double x) {
-  double s = c[0] * x;
-  s = fma(c[1], dpp_d<kRowRor + 4>(x), s);
-  s = fma(c[2], dpp_d<kRowRor + 8>(x), s);
-  s = fma(c[3], dpp_d<kRowRor + 12>(x), s);
-  return s;
-}
-// z contraction of a [nd] LDS slice at node (j, i) = l & 15
-__device__ inline double cz4(const double c[4], const double* s, int ji) {
-  double acc = c[0] * s[ji];
-  acc = fma(c[1], s[16 + ji], acc);
-  acc = fma(c[2], s[32 + ji], acc);
-  acc = fma(c[3], s[48 + ji], acc);
-  return acc;
-}
-
-// rows of a node-indexed matrix table T (n = 4) matched to the lane
-// exchanges: cx[r] = T[i][i'] and cy[r] = T[j][j'] with i', j' the node
-// indices that rotation r delivers (found by sending the indices themselves
-// through the same exchange), cz[m] = T[k][m]
-__device__ inline void rot_rows4(const double* T, int i, int j, int k, double cx[4], double cy[4], double cz[4]) {
-  const int pi1 = __builtin_amdgcn_mov_dpp(i, quad_rot<1>(), 0xF, 0xF, true);
-  const int pi2 = __builtin_amdgcn_mov_dpp(i, quad_rot<2>(), 0xF, 0xF, true);
-  const int pi3 = __builtin_amdgcn_mov_dpp(i, quad_rot<3>(), 0xF, 0xF, true);
-  const int pj1 = __builtin_amdgcn_mov_dpp(j, kRowRor + 4, 0xF, 0xF, true);
-  const int pj2 = __builtin_amdgcn_mov_dpp(j, kRowRor + 8, 0xF, 0xF, true);
-  const int pj3 = __builtin_amdgcn_mov_dpp(j, kRowRor + 12, 0xF, 0xF, true);
-  cx[0] = T[i * 4 + i]; cx[1] = T[i * 4 + pi1]; cx[2] = T[i * 4 + pi2]; cx[3] = T[i * 4 + pi3];
-  cy[0] = T[j * 4 + j]; cy[1] = T[j * 4 + pj1]; cy[2] = T[j * 4 + pj2]; cy[3] = T[j * 4 + pj3];
+// tables of the lane for a matrix T: its entry at (lane bits 0-1, bits 4-5),
+// and its row for the y contraction, own node first, then the nodes one, two
+// and three steps further
+struct Tab4 {
+  double T, y[4];
+};
+__device__ inline Tab4 tab4(const double* g, int lane) {
+  const int lo = lane & 3, j = (lane >> 2) & 3, k = lane >> 4;
+  Tab4 t;
+  t.T = g[lo * 4 + k];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) cz[m] = T[k * 4 + m];
+  for (int m = 0; m < 4; ++m) t.y[m] = g[j * 4 + ((j + m) & 3)];
+  return t;
 }
+// the lane's node m steps further along y
+__device__ inline int step_y(int lane, int m) { return (lane & 51) | ((lane + 4 * m) & 12); }
 
-__global__ __launch_bounds__(kThreads3, 3) void k_pred3_w64(Phys ph, Tab<4> tb, Args3 a) {
+// Workgroups of one wavefront: LDS and barriers are per cell anyway, and the
+// last round of workgroups ends sooner (four cells: 173.7 us at 25^3).
+constexpr int kW64Cells = 1;
+__global__ __launch_bounds__(kWave * kW64Cells, 3) void k_pred3_w64(Phys ph, Tab<4> tb, Args3 a) {
   constexpr int n = 4, nd = 64;
   extern __shared__ double lds[];
   const int tid = threadIdx.x, slot = tid >> 6, r = tid & 63;
-  const int cell = blockIdx.x * (kThreads3 / kWave) + slot;
+  const int cell = blockIdx.x * kW64Cells + slot;
   const bool valid = cell < a.C;
   const int c = valid ? cell : a.C - 1;   // loads stay in bounds; nothing is stored for such lanes
   double* sq = lds + slot * 20 * nd;      // state slice [5][nd]; the averaged state in the epilogue
-  double* sF = sq + 5 * nd;               // z fluxes [5][nd]; all averaged fluxes [3][5][nd] in the epilogue
-  const int i = r & 3, j = (r >> 2) & 3, k = r >> 4, ji = r & 15;
+  double* sF = sq + 5 * nd;               // y fluxes [4][nd]; all averaged fluxes [3][5][nd] in the epilogue
+  const int k = r >> 4;
   const double h = a.h;
   const int ck = c / (a.nx * a.ny);
   const double z = (a.z0 + ck * h) + h * a.gtab[GTab::XI * n + k];
-  double rb, pb;
-  background(ph, z, rb, pb);
-  const double mu_h = ph.mu / h, kappa_h = ph.kappa / h, gh = ph.geff * h;
-  const double dt = a.clock[1], sdt = -dt / h;
-  double Cx[4], Cy[4], Cz[4];
-  rot_rows4(a.gtab + GTab::d(n), i, j, k, Cx, Cy, Cz);
-  const double* Qc = a.Q + (size_t)c * 5 * nd;
-  double Q0[5], X[n][5];
-#pragma unroll
-  for (int v = 0; v < 5; ++v) Q0[v] = Qc[v * nd + r];
+  const double rb = a.bg[2 * (ck * n + k)];
+  FluxC3 fc = flux_consts3(ph, h);
+  fc.gz = ph.geff * z;
+  fc.pb = a.bg[2 * (ck * n + k) + 1];
+  const double dt = a.clock[1], ih = 1.0 / h;
+  const Tab4 D = tab4(a.gtab + GTab::d(n), r);
+  const double one = (r & 3) == (r >> 4) ? 1.0 : 0.0;
+  const int y1 = step_y(r, 1), y2 = step_y(r, 2), y3 = step_y(r, 3);
+  const double* Qc = a.Q + (size_t)c * 5 * nd + r;
+  double X[n][5];
 #pragma unroll
   for (int b = 0; b < n; ++b)
 #pragma unroll
-    for (int v = 0; v < 5; ++v) X[b][v] = Q0[v];
+    for (int v = 0; v < 5; ++v) X[b][v] = Qc[v * nd];
 
-  auto grad_flux = [&](const double q[5], double F[3][5], double& Sw) {
+  // gradients of one level: its slice to LDS for y, x and z in registers
+  auto gradients = [&](const double q[5], double g[3][5]) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) sq[v * nd + r] = q[v];
     wave_sync();
-    double g[3][5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      g[0][v] = cx4(Cx, q[v]);
-      g[1][v] = cy4(Cy, q[v]);
-      g[2][v] = cz4(Cz, sq + v * nd, ji);
+      g[0][v] = mm4(mm4(q[v], one, 0.0), D.T, 0.0);
+      g[2][v] = mm4(D.T, q[v], 0.0);
+      const double* s = sq + v * nd;
+      g[1][v] = fma(D.y[3], s[y3], fma(D.y[2], s[y2], fma(D.y[1], s[y1], D.y[0] * q[v])));
     }
-    flux_source3(ph, q, g, z, rb, pb, mu_h, kappa_h, gh, F, Sw);
   };
 
   for (int it = 0; it < a.iters; ++it) {
@@ -440,19 +455,29 @@ __global__ __launch_bounds__(kThreads3, 3) void k_pred3_w64(Phys ph, Tab<4> tb, 
         for (int v = 0; v < 5; ++v) X[b][v] = X[0][v];
         continue;
       }
-      double F[3][5], Sw;
-      grad_flux(X[b], F, Sw);
+      double g[3][5], F[3][4];
+      gradients(X[b], g);
+      flux_xyz(fc, X[b], g, F);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) sF[v * nd + r] = F[2][v];
+      for (int v = 0; v < 4; ++v) sF[v * nd + r] = F[1][v];
       wave_sync();
-      // the residual of time level b (times dt) replaces its iterate
+      // the residual of time level b (times -h) replaces its iterate; the
+      // mass flux is the momentum, its divergence a sum of gradients
+      const double src = fc.gh * (X[b][0] - rb);
+      X[b][0] = (g[0][1] + g[1][2]) + g[2][3];
 #pragma unroll
-      for (int v = 0; v < 5; ++v)
-        X[b][v] = sdt * (cx4(Cx, F[0][v]) + cy4(Cy, F[1][v]) + cz4(Cz, sF + v * nd, ji));
-      X[b][3] = fma(dt, Sw, X[b][3]);
+      for (int v = 0; v < 4; ++v) {
+        const double* s = sF + v * nd;
+        double acc = mm4(D.T, F[2][v], mm4(mm4(F[0][v], one, 0.0), D.T, 0.0));
+        acc = fma(D.y[0], F[1][v], acc);
+        acc = fma(D.y[1], s[y1], acc);
+        acc = fma(D.y[2], s[y2], acc);
+        acc = fma(D.y[3], s[y3], acc);
+        X[b][1 + v] = v == 2 ? acc + src : acc;
+      }
       wave_sync();
     }
-    // X <- Q + K1^{-1} W X: in-place solve with the unpivoted LU factors
+    // X <- Q - (dt/h) K1^{-1} W X: in-place solve with the unpivoted LU factors
     const double* lu = a.gtab + GTab::lu(n);
     int o = 0;
 #pragma unroll
@@ -476,57 +501,94 @@ __global__ __launch_bounds__(kThreads3, 3) void k_pred3_w64(Phys ph, Tab<4> tb, 
         for (int v = 0; v < 5; ++v) X[ii][v] = fma(-u, X[jj][v], X[ii][v]);
       }
     }
+    const double sdt = -dt * ih;
 #pragma unroll
-    for (int a2 = 0; a2 < n; ++a2)
+    for (int v = 0; v < 5; ++v) {
+      const double q0 = Qc[v * nd];
 #pragma unroll
-      for (int v = 0; v < 5; ++v) X[a2][v] += Q0[v];
+      for (int a2 = 0; a2 < n; ++a2) X[a2][v] = fma(sdt, X[a2][v], q0);
+    }
   }
 
   // time averages; the averaged fluxes accumulate in the lane's own LDS
   // words [3][5][nd] (registers are short here), the state in registers
-  double Qb[5], Sb = 0.0;
+  double Qb[5];
 #pragma unroll
   for (int v = 0; v < 5; ++v) Qb[v] = 0.0;
 #pragma unroll
   for (int b = 0; b < n; ++b) {
-    double F[3][5], Sw;
-    grad_flux(X[b], F, Sw);
+    double g[3][5], F[3][4];
+    gradients(X[b], g);
+    flux_xyz(fc, X[b], g, F);
     const double w = tb.w[b];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      Qb[v] = fma(w, X[b][v], Qb[v]);
+    for (int v = 0; v < 5; ++v) Qb[v] = fma(w, X[b][v], Qb[v]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        double* acc = sF + (d * 5 + v) * nd + r;
+        double* acc = sF + (d * 5 + 1 + v) * nd + r;
         *acc = b == 0 ? w * F[d][v] : fma(w, F[d][v], *acc);
       }
-    }
-    Sb = fma(w, Sw, Sb);
     wave_sync();
   }
 #pragma unroll
   for (int v = 0; v < 5; ++v) sq[v * nd + r] = Qb[v];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) sF[d * 5 * nd + r] = Qb[1 + d];
+  const double Sb = -ph.geff * (Qb[0] - rb);
   wave_sync();
 
   // Lane indices and cell again from the thread id: kept live across the
   // sweeps they would occupy registers that the sweeps need (and spill).
   int t2 = threadIdx.x;
   asm volatile("" : "+v"(t2));
-  const int r2 = t2 & 63, i2 = r2 & 3, j2 = (r2 >> 2) & 3, k2 = r2 >> 4;
-  const int cell2 = blockIdx.x * (kThreads3 / kWave) + (t2 >> 6);
-  // volume term with the weighted transposed derivative matrix, and Q*
-  double Wx[4], Wy[4], Wz[4];
-  rot_rows4(a.gtab + GTab::dw(n), i2, j2, k2, Wx, Wy, Wz);
-  const double ih = 1.0 / h;
-  if (cell2 < a.C) {
-    double* Qsc = a.Qs + (size_t)cell2 * 5 * nd;
+  const int r2 = t2 & 63;
+  const int cell2 = blockIdx.x * kW64Cells + (t2 >> 6);
+  // Volume term with the weighted transposed derivative matrix, and the face
+  // data: the values at both ends of a line are a product with the two rows
+  // e0, e1 (lanes with k = 0 and 1 hold the lower and the upper face's nodes);
+  // along y from LDS.
+  const int lo2 = r2 & 3, j2 = (r2 >> 2) & 3, k2 = r2 >> 4;
+  const Tab4 W = tab4(a.gtab + GTab::dw(n), r2);
+  const double one2 = lo2 == k2 ? 1.0 : 0.0;
+  const double E = lo2 < 2 ? a.gtab[(lo2 == 0 ? GTab::E0 : GTab::E1) * n + k2] : 0.0;
+  const bool ok = cell2 < a.C;
+  double* FDc = a.FD + (size_t)(ok ? cell2 : 0) * 60 * 16;
+  double* Qsc = a.Qs + (size_t)(ok ? cell2 : 0) * 5 * nd;
+  const double* Q2 = a.Q + (size_t)(ok ? cell2 : 0) * 5 * nd;
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      const double vol = cx4(Wx, sF[v * nd + r2]) + cy4(Wy, sF[(5 + v) * nd + r2]) +
-                         cz4(Wz, sF + (10 + v) * nd, r2 & 15);
-      Qsc[v * nd + r2] = Q0[v] + dt * (vol * ih + (v == 3 ? Sb : 0.0));
+  for (int v = 0; v < 5; ++v) {
+    const double q = sq[v * nd + r2], fx = sF[v * nd + r2], fy = sF[(5 + v) * nd + r2], fz = sF[(10 + v) * nd + r2];
+    const double qt = mm4(q, one2, 0.0), fxt = mm4(fx, one2, 0.0);   // x and z exchanged
+    double acc = mm4(W.T, fz, mm4(fxt, W.T, 0.0));
+    const double* s = sF + (5 + v) * nd;
+    acc = fma(W.y[0], fy, acc);
+#pragma unroll
+    for (int m = 1; m < 4; ++m) acc = fma(W.y[m], s[step_y(r2, m)], acc);
+    const double xq = mm4(E, qt, 0.0), xf = mm4(E, fxt, 0.0), zq = mm4(E, q, 0.0), zf = mm4(E, fz, 0.0);
+    if (ok) {
+      Qsc[v * nd + r2] = fma(dt, fma(acc, ih, v == 3 ? Sb : 0.0), Q2[v * nd + r2]);
+      if (k2 < 2) {
+        double* fx0 = FDc + (k2 * 10 + v) * 16 + lo2 * 4 + j2;        // faces 0, 1: nodes (z, y)
+        fx0[0] = xq;
+        fx0[5 * 16] = xf;
+        double* fz0 = FDc + ((4 + k2) * 10 + v) * 16 + j2 * 4 + lo2;  // faces 4, 5: nodes (y, x)
+        fz0[0] = zq;
+        fz0[5 * 16] = zf;
+      }
     }
-    face_data3<n>(tb, sq, sF, a.FD + (size_t)cell2 * 60 * 16, r2);
+  }
+  // faces 2, 3: nodes (z, x), 20 lines of 16 nodes
+#pragma unroll
+  for (int it = 0; it < 5; ++it) {
+    const int q = it * 4 + k2, hi = q >= 10, kv = hi ? q - 10 : q;   // face, (kind, variable)
+    const int st = r2 & 15, zz = st >> 2, xx = st & 3;
+    const double* s = (kv < 5 ? sq + kv * nd : sF + kv * nd) + zz * 16 + xx;
+    double acc = 0.0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc = fma(a.gtab[(hi ? GTab::E1 : GTab::E0) * n + m], s[4 * m], acc);
+    if (ok) FDc[(size_t)((2 + hi) * 10 + kv) * 16 + st] = acc;
   }
 }
 
@@ -745,7 +807,8 @@ static int pred3_n(const Phys& ph, const HostBasis& B, const Args3& a, hipStream
   const int blocks = (a.C + G::CB - 1) / G::CB;
   const size_t lds = sizeof(double) * (size_t)G::CB * G::pred_slot;
   if constexpr (n == 4)
-    hipLaunchKernelGGL(k_pred3_w64, dim3(blocks), dim3(kThreads3), lds, s, ph, tab_of<n>(B), a);
+    hipLaunchKernelGGL(k_pred3_w64, dim3((a.C + kW64Cells - 1) / kW64Cells), dim3(kWave * kW64Cells),
+                       sizeof(double) * kW64Cells * 20 * 64, s, ph, tab_of<n>(B), a);
   else
     hipLaunchKernelGGL(k_pred3<n>, dim3(blocks), dim3(kThreads3), lds, s, ph, tab_of<n>(B), a);
   return check_launch("predictor3");
@@ -787,6 +850,11 @@ int launch_corr3(const Phys& ph, int n, const Args3& a, hipStream_t s) {
 int launch_dt3(const Phys& ph, int n, const Args3& a, hipStream_t s) {
   if (a.C == 0) return ADG_OK;
   ADG3_DISPATCH(dt3_n, n, ph, a, s);
+}
+int launch_background3(const Phys& ph, int n, const Args3& a, double* bg, hipStream_t s) {
+  const long long tot = (long long)a.nz * n;
+  hipLaunchKernelGGL(k_background3, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, ph, a, n, bg);
+  return check_launch("background3");
 }
 int launch_init3(const Phys& ph, int n, const Args3& a, int kind, const Bubbles3& B, double t0, double* Q,
                  hipStream_t s) {
