@@ -36,52 +36,6 @@
 
 namespace adg {
 
-// A wavefront-uniform table read through scalar loads (opaque, so that the
-// entries are loaded where they are used instead of being held).
-typedef const __attribute__((address_space(4))) double* ctab;
-__device__ inline ctab scalar_table(const double* g) {
-  asm volatile("" : "+s"(g));
-  return (ctab)g;
-}
-
-// out = T in for a centro-antisymmetric T in even-odd form (layout with
-// GTab): 36 operations instead of 49 at n = 7.
-template <int n>
-struct EO {
-  static constexpr int h = n / 2, mid = (n - 1) / 2;
-  double A[h][h], B[h][h], C[h], M[h];
-  __device__ explicit EO(ctab g) {
-#pragma unroll
-    for (int i = 0; i < h; ++i) {
-#pragma unroll
-      for (int m = 0; m < h; ++m) { A[i][m] = g[i * h + m]; B[i][m] = g[h * h + i * h + m]; }
-      C[i] = n % 2 ? g[2 * h * h + i] : 0.0;
-      M[i] = n % 2 ? g[2 * h * h + h + i] : 0.0;
-    }
-  }
-  __device__ inline void apply(const double in[n], double out[n]) const {
-    double e[h], o[h];
-#pragma unroll
-    for (int m = 0; m < h; ++m) { e[m] = in[m] + in[n - 1 - m]; o[m] = in[m] - in[n - 1 - m]; }
-    double mv = in[mid];
-    if constexpr (n % 2) {
-      double S = M[0] * o[0];
-#pragma unroll
-      for (int m = 1; m < h; ++m) S = fma(M[m], o[m], S);
-      out[mid] = S;
-    }
-#pragma unroll
-    for (int i = 0; i < h; ++i) {
-      double S = A[i][0] * o[0], U = B[i][0] * e[0];
-#pragma unroll
-      for (int m = 1; m < h; ++m) { S = fma(A[i][m], o[m], S); U = fma(B[i][m], e[m], U); }
-      if constexpr (n % 2) U = fma(C[i], mv, U);
-      out[i] = S + U;
-      out[n - 1 - i] = S - U;
-    }
-  }
-};
-
 // Per-launch and per-cell constants of the flux.
 struct FluxC {
   double gm1, hgm1, mu, mu23, kap, gh;   // gm1, gm1/2, mu/h, (2/3) mu/h, kappa/(h R), g h

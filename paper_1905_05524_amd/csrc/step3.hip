@@ -4,7 +4,7 @@
 // states and the health check.
 //
 // Work decomposition of the corrector, the time step and the predictor of
-// orders other than N = 3.  A workgroup of kThreads3 threads holds CB cells; the
+// N = 1 and 2.  A workgroup of kThreads3 threads holds CB cells; the
 // thread t owns spatial node t % nd (nd = n^3) of cell slot t / nd, so a
 // cell's nodes are consecutive lanes.  For n = 2 and n = 4 every cell lies in
 // one wavefront and the LDS hand-offs between its nodes need only a
@@ -15,8 +15,10 @@
 // Tensor-product contractions along x, y and z read n values of an LDS slice
 // per output; the space-time iterate of a node (n time levels x 5 variables)
 // stays in registers.  The predictor of N = 3 (k_pred3_w64) keeps that layout
-// with one wavefront per cell and contracts with matrix instructions.
+// with one wavefront per cell and contracts with matrix instructions; those of
+// N = 4 and 5 (k_pred3_rows) work on all time levels at once.
 #include "adg3_internal.h"
+#include "step_internal.h"
 
 namespace adg {
 
@@ -362,6 +364,34 @@ __global__ __launch_bounds__(kThreads3) void k_pred3(Phys ph, Tab<n> tb, Args3 a
   }
 }
 
+// X <- K1^{-1} W X over the time levels: in-place solve with the unpivoted LU
+// factors, the weights folded into them
+template <int n>
+__device__ inline void solve_time(const double* lu, double X[n][5]) {
+  int o = 0;
+#pragma unroll
+  for (int ii = 1; ii < n; ++ii) {
+#pragma unroll
+    for (int jj = 0; jj < ii; ++jj) {
+      const double l = lu[o++];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) X[ii][v] = fma(-l, X[jj][v], X[ii][v]);
+    }
+  }
+#pragma unroll
+  for (int ii = n - 1; ii >= 0; --ii) {
+    const double iu = lu[o++];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) X[ii][v] *= iu;
+#pragma unroll
+    for (int jj = ii + 1; jj < n; ++jj) {
+      const double u = lu[o++];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) X[ii][v] = fma(-u, X[jj][v], X[ii][v]);
+    }
+  }
+}
+
 // ------------------------------------------------ predictor, n = 4 (N = 3)
 // One cell per wavefront, lane l = 16 k + 4 j + i, the four time levels of a
 // node in registers.  Lines of four nodes are what one 4 x 4 x 4 matrix
@@ -477,30 +507,8 @@ __global__ __launch_bounds__(kWave * kW64Cells, 3) void k_pred3_w64(Phys ph, Tab
       }
       wave_sync();
     }
-    // X <- Q - (dt/h) K1^{-1} W X: in-place solve with the unpivoted LU factors
-    const double* lu = a.gtab + GTab::lu(n);
-    int o = 0;
-#pragma unroll
-    for (int ii = 1; ii < n; ++ii) {
-#pragma unroll
-      for (int jj = 0; jj < ii; ++jj) {
-        const double l = lu[o++];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) X[ii][v] = fma(-l, X[jj][v], X[ii][v]);
-      }
-    }
-#pragma unroll
-    for (int ii = n - 1; ii >= 0; --ii) {
-      const double iu = lu[o++];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) X[ii][v] *= iu;
-#pragma unroll
-      for (int jj = ii + 1; jj < n; ++jj) {
-        const double u = lu[o++];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) X[ii][v] = fma(-u, X[jj][v], X[ii][v]);
-      }
-    }
+    // X <- Q - (dt/h) K1^{-1} W X
+    solve_time<n>(a.gtab + GTab::lu(n), X);
     const double sdt = -dt * ih;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
@@ -589,6 +597,305 @@ __global__ __launch_bounds__(kWave * kW64Cells, 3) void k_pred3_w64(Phys ph, Tab
 #pragma unroll
     for (int m = 0; m < 4; ++m) acc = fma(a.gtab[(hi ? GTab::E1 : GTab::E0) * n + m], s[4 * m], acc);
     if (ok) FDc[(size_t)((2 + hi) * 10 + kv) * 16 + st] = acc;
+  }
+}
+
+// ------------------------------------------- predictor, n = 5 and 6
+// One cell per workgroup, all time levels at once, the iterate in LDS, and
+// every contraction along lines that one lane holds in registers.  The threads
+// change between three roles, with a barrier between them:
+//   nodes   (k, j, i): all levels of one node, for the time solve;
+//   rows    (level, k, j): a line of nodes along x, for the x contractions
+//           and the flux;
+//   planes  (level, variable, i): the nodes of one variable at one x, for the
+//           y and z contractions.
+// Two slices of five variables serve the exchanges: A holds the iterate, then
+// the y gradients, the y fluxes, their sum of divergences, the residual; B the
+// z gradients, then the z fluxes.  Reads and writes of one node and level: 37
+// and 32 doubles per sweep, where k_pred3's 150 and 20 kept the LDS busy.
+// Bound by latency: LDS 40 and vector units 34 per cent busy with the six
+// wavefronts that 50 kB per cell admit at n = 5 (one slice only, with more
+// held in registers, spills: 384 us).  13^3 cells of N = 4: 153 us, 255 us
+// with k_pred3; 9^3 of N = 5: 177, 245; one round of cells (5^3 of N = 4,
+// 3^3 of N = 5): 35 and 60, 52 and 82.  At n = 3 and 2 k_pred3 is the faster
+// (27^3 of N = 2 122, 135; 40^3 of N = 1 64, 112): its lines are short.
+template <int n>
+struct Rows3 {
+  static constexpr int nn = n * n, nd = nn * n;
+  static constexpr int NT = (nd + kWave - 1) / kWave * kWave;   // threads
+  // strides of level, k, j, i and variable: free of bank conflicts for rows
+  // and, at n = 5, nodes; planes at most 1.5 times the time without conflicts
+  static constexpr int SB = n == 6 ? 36 : nd, SK = n == 6 ? 6 : nn, SJ = n == 6 ? 1 : n, SI = n == 6 ? 217 : 1;
+  static constexpr int VS = n == 6 ? 1302 : 629;
+  static constexpr int B = 5 * VS;                              // slice B behind slice A
+  static constexpr int size = 10 * VS;
+  static_assert((n - 1) * (SB + SK + SJ + SI) < VS && 20 * nd <= size && 5 * nn <= NT, "layout");
+};
+
+template <int n>
+__global__ __launch_bounds__(Rows3<n>::NT, n == 6 ? 1 : 2) void k_pred3_rows(Phys ph, Tab<n> tb, Args3 a) {
+  using L = Rows3<n>;
+  constexpr int nn = L::nn, nd = L::nd, VS = L::VS, B = L::B;
+  extern __shared__ double lds[];
+  const int tid = threadIdx.x, c = blockIdx.x, layer = c / (a.nx * a.ny);
+  const double h = a.h, dt = a.clock[1], ih = 1.0 / h;
+
+  // nodes; threads past the last read another node's words and write nothing
+  const bool tact = tid < nd;
+  const int r = tact ? tid : 0;
+  const int i = r % n, j = (r / n) % n, k = r / nn;
+  double* tp = lds + k * L::SK + j * L::SJ + i * L::SI;
+  // rows
+  const int xb = tid / nn, xk = (tid / n) % n, xj = tid % n;
+  double* xp = lds + xb * L::SB + xk * L::SK + xj * L::SJ;
+  FluxC3 fc = flux_consts3(ph, h);
+  fc.gz = ph.geff * ((a.z0 + layer * h) + h * a.gtab[GTab::XI * n + xk]);
+  const double rb = a.bg[2 * (layer * n + xk)];
+  fc.pb = a.bg[2 * (layer * n + xk) + 1];
+  // planes: of all variables, and of the four with a flux to contract
+  const int pb5 = tid / (5 * n), pb4 = tid / (4 * n);
+  double* p5 = lds + pb5 * L::SB + (tid / n) % 5 * VS + tid % n * L::SI;
+  double* p4 = lds + pb4 * L::SB + ((tid / n) % 4 + 1) * VS + tid % n * L::SI;
+
+  const double* Qc = a.Q + (size_t)c * 5 * nd + r;
+  double X[n][5];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    X[0][v] = Qc[v * nd];
+#pragma unroll
+    for (int b = 1; b < n; ++b) X[b][v] = X[0][v];
+  }
+
+  // Gradients of lv levels, from the iterate in A: along x in gx, y in A, z in
+  // B.  q is the row's state.
+  auto gradients = [&](int lv, bool xact, double q[5][n], double gx[5][n]) {
+    __syncthreads();
+    if (xact) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v)
+#pragma unroll
+        for (int m = 0; m < n; ++m) q[v][m] = xp[v * VS + m * L::SI];
+    }
+    __syncthreads();
+    const EO<n> eo(scalar_table(a.gtab + GTab::eo_d(n)));
+    if (pb5 < lv) {
+      double in[n][n];
+#pragma unroll
+      for (int z = 0; z < n; ++z)
+#pragma unroll
+        for (int y = 0; y < n; ++y) in[z][y] = p5[z * L::SK + y * L::SJ];
+#pragma unroll
+      for (int z = 0; z < n; ++z) {
+        double out[n];
+        eo.apply(in[z], out);
+#pragma unroll
+        for (int y = 0; y < n; ++y) p5[z * L::SK + y * L::SJ] = out[y];
+      }
+#pragma unroll
+      for (int y = 0; y < n; ++y) {
+        double col[n], out[n];
+#pragma unroll
+        for (int z = 0; z < n; ++z) col[z] = in[z][y];
+        eo.apply(col, out);
+#pragma unroll
+        for (int z = 0; z < n; ++z) p5[B + z * L::SK + y * L::SJ] = out[z];
+      }
+    }
+    if (xact) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) eo.apply(q[v], gx[v]);
+    }
+    __syncthreads();
+  };
+  // state and gradients of node m of the row
+  auto node_flux = [&](int m, const double q[5][n], const double gx[5][n], double g[3][5], double F[3][4]) {
+    double qm[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      qm[v] = q[v][m];
+      g[0][v] = gx[v][m];
+      g[1][v] = xp[v * VS + m * L::SI];
+      g[2][v] = xp[B + v * VS + m * L::SI];
+    }
+    flux_xyz(fc, qm, g, F);
+  };
+
+  for (int it = 0; it < a.iters; ++it) {
+    // the first sweep starts from Q^n at every time level: all levels share
+    // level 0's residual (bit for bit)
+    const int lv = it ? n : 1;
+    const bool xact = xb < lv;
+    if (tact) {
+#pragma unroll
+      for (int b = 0; b < n; ++b)
+        if (b < lv) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) tp[v * VS + b * L::SB] = X[b][v];
+        }
+    }
+    double q[5][n], R[5][n];
+    {
+      double gx[5][n];
+      gradients(lv, xact, q, gx);
+      if (xact) {
+        double Fx[4][n];
+#pragma unroll
+        for (int m = 0; m < n; ++m) {
+          double g[3][5], F[3][4];
+          node_flux(m, q, gx, g, F);
+          // the mass flux is the momentum, its divergence a sum of gradients
+          R[0][m] = (g[0][1] + g[1][2]) + g[2][3];
+          R[3][m] = fc.gh * (q[0][m] - rb);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            Fx[v][m] = F[0][v];
+            xp[(1 + v) * VS + m * L::SI] = F[1][v];
+            xp[B + (1 + v) * VS + m * L::SI] = F[2][v];
+          }
+        }
+        const EO<n> eo(scalar_table(a.gtab + GTab::eo_d(n)));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double out[n];
+          eo.apply(Fx[v], out);
+#pragma unroll
+          for (int m = 0; m < n; ++m) R[1 + v][m] = v == 2 ? R[3][m] + out[m] : out[m];
+        }
+      }
+    }
+    __syncthreads();
+    {
+      const EO<n> eo(scalar_table(a.gtab + GTab::eo_d(n)));
+      if (pb4 < lv) {
+        double S[n][n];
+#pragma unroll
+        for (int y = 0; y < n; ++y) {
+          double col[n], out[n];
+#pragma unroll
+          for (int z = 0; z < n; ++z) col[z] = p4[B + z * L::SK + y * L::SJ];
+          eo.apply(col, out);
+#pragma unroll
+          for (int z = 0; z < n; ++z) S[z][y] = out[z];
+        }
+#pragma unroll
+        for (int z = 0; z < n; ++z) {
+          double in[n], out[n];
+#pragma unroll
+          for (int y = 0; y < n; ++y) in[y] = p4[z * L::SK + y * L::SJ];
+          eo.apply(in, out);
+#pragma unroll
+          for (int y = 0; y < n; ++y) p4[z * L::SK + y * L::SJ] = S[z][y] + out[y];
+        }
+      }
+    }
+    __syncthreads();
+    if (xact) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        xp[m * L::SI] = R[0][m];
+#pragma unroll
+        for (int v = 1; v < 5; ++v) xp[v * VS + m * L::SI] += R[v][m];
+      }
+    }
+    __syncthreads();
+    // (no condition on the thread: no iterate has to be kept across the sweep)
+#pragma unroll
+    for (int b = 0; b < n; ++b)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) X[b][v] = tp[v * VS + (it ? b * L::SB : 0)];
+    solve_time<n>(a.gtab + GTab::lu(n), X);
+    const double sdt = -dt * ih;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      const double q0 = Qc[v * nd];
+#pragma unroll
+      for (int b = 0; b < n; ++b) X[b][v] = fma(sdt, X[b][v], q0);
+    }
+  }
+
+  // time averages: x and y fluxes of the levels through A and B, then the z ones
+  double Qb[5], Fb[3][4];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    Qb[v] = 0.0;
+#pragma unroll
+    for (int b = 0; b < n; ++b) Qb[v] = fma(tb.w[b], X[b][v], Qb[v]);
+  }
+  if (tact) {
+#pragma unroll
+    for (int b = 0; b < n; ++b)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) tp[v * VS + b * L::SB] = X[b][v];
+  }
+  {
+    const bool xact = xb < n;
+    double q[5][n], gx[5][n], Fz[4][n];
+    gradients(n, xact, q, gx);
+    if (xact) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        double g[3][5], F[3][4];
+        node_flux(m, q, gx, g, F);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          xp[(1 + v) * VS + m * L::SI] = F[0][v];
+          xp[B + (1 + v) * VS + m * L::SI] = F[1][v];
+          Fz[v][m] = F[2][v];
+        }
+      }
+    }
+    auto average = [&](int d, const double* p) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double s = tb.w[0] * p[(1 + v) * VS];
+#pragma unroll
+        for (int b = 1; b < n; ++b) s = fma(tb.w[b], p[(1 + v) * VS + b * L::SB], s);
+        Fb[d][v] = s;
+      }
+    };
+    __syncthreads();
+    average(0, tp);
+    average(1, tp + B);
+    __syncthreads();
+    if (xact) {
+#pragma unroll
+      for (int m = 0; m < n; ++m)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) xp[(1 + v) * VS + m * L::SI] = Fz[v][m];
+    }
+    __syncthreads();
+    average(2, tp);
+  }
+  __syncthreads();
+  double* sF = lds + 5 * nd;   // averaged state [5][nd] and fluxes [3][5][nd]
+  if (tact) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) lds[v * nd + r] = Qb[v];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      sF[d * 5 * nd + r] = Qb[1 + d];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sF[(d * 5 + 1 + v) * nd + r] = Fb[d][v];
+    }
+  }
+  __syncthreads();
+  if (tact) {
+    // volume term (Dw[i][m] = w_m D[m][i] / w_i along each direction) and Q*
+    double Wi[n], Wj[n], Wk[n];
+#pragma unroll
+    for (int m = 0; m < n; ++m) {
+      Wi[m] = a.gtab[GTab::dw(n) + i * n + m];
+      Wj[m] = a.gtab[GTab::dw(n) + j * n + m];
+      Wk[m] = a.gtab[GTab::dw(n) + k * n + m];
+    }
+    const double Sb = -ph.geff * (Qb[0] - a.bg[2 * (layer * n + k)]);
+    double* Qsc = a.Qs + (size_t)c * 5 * nd + r;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      const double vol = div3<n>(sF, v, i, j, k, Wi, Wj, Wk);
+      Qsc[v * nd] = fma(dt, fma(vol, ih, v == 3 ? Sb : 0.0), Qc[v * nd]);
+    }
+    face_data3<n>(tb, lds, sF, a.FD + (size_t)c * 60 * nn, r);
   }
 }
 
@@ -809,6 +1116,9 @@ static int pred3_n(const Phys& ph, const HostBasis& B, const Args3& a, hipStream
   if constexpr (n == 4)
     hipLaunchKernelGGL(k_pred3_w64, dim3((a.C + kW64Cells - 1) / kW64Cells), dim3(kWave * kW64Cells),
                        sizeof(double) * kW64Cells * 20 * 64, s, ph, tab_of<n>(B), a);
+  else if constexpr (n > 4)
+    hipLaunchKernelGGL(k_pred3_rows<n>, dim3(a.C), dim3(Rows3<n>::NT), sizeof(double) * Rows3<n>::size, s, ph,
+                       tab_of<n>(B), a);
   else
     hipLaunchKernelGGL(k_pred3<n>, dim3(blocks), dim3(kThreads3), lds, s, ph, tab_of<n>(B), a);
   return check_launch("predictor3");
