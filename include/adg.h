@@ -254,8 +254,8 @@ int adg_autotune(adg_mesh* m, int reps, void* stream, int* cells_per_wave, int* 
  * nodes in the order (lower side nodes 0..n-1, upper side nodes 0..n-1);
  * d|x|/dx = 0 at x = 0. */
 
-/* Size of the adjoint workspace (Picard iterate store of one step, face
- * adjoints, loss partials). */
+/* Size of the adjoint workspace (Picard iterate store of one step, loss
+ * partials). */
 int adg_adjoint_workspace_bytes(const adg_mesh* m, size_t* bytes);
 
 /* lam_n = (dQ^{n+1}/dQ^n)^T lam_np1 for the step that starts from the

@@ -6,17 +6,17 @@
 // Its adjoint maps lambda^{n+1} = dL/dQ^{n+1} to lambda^n = dL/dQ^n:
 //   1. the forward predictor is recomputed from the checkpoint Q^n, storing
 //      the Picard iterates (iterate store);
-//   2. lifting adjoint: per cell and face, the face-flux adjoint of this
-//      cell's half of the surface integral;
-//   3. face adjoint: per face, both halves summed, then the reverse of the
-//      Rusanov flux (and of a wall ghost) onto this cell's face data;
+//   2. lifting adjoint: per cell and face, the face-flux adjoint of both
+//      cells' halves of the surface integral;
+//   3. face adjoint: per face, the reverse of the Rusanov flux (and of a wall
+//      ghost) onto this cell's face data;
 //      non-smooth points take the subgradient of the first maximum in the
 //      scan order (side L nodes 0..n-1, then side R), and d|x|/dx = 0 at 0;
 //   4. reverse predictor: face extrapolations, volume term and time
 //      averages, then the Picard sweeps in reverse order (R = S - div F:
 //      transposed derivative contractions and the reverse of the pointwise
 //      flux), accumulating dL/dQ^n.
-#include "adg_internal.h"
+#include "step_internal.h"
 
 namespace adg {
 
@@ -27,179 +27,60 @@ __device__ inline void wave_sync_a() {
 }
 
 // --------------------------------------------------------- pointwise VJP
-// Reverse of the predictor's flux and gravity source at one node: given
-// adjoints aFx, aFz of the fluxes and aSw of the source, returns the adjoints
-// of the state and its (physical) gradients.
-__device__ inline void flux_source_vjp(const Phys& ph, const double q[4], const double gx[4],
-                                       const double gz[4], double z, double rb, const double aFx[4],
-                                       const double aFz[4], double aSw, double aq[4], double agx[4],
-                                       double agz[4]) {
-  (void)rb;
-  // forward intermediates
+// Reverse of the predictor's fluxes at one node.  q: state; gx, gz: gradients
+// in reference coordinates; aFx, aFz: adjoints of the fluxes.  Returns the
+// adjoints of the state and of the gradients.  Notation and constants are
+// those of the forward flux: a = rho du/dx and so on, so that the stresses
+// and the conductivity are proportional to 1/rho and their share of the
+// density's adjoint is one sum.
+__device__ inline void flux_vjp(const FluxC& c, const double q[4], const double gx[4], const double gz[4],
+                                const double aFx[4], const double aFz[4], double aq[4], double agx[4], double agz[4]) {
+  // forward
   const double rho = q[0], mx = q[1], mz = q[2], E = q[3];
-  const double ir = 1.0 / rho;
+  const double ir = recip(rho);
   const double u = mx * ir, w = mz * ir;
-  const double gzz = ph.gravity ? ph.g * z : 0.0;
-  const double p = ph.gm1 * (E - 0.5 * (mx * u + mz * w) - rho * gzz);
-  const double T = p * ir * ph.iR;
-  const double dux = (gx[1] - u * gx[0]) * ir, duz = (gz[1] - u * gz[0]) * ir;
-  const double dwx = (gx[2] - w * gx[0]) * ir, dwz = (gz[2] - w * gz[0]) * ir;
-  const double hv2 = 0.5 * (u * u + w * w) + gzz;
-  const double dpx = ph.gm1 * (gx[3] - hv2 * gx[0] - rho * (u * dux + w * dwx));
-  double dpz = ph.gm1 * (gz[3] - hv2 * gz[0] - rho * (u * duz + w * dwz));
-  if (ph.gravity) dpz -= ph.gm1 * rho * ph.g;
-  const double div = dux + dwz;
-  const double sxx = ph.mu * ((2.0 / 3.0) * div - 2.0 * dux);
-  const double szz = ph.mu * ((2.0 / 3.0) * div - 2.0 * dwz);
-  const double sxz = -ph.mu * (duz + dwx);
+  const double ke = fma(mx, u, mz * w);
+  const double p = fma(-c.hgm1, ke, c.gm1 * fma(-c.gz, rho, E));
+  const double pir = p * ir;
+  const double ax = fma(-u, gx[0], gx[1]), az = fma(-u, gz[0], gz[1]);
+  const double cx = fma(-w, gx[0], gx[2]), cz = fma(-w, gz[0], gz[2]);
+  const double kin = 0.5 * ir * ke, hv = kin + c.gz;
+  const double dx = fma(-w, cx, fma(-u, ax, fma(-hv, gx[0], gx[3])));
+  const double dz = fma(-c.gh, rho, fma(-w, cz, fma(-u, az, fma(-hv, gz[0], gz[3]))));
+  const double m23 = c.mu23 * ir, mi = c.mu * ir, k = c.kap * ir;
+  const double sxx = m23 * fma(-2.0, ax, cz), szz = m23 * fma(-2.0, cz, ax), sxz = -mi * (az + cx);
+  const double qx = fma(-pir, gx[0], c.gm1 * dx), qz = fma(-pir, gz[0], c.gm1 * dz);
   const double H = E + p;
-  // reverse sweep
-  double brho = 0, bmx = 0, bmz = 0, bE = 0;
-  double bu = 0, bw = 0, bH = 0, bpm = 0, bsxx = 0, bszz = 0, bsxz = 0, bdTx = 0, bdTz = 0;
-  for (int v = 0; v < 4; ++v) { agx[v] = 0.0; agz[v] = 0.0; }
-  if (ph.gravity) brho += -ph.g * aSw;
-  // Fz3 = w H + u sxz + w szz - kappa dTz
-  bw += aFz[3] * (H + szz); bH += aFz[3] * w; bu += aFz[3] * sxz; bsxz += aFz[3] * u; bszz += aFz[3] * w;
-  bdTz += -ph.kappa * aFz[3];
-  // Fz2 = mz w + pm + szz
-  bmz += aFz[2] * w; bw += aFz[2] * mz; bpm += aFz[2]; bszz += aFz[2];
-  // Fz1 = mx w + sxz
-  bmx += aFz[1] * w; bw += aFz[1] * mx; bsxz += aFz[1];
-  // Fz0 = mz
-  bmz += aFz[0];
-  // Fx3 = u H + u sxx + w sxz - kappa dTx
-  bu += aFx[3] * (H + sxx); bH += aFx[3] * u; bsxx += aFx[3] * u; bw += aFx[3] * sxz; bsxz += aFx[3] * w;
-  bdTx += -ph.kappa * aFx[3];
-  // Fx2 = mz u + sxz
-  bmz += aFx[2] * u; bu += aFx[2] * mz; bsxz += aFx[2];
-  // Fx1 = mx u + pm + sxx
-  bmx += aFx[1] * u; bu += aFx[1] * mx; bpm += aFx[1]; bsxx += aFx[1];
-  // Fx0 = mx
-  bmx += aFx[0];
-  // H = E + p
-  bE += bH;
-  double bp = bH;
-  // sxz = -mu (duz + dwx)
-  double bduz = -ph.mu * bsxz, bdwx = -ph.mu * bsxz;
-  // szz = mu (2/3 div - 2 dwz), sxx = mu (2/3 div - 2 dux)
-  double bdiv = ph.mu * (2.0 / 3.0) * (bszz + bsxx);
-  double bdwz = -2.0 * ph.mu * bszz, bdux = -2.0 * ph.mu * bsxx;
-  // div = dux + dwz
-  bdux += bdiv; bdwz += bdiv;
-  // dTz = (dpz - R T gz0) ir iR ; dTx likewise
-  const double c_ = ir * ph.iR;
-  double bdpz = bdTz * c_, bdpx = bdTx * c_;
-  double bT = -ph.R * (gz[0] * bdTz + gx[0] * bdTx) * c_;
-  agz[0] += -ph.R * T * bdTz * c_;
-  agx[0] += -ph.R * T * bdTx * c_;
-  double bir = (bdTz * (dpz - ph.R * T * gz[0]) + bdTx * (dpx - ph.R * T * gx[0])) * ph.iR;
-  // dpz = gm1 (gz3 - hv2 gz0 - rho (u duz + w dwz)) - [grav] gm1 rho g
-  double t = bdpz * ph.gm1;
-  agz[3] += t;
-  double bhv2 = -t * gz[0];
-  agz[0] += -t * hv2;
-  brho += -t * (u * duz + w * dwz);
-  bu += -t * rho * duz; bduz += -t * rho * u; bw += -t * rho * dwz; bdwz += -t * rho * w;
-  if (ph.gravity) brho += -bdpz * ph.gm1 * ph.g;
-  // dpx = gm1 (gx3 - hv2 gx0 - rho (u dux + w dwx))
-  t = bdpx * ph.gm1;
-  agx[3] += t;
-  bhv2 += -t * gx[0];
-  agx[0] += -t * hv2;
-  brho += -t * (u * dux + w * dwx);
-  bu += -t * rho * dux; bdux += -t * rho * u; bw += -t * rho * dwx; bdwx += -t * rho * w;
-  // hv2 = 1/2 (u^2 + w^2) + gzz
-  bu += bhv2 * u; bw += bhv2 * w;
-  // dwz = (gz2 - w gz0) ir ; dwx ; duz ; dux
-  agz[2] += bdwz * ir; bw += -bdwz * gz[0] * ir; agz[0] += -bdwz * w * ir; bir += bdwz * (gz[2] - w * gz[0]);
-  agx[2] += bdwx * ir; bw += -bdwx * gx[0] * ir; agx[0] += -bdwx * w * ir; bir += bdwx * (gx[2] - w * gx[0]);
-  agz[1] += bduz * ir; bu += -bduz * gz[0] * ir; agz[0] += -bduz * u * ir; bir += bduz * (gz[1] - u * gz[0]);
-  agx[1] += bdux * ir; bu += -bdux * gx[0] * ir; agx[0] += -bdux * u * ir; bir += bdux * (gx[1] - u * gx[0]);
-  // T = p ir iR
-  bp += bT * ir * ph.iR; bir += bT * p * ph.iR;
-  // pm = p - pb or p
-  bp += bpm;
-  // p = gm1 (E - 1/2 (mx u + mz w) - rho gzz)
-  t = bp * ph.gm1;
-  bE += t;
-  bmx += -0.5 * t * u; bu += -0.5 * t * mx;
-  bmz += -0.5 * t * w; bw += -0.5 * t * mz;
-  brho += -t * gzz;
-  // u = mx ir, w = mz ir
-  bmx += bu * ir; bir += bu * mx;
-  bmz += bw * ir; bir += bw * mz;
-  // ir = 1/rho
-  brho += -bir * ir * ir;
-  aq[0] = brho; aq[1] = bmx; aq[2] = bmz; aq[3] = bE;
-}
-
-// ------------------------------------------------- line jobs (half tables)
-template <int n>
-struct HalfA { static constexpr int nh = (n + 1) / 2; };
-
-template <int n>
-__device__ inline void vtab_load(const double* g, double (&M)[HalfA<n>::nh][n]) {
-#pragma unroll
-  for (int i = 0; i < HalfA<n>::nh; ++i)
-#pragma unroll
-    for (int m = 0; m < n; ++m) {
-      M[i][m] = g[i * n + m];
-      asm volatile("" : "+v"(M[i][m]));
-    }
-}
-
-// the same table left to the compiler: its entries are uniform, so they can
-// live in scalar registers
-template <int n>
-__device__ inline void stab_load(const double* g, double (&M)[HalfA<n>::nh][n]) {
-#pragma unroll
-  for (int i = 0; i < HalfA<n>::nh; ++i)
-#pragma unroll
-    for (int m = 0; m < n; ++m) M[i][m] = g[i * n + m];
-}
-
-// out = M in along a line (M centro-antisymmetric, first nh rows stored)
-template <int n>
-__device__ inline void line_M(const double (&M)[HalfA<n>::nh][n], int base, int stride, const double* src,
-                              double* dst, double scale) {
-  constexpr int nh = HalfA<n>::nh;
-  double in[n];
-#pragma unroll
-  for (int m = 0; m < n; ++m) in[m] = src[base + m * stride];
-#pragma unroll
-  for (int i = 0; i < nh; ++i) {
-    double s = 0.0;
-#pragma unroll
-    for (int m = 0; m < n; ++m) s = fma(M[i][m], in[m], s);
-    dst[base + i * stride] = scale * s;
-  }
-#pragma unroll
-  for (int i = 0; i < n / 2; ++i) {
-    double s = 0.0;
-#pragma unroll
-    for (int m = 0; m < n; ++m) s = fma(M[i][m], in[n - 1 - m], s);
-    dst[base + (n - 1 - i) * stride] = -scale * s;
-  }
-}
-
-// out = M^T in along a line: out[m] = sum_i M[i][m] in[i], with
-// M[i][m] = -M[n-1-i][n-1-m] for the rows not stored
-template <int n>
-__device__ inline void line_MT(const double (&M)[HalfA<n>::nh][n], int base, int stride, const double* src,
-                               double* dst, double scale) {
-  constexpr int nh = HalfA<n>::nh;
-  double in[n];
-#pragma unroll
-  for (int i = 0; i < n; ++i) in[i] = src[base + i * stride];
-#pragma unroll
-  for (int m = 0; m < n; ++m) {
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < nh; ++i) s = fma(M[i][m], in[i], s);
-#pragma unroll
-    for (int i = nh; i < n; ++i) s = fma(-M[n - 1 - i][n - 1 - m], in[i], s);
-    dst[base + m * stride] = scale * s;
-  }
+  // reverse: Fx1 = mx u + p + sxx, Fx2 = Fz1 = mx w + sxz, Fz2 = mz w + p + szz,
+  // Fx3 = u (H + sxx) + w sxz - k qx, Fz3 = w (H + szz) + u sxz - k qz
+  const double A1 = aFx[1], A2 = aFx[2] + aFz[1], A3 = aFx[3], B2 = aFz[2], B3 = aFz[3];
+  const double bxx = fma(A3, u, A1), bzz = fma(B3, w, B2), bxz = fma(B3, u, fma(A3, w, A2));
+  double bu = fma(A3, H + sxx, fma(B3, sxz, A1 * mx));
+  double bw = fma(B3, H + szz, fma(A3, sxz, fma(A2, mx, B2 * mz)));
+  const double bH = fma(A3, u, B3 * w);
+  const double bk = -fma(A3, qx, B3 * qz);
+  const double bqx = -k * A3, bqz = -k * B3;
+  const double bdx = c.gm1 * bqx, bdz = c.gm1 * bqz;
+  const double bpir = -fma(bqx, gx[0], bqz * gz[0]);
+  const double bhv = -fma(bdx, gx[0], bdz * gz[0]);
+  const double t = -mi * bxz;
+  const double bax = fma(m23, fma(-2.0, bxx, bzz), -u * bdx), bcz = fma(m23, fma(-2.0, bzz, bxx), -w * bdz);
+  const double bcx = fma(-w, bdx, t), baz = fma(-u, bdz, t);
+  bu -= fma(bdx, ax, bdz * az);
+  bw -= fma(bdx, cx, bdz * cz);
+  bu = fma(bhv, u, fma(-gx[0], bax, fma(-gz[0], baz, bu)));
+  bw = fma(bhv, w, fma(-gx[0], bcx, fma(-gz[0], bcz, bw)));
+  const double T = c.gm1 * (fma(ir, bpir, bH) + (A1 + B2));
+  double br = fma(sxx, bxx, fma(szz, bzz, fma(sxz, bxz, fma(k, bk, fma(pir, bpir, fma(u, bu, w * bw))))));
+  br = fma(-ir, br, fma(T, kin - c.gz, -c.gh * bdz));
+  agx[0] = -fma(pir, bqx, fma(hv, bdx, fma(u, bax, w * bcx)));
+  agz[0] = -fma(pir, bqz, fma(hv, bdz, fma(u, baz, w * bcz)));
+  agx[1] = bax; agx[2] = bcx; agx[3] = bdx;
+  agz[1] = baz; agz[2] = bcz; agz[3] = bdz;
+  aq[0] = br;
+  aq[1] = fma(-T, u, fma(ir, bu, fma(A1, u, fma(A2, w, aFx[0]))));
+  aq[2] = fma(-T, w, fma(ir, bw, fma(B2, w, aFz[0])));
+  aq[3] = T + bH;
 }
 
 struct AdjArgs {
@@ -208,7 +89,6 @@ struct AdjArgs {
   double* lam_out;       // dL/dQ^n
   const double* FD;      // forward face data (recomputed)
   const double* store;   // iterates [C][I][n][4][n][n]
-  double* lamFD;         // [C][4 faces][2][4][n]
   const double* clock;
   const double* geom;
   const int* nbr;
@@ -307,31 +187,34 @@ __device__ inline void ghost_vjp(const Phys& ph, double zf, const double Qi[4], 
   aQi[0] += -(bu * u + bw * w) * ir;
 }
 
-// Per cell, lanes (f, k): total flux adjoint of face f at node k (this
-// cell's half plus the neighbour's, both from the lifting adjoint of the
-// incoming adjoint state), then the reverse of the Rusanov flux
-// onto this cell's own face data (and, at walls, through the ghost).
+// Reverse of the Rusanov flux on one face of a cell, a lane per face node k:
+// total flux adjoint of face f (this cell's half plus the neighbour's, both
+// from the lifting adjoint of the incoming adjoint state), then the adjoints of
+// this cell's own face data (at walls also through the ghost).  `load` fetches
+// the node's data and publishes its speeds and its share of dL/ds, which
+// `reverse` needs from every node of the face.
 template <int n>
-__global__ __launch_bounds__(kWave) void k_face_adj(Phys ph, AdjArgs a) {
-  __shared__ double sLam[4][2][n], sLv[4][2][n], sQd[4][n];
-  const int c = blockIdx.x, lane = threadIdx.x;
-  const bool act = lane < 4 * n;
-  const int f = act ? lane / n : 0, k = lane % n;
-  const int d = f >> 1;
-  const bool lower = (f & 1) == 0;     // this cell is side R
-  const double* gt = a.gtab;
-  const double h = a.geom[4 * c + 2], z0 = a.geom[4 * c + 1];
-  const int* nb = a.nbr + (size_t)c * 16 + f * 4;
-  const int kind = act ? nb[0] : kWall;
-  double Qm[4], Fm[4], Qo[4], Fo[4], aG[4];
-  const double zf = (d == 0) ? z0 + h * gt[GTab::XI * n + k] : z0 + ((f & 1) ? h : 0.0);
-  if (act) {
+struct FaceAdj {
+  double Qm[4], Fm[4], Qo[4], Fo[4], aG[4], zf, h;
+  int d, wall;
+  bool lower;     // this cell is side R
+
+  // sx [5][n] of the face: speeds [2][n], viscous speeds [2][n], shares [n]
+  __device__ inline void load(const Phys& ph, const AdjArgs& a, int c, int f, int k, double* sx) {
+    const double* gt = a.gtab;
+    const int* nb = a.nbr + (size_t)c * 16 + f * 4;
+    const double z0 = a.geom[4 * c + 1];
+    h = a.geom[4 * c + 2];
+    d = f >> 1;
+    lower = (f & 1) == 0;
+    wall = nb[0] != kConforming;
+    zf = (d == 0) ? z0 + h * gt[GTab::XI * n + k] : z0 + ((f & 1) ? h : 0.0);
     const double* fd = a.FD + (size_t)c * 32 * n + f * 8 * n;
     for (int v = 0; v < 4; ++v) {
       Qm[v] = fd[v * n + k]; Fm[v] = fd[4 * n + v * n + k];
       aG[v] = lift_adj_half<n>(a, c, f, k, v);
     }
-    if (kind == kConforming) {
+    if (!wall) {
       const int o = nb[1];
       const double* fo = a.FD + (size_t)o * 32 * n + (f ^ 1) * 8 * n;
       for (int v = 0; v < 4; ++v) {
@@ -341,228 +224,323 @@ __global__ __launch_bounds__(kWave) void k_face_adj(Phys ph, AdjArgs a) {
     } else {
       ghost_fwd(ph, d, zf, Qm, Fm, Qo, Fo);
     }
-    double QL[4], QR[4];
-    for (int v = 0; v < 4; ++v) { QL[v] = lower ? Qo[v] : Qm[v]; QR[v] = lower ? Qm[v] : Qo[v]; }
-    double l, lv;
-    eig_a(ph, d, QL, zf, l, lv); sLam[f][0][k] = l; sLv[f][0][k] = lv;
-    eig_a(ph, d, QR, zf, l, lv); sLam[f][1][k] = l; sLv[f][1][k] = lv;
+    double l, lv, ds = 0.0;
+    eig_a(ph, d, lower ? Qo : Qm, zf, l, lv); sx[k] = l; sx[2 * n + k] = lv;
+    eig_a(ph, d, lower ? Qm : Qo, zf, l, lv); sx[n + k] = l; sx[3 * n + k] = lv;
     // this node's share of dL/ds = sum_v aG . (-1/2 (QR - QL))
-    double ds = 0.0;
-    for (int v = 0; v < 4; ++v) ds += aG[v] * (-0.5 * (QR[v] - QL[v]));
-    sQd[f][k] = ds;
+    for (int v = 0; v < 4; ++v) ds += aG[v] * (lower ? -0.5 * (Qm[v] - Qo[v]) : -0.5 * (Qo[v] - Qm[v]));
+    sx[4 * n + k] = ds;
   }
-  wave_sync_a();
-  if (!act) return;
-  // speed and its argmax: first maximum in the order L nodes 0..n-1, R nodes 0..n-1
-  double lam = sLam[f][0][0], lvm = sLv[f][0][0];
-  int al = 0, av = 0;
-  for (int side = 0; side < 2; ++side)
-    for (int m = 0; m < n; ++m) {
-      const int id = side * n + m;
-      if (id == 0) continue;
-      if (sLam[f][side][m] > lam) { lam = sLam[f][side][m]; al = id; }
-      if (sLv[f][side][m] > lvm) { lvm = sLv[f][side][m]; av = id; }
+
+  // out [2][4][n]: adjoints of the face's state and flux
+  __device__ inline void reverse(const Phys& ph, int k, const double* sx, double* out) const {
+    // speed and its argmax: first maximum in the order L nodes 0..n-1, R nodes 0..n-1
+    double lam = sx[0], lvm = sx[2 * n], bs = 0.0;
+    int al = 0, av = 0;
+    for (int m = 1; m < 2 * n; ++m) {
+      if (sx[m] > lam) { lam = sx[m]; al = m; }
+      if (sx[2 * n + m] > lvm) { lvm = sx[2 * n + m]; av = m; }
     }
-  const double eta = (2.0 * ph.N + 1.0) / (h * 1.2533141373155002512);
-  const double s = lam + 2.0 * eta * lvm;
-  double bs = 0.0;
-  for (int m = 0; m < n; ++m) bs += sQd[f][m];
-  // G = 1/2 (FL + FR) - 1/2 s (QR - QL): adjoints of (QL, FL, QR, FR) at node k
-  double aQL[4], aFL[4], aQR[4], aFR[4];
-  for (int v = 0; v < 4; ++v) {
-    aFL[v] = 0.5 * aG[v]; aFR[v] = 0.5 * aG[v];
-    aQL[v] = 0.5 * s * aG[v]; aQR[v] = -0.5 * s * aG[v];
+    for (int m = 0; m < n; ++m) bs += sx[4 * n + m];
+    const double eta = (2.0 * ph.N + 1.0) / (h * 1.2533141373155002512);
+    const double s = lam + 2.0 * eta * lvm;
+    // G = 1/2 (FL + FR) - 1/2 s (QR - QL): adjoints of both sides' data at node
+    // k, m this cell's and g the other's
+    double aQm[4], aQg[4], aF[4];
+    for (int v = 0; v < 4; ++v) {
+      aF[v] = 0.5 * aG[v];
+      aQg[v] = (lower ? 0.5 : -0.5) * s * aG[v];
+      aQm[v] = -aQg[v];
+    }
+    // speed terms at the argmax nodes (if they are this node)
+    const int km = lower ? n + k : k, kg = lower ? k : n + k;
+    double gl[4], gv[4];
+    if (al == km || av == km) {
+      eig_grad(ph, d, Qm, zf, gl, gv);
+      for (int v = 0; v < 4; ++v) {
+        if (al == km) aQm[v] += bs * gl[v];
+        if (av == km) aQm[v] += bs * 2.0 * eta * gv[v];
+      }
+    }
+    if (wall) {
+      if (al == kg || av == kg) {
+        eig_grad(ph, d, Qo, zf, gl, gv);
+        for (int v = 0; v < 4; ++v) {
+          if (al == kg) aQg[v] += bs * gl[v];
+          if (av == kg) aQg[v] += bs * 2.0 * eta * gv[v];
+        }
+      }
+      double aQi[4], aFi[4];
+      ghost_vjp(ph, zf, Qm, aQg, aF, aQi, aFi);
+      for (int v = 0; v < 4; ++v) { aQm[v] += aQi[v]; aF[v] += aFi[v]; }
+    }
+    for (int v = 0; v < 4; ++v) { out[v * n + k] = aQm[v]; out[4 * n + v * n + k] = aF[v]; }
   }
-  // speed terms at the argmax nodes (if they are this node)
-  // speed terms at the argmax nodes (if they are this node)
-  double gl[4], gv[4];
-  if (al == k) {
-    eig_grad(ph, d, lower ? Qo : Qm, zf, gl, gv);
-    for (int v = 0; v < 4; ++v) aQL[v] += bs * gl[v];
-  } else if (al == n + k) {
-    eig_grad(ph, d, lower ? Qm : Qo, zf, gl, gv);
-    for (int v = 0; v < 4; ++v) aQR[v] += bs * gl[v];
-  }
-  if (av == k) {
-    eig_grad(ph, d, lower ? Qo : Qm, zf, gl, gv);
-    for (int v = 0; v < 4; ++v) aQL[v] += bs * 2.0 * eta * gv[v];
-  } else if (av == n + k) {
-    eig_grad(ph, d, lower ? Qm : Qo, zf, gl, gv);
-    for (int v = 0; v < 4; ++v) aQR[v] += bs * 2.0 * eta * gv[v];
-  }
-  double aQm[4], aFm[4], aQg[4], aFg[4];
-  for (int v = 0; v < 4; ++v) {
-    aQm[v] = lower ? aQR[v] : aQL[v];
-    aFm[v] = lower ? aFR[v] : aFL[v];
-    aQg[v] = lower ? aQL[v] : aQR[v];
-    aFg[v] = lower ? aFL[v] : aFR[v];
-  }
-  if (kind == kWall) {
-    double aQi[4], aFi[4];
-    ghost_vjp(ph, zf, Qm, aQg, aFg, aQi, aFi);
-    for (int v = 0; v < 4; ++v) { aQm[v] += aQi[v]; aFm[v] += aFi[v]; }
-  }
-  double* out = a.lamFD + (size_t)c * 32 * n + f * 8 * n;
-  for (int v = 0; v < 4; ++v) { out[v * n + k] = aQm[v]; out[4 * n + v * n + k] = aFm[v]; }
-}
+};
 
 // ------------------------------------------------------- reverse predictor
-// One workgroup of NW wavefronts per cell; wavefront w owns the time levels
-// b = w, w + NW, ... (NW = min(n, 4): at order 6, three cells' workgroups
-// share a CU, so a 27x27 mesh runs in one round).  The reverse of every time
-// level of a sweep (and of the final pass) is independent of the others once
-// the sweep's residual adjoints are known, so the levels run side by side;
-// the workgroup synchronises only where the levels meet (the time matrix
-// mixes them).  Each wavefront has its own LDS slice buffers; the iterate
-// adjoints Lq and the residual adjoints sR are shared.
-template <int n>
-constexpr int adj_waves() { return n < 4 ? n : 4; }
+// One workgroup of four wavefronts per CB cells.  All time levels of a sweep
+// run side by side, and the threads change between three roles, with a barrier
+// between them:
+//   time columns (variable, cell, j, i): all levels of one value, for the
+//           transposed time matrix; the iterate's adjoint lives here;
+//   lines   (variable, cell, level, j or i): a row or a column in registers,
+//           for the derivatives and their transposes;
+//   nodes   (cell, level, j, i): the reverse of the fluxes.
+// Wavefront w works on variable w in the first two roles.  Adjoints are
+// divided by the quadrature weights w_i w_j of their node: along a line
+// D^T = W Dw W^{-1} and Dw^T = W D W^{-1}, so the transposed contractions are
+// those of the forward sweep and have its even-odd form.  The face adjoints of
+// the cell come first, in the same kernel (in one of their own they cost a
+// launch and a trip through memory, 4 us).  Buffers, each
+// [4 variables][level][j][i]: A and B along x and z (adjoints of the fluxes,
+// gradients, adjoints of the gradients), C (residual adjoints, then the direct
+// adjoints of the state), Q (the iterate).
+//
+// Bound by the chain of a cell: six barriers and some 550 FP64 and 150 LDS
+// instructions of a wavefront per sweep at n = 7, 3.5 us.  Step adjoint
+// without the predictor, before (time levels one per wavefront, lines as dot
+// products, face adjoints apart) and now: 27 x 27 cells of n = 7 74 and 60 us,
+// 41 x 23 of n = 5 54 and 26, 45 x 45 of n = 6 128 and 95, of n = 3 37 and 18,
+// 9 x 9 of n = 7 40 and 33.  Loading the next iterate a sweep ahead: no gain,
+// and at n = 7 spills.
+template <int n, int CB>
+struct AdjLay {
+  static constexpr int nn = n * n;
+  static constexpr bool grid8 = CB == 1 && (n == 6 || n == 7);   // lane 8 hi + lo, else hi n + lo
+  static_assert(grid8 || CB * nn <= kWave, "a lane per line of each cell");
+  // strides of level, row and node within a variable: free of bank conflicts
+  // for rows, columns and time columns
+  static constexpr int BS = grid8 ? 8 : n, JS = 1;
+  static constexpr int IS = grid8 ? 55 : n == 8 ? 65 : n == 7 ? 49 : n == 6 ? 41 : n == 5 ? 25 : n == 4 ? 19 : n == 3 ? 10 : 4;
+  static constexpr int VS = (n - 1) * (BS + JS + IS) + 1;
+  static constexpr int buf = 4 * VS, cell = 4 * buf;
+  static constexpr int NT = 4 * kWave;
+  static constexpr int NP = (CB * n * nn + NT - 1) / NT;           // nodes per thread
+  static_assert(NP == 1 || CB == 1, "a thread's nodes lie in one cell");
+  static_assert(CB * 8 * n <= NT, "one slice line per thread");
+};
 
-template <int n>
-__global__ __launch_bounds__(kWave * adj_waves<n>()) void k_pred_adj(Phys ph, AdjArgs a) {
-  constexpr int nn = n * n, sl = 4 * nn, NW = adj_waves<n>();
-  __shared__ double Lq[n * sl];        // adjoint of the iterate at every time node
-  __shared__ double sR[n * sl];        // residual adjoints of one reverse sweep
-  __shared__ double sW[NW][3 * sl];    // per wavefront: state slice, then gradients / adjoint work
-  const int c = blockIdx.x, w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  double* sq = sW[w];
-  double* sg = sW[w] + sl;             // [2][sl]: gradients along x and z, reused for the adjoint work
-  const bool node = lane < nn;
-  const int l = node ? lane : 0;
-  const int jz = l / n, ix = l % n;
-  const bool job = lane < 8 * n;
-  const int dir = lane / (4 * n), jv = (lane % (4 * n)) / n, line = lane % n;
-  const int jbase = jv * nn + (dir == 0 ? line * n : line), jstride = dir == 0 ? 1 : n;
+template <int n, int CB>
+__global__ __launch_bounds__(4 * kWave, 3) void k_pred_adj(Phys ph, AdjArgs a) {
+  using L = AdjLay<n, CB>;
+  constexpr int nn = L::nn, sl = 4 * nn, BS = L::BS, JS = L::JS, IS = L::IS, VS = L::VS, buf = L::buf, NP = L::NP;
+  __shared__ double lds[CB * L::cell], sface[CB * 52 * n];   // face adjoints [4][2][4][n], exchange [4][5][n] per cell
+  const int t = threadIdx.x, lane = t % kWave;
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
   const double* gt = a.gtab;
   const double dt = a.clock[1];
-  const double z0 = a.geom[4 * c + 1], h = a.geom[4 * c + 2];
-  const double ih = 1.0 / h;
-  const double z = z0 + h * gt[GTab::XI * n + jz];
-  double rb, pb;
-  background(ph, z, rb, pb);
-  (void)pb;
-  double Dv[HalfA<n>::nh][n];
-  stab_load<n>(gt + GTab::d(n), Dv);
-  const double* Qc = a.Qn + (size_t)c * sl;
-  const double* lin = a.lam_in + (size_t)c * sl;
-  const double* lfd = a.lamFD + (size_t)c * 32 * n;
-  const double* store = a.store + (size_t)c * a.iters * n * sl;
   const int I = a.iters;
 
-  // (a) adjoints of Q*, of the averaged state, fluxes and source (every
-  // wavefront computes them for its own use)
-  double aQn[4], aQb[4], aFbx[4], aFbz[4], aSb = 0.0;
-  double lq[4];
-  for (int v = 0; v < 4; ++v) lq[v] = node ? lin[v * nn + l] : 0.0;
-  for (int v = 0; v < 4; ++v) aQn[v] = w == 0 ? lq[v] : 0.0;   // direct part, counted once
-  aSb = dt * lq[2];
-  if (node)
-    for (int v = 0; v < 4; ++v) sq[v * nn + l] = lq[v];
-  wave_sync_a();
+  // lines and time columns; idle lanes read along with lane 0 and write nothing
+  const int s0 = L::grid8 ? 0 : lane / nn;
+  const int h0 = L::grid8 ? lane / 8 : lane % nn / n, l0 = L::grid8 ? lane % 8 : lane % n;
+  const bool act = L::grid8 ? h0 < n && l0 < n : s0 < CB;
+  const int slot = act ? s0 : 0, hi = act ? h0 : 0, lo = act ? l0 : 0, r = hi * n + lo;
+  const int c = min((int)blockIdx.x * CB + slot, a.C - 1);   // loads stay in bounds
+  const bool valid = act && (int)blockIdx.x * CB + slot < a.C;
+  double* A = lds + slot * L::cell + w * VS;
+  double* B = A + buf;
+  double* Cb = A + 2 * buf;
+  double* Qb = A + 3 * buf;
+  const int rowo = hi * BS + lo * JS, colo = hi * BS + lo * IS, timo = hi * JS + lo * IS;
+  const double dth = dt / a.geom[4 * c + 2];
+  const double* Qc = a.Qn + (size_t)c * sl + w * nn;
+  const double* store = a.store + (size_t)c * I * n * sl + hi * sl + w * nn;
+
+  // nodes
+  const int cn = min((int)blockIdx.x * CB + t % (CB * nn) / nn, a.C - 1);
+  FluxC fc;
   {
-    double Wv[HalfA<n>::nh][n];
-    stab_load<n>(gt + GTab::dw(n), Wv);
-    // lambda_Fbar = (dt/h) Dw^T lambda_Q* along x (rows) and z (columns)
-    if (job) line_MT<n>(Wv, jbase, jstride, sq, sg + dir * sl, dt * ih);
+    const double h = a.geom[4 * cn + 2], ih = 1.0 / h;
+    fc.gm1 = ph.gm1;
+    fc.hgm1 = 0.5 * ph.gm1;
+    fc.mu = ph.mu * ih;
+    fc.mu23 = fc.mu * (2.0 / 3.0);
+    fc.kap = ph.kappa * ih * ph.iR;
+    fc.gh = ph.geff * h;
+    fc.pb = 0.0;
   }
-  wave_sync_a();
-  if (node) {
-    const double e0i = gt[GTab::E0 * n + ix], e1i = gt[GTab::E1 * n + ix];
-    const double e0j = gt[GTab::E0 * n + jz], e1j = gt[GTab::E1 * n + jz];
-    for (int v = 0; v < 4; ++v) {
-      // face extrapolations: x faces use row jz, z faces column ix
-      aQb[v] = e0i * lfd[(0 * 2 + 0) * 4 * n + v * n + jz] + e1i * lfd[(1 * 2 + 0) * 4 * n + v * n + jz] +
-               e0j * lfd[(2 * 2 + 0) * 4 * n + v * n + ix] + e1j * lfd[(3 * 2 + 0) * 4 * n + v * n + ix];
-      aFbx[v] = sg[v * nn + l] + e0i * lfd[(0 * 2 + 1) * 4 * n + v * n + jz] +
-                e1i * lfd[(1 * 2 + 1) * 4 * n + v * n + jz];
-      aFbz[v] = sg[sl + v * nn + l] + e0j * lfd[(2 * 2 + 1) * 4 * n + v * n + ix] +
-                e1j * lfd[(3 * 2 + 1) * 4 * n + v * n + ix];
+  int no[NP], nij[NP];   // offset and slice index of the thread's nodes
+  double nw[NP], ngz[NP];   // their time weight and g z
+  bool nact[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int id = t + p * L::NT, k = id % (CB * nn), i = id / (CB * nn);
+    const int s = k / nn, b = k % nn / n, j = k % n;
+    nact[p] = i < n;
+    no[p] = nact[p] ? s * L::cell + b * BS + j * JS + i * IS : 0;
+    nw[p] = gt[GTab::W * n + b];
+    ngz[p] = ph.geff * (a.geom[4 * cn + 1] + a.geom[4 * cn + 2] * gt[GTab::XI * n + j]);
+    nij[p] = nact[p] ? s * L::cell + j * n + i : 0;
+  }
+
+  // adjoints of the averaged state, fluxes and source, as slices [v][j][i]
+  double X[n], aQn;
+  {
+    const double* lin = a.lam_in + (size_t)c * sl;
+    const double ij = 1.0 / gt[GTab::W * n + hi], ii = 1.0 / gt[GTab::W * n + lo];
+    aQn = lin[w * nn + r] * (ij * ii);
+    double* A0 = A - w * VS;
+    if (act) A0[2 * buf + w * nn + r] = aQn;
+    FaceAdj<n> face;
+    const int fs = t / (4 * n), ff = t % (4 * n) / n, fk = t % n;
+    double* sf = sface + fs * 52 * n + ff * 8 * n;
+    double* sx = sface + fs * 52 * n + 32 * n + ff * 5 * n;
+    if (t < CB * 4 * n) face.load(ph, a, min((int)blockIdx.x * CB + fs, a.C - 1), ff, fk, sx);
+    __syncthreads();
+    if (t < CB * 4 * n) face.reverse(ph, fk, sx, sf);
+    if (t < CB * 8 * n) {
+      const EO<n> D(scalar_table(gt + GTab::eo_d(n)));
+      const int k = t % (8 * n), dir = k >= 4 * n, v = k % (4 * n) / n, line = k % n;
+      const int base = t / (8 * n) * L::cell + v * nn + (dir ? line : line * n), st = dir ? n : 1;
+      double in[n], out[n];
+#pragma unroll
+      for (int m = 0; m < n; ++m) in[m] = lds[2 * buf + base + m * st];
+      D.apply(in, out);
+#pragma unroll
+      for (int m = 0; m < n; ++m) lds[dir * buf + base + m * st] = out[m];
+    }
+    __syncthreads();
+    const double L0i = gt[GTab::L0 * n + lo] * ij, L1i = gt[GTab::L1 * n + lo] * ij;
+    const double L0j = gt[GTab::L0 * n + hi] * ii, L1j = gt[GTab::L1 * n + hi] * ii;
+    const double* f = sface + slot * 52 * n + w * n;
+    double qa = fma(L0i, f[hi], L1i * f[8 * n + hi]);
+    qa = fma(L0j, f[16 * n + lo], fma(L1j, f[24 * n + lo], qa));
+    if (w == 0) qa = fma(-ph.geff * dt * (ij * ii), lin[2 * nn + r], qa);   // gravity source
+    f += 4 * n;
+    const double fx = fma(L0i, f[hi], L1i * f[8 * n + hi]), fz = fma(L0j, f[16 * n + lo], L1j * f[24 * n + lo]);
+    if (act) {
+      double* o = A0 + w * nn + r;
+      o[0] = fma(dth, o[0], fx);
+      o[buf] = fma(dth, o[buf], fz);
+      o[2 * buf] = qa;
     }
   }
-  wave_sync_a();
 
-  // reverse of "flux/source at time level b": given aF (x, z) and aSw per
-  // node, the state adjoint (direct + through the gradients) plus add[]
-  // becomes Lq[b]
-  auto slice_vjp = [&](int b, const double* qsrc, const double aFx[4], const double aFz[4], double aSw,
-                       const double add[4]) {
-    double q[4] = {0, 0, 0, 0};   // the node's state, kept for the flux adjoint
-    if (node)
-      for (int v = 0; v < 4; ++v) { q[v] = qsrc[v * nn + l]; sq[v * nn + l] = q[v]; }
-    wave_sync_a();
-    if (job) line_M<n>(Dv, jbase, jstride, sq, sg + dir * sl, ih);     // gradients
-    wave_sync_a();
-    double aq[4] = {0, 0, 0, 0};
-    if (node) {
-      double gx[4], gz[4], agx[4], agz[4];
-      for (int v = 0; v < 4; ++v) { gx[v] = sg[v * nn + l]; gz[v] = sg[sl + v * nn + l]; }
-      flux_source_vjp(ph, q, gx, gz, z, rb, aFx, aFz, aSw, aq, agx, agz);
-      for (int v = 0; v < 4; ++v) { sg[v * nn + l] = agx[v]; sg[sl + v * nn + l] = agz[v]; }
+  // it = I: the time averages, at the last iterate; then the Picard sweeps in
+  // reverse, q^{it+1}[a] = Q^n + dt sum_b P[a][b] R(q^it[b])
+#pragma unroll 1
+  for (int it = I; it >= 0; it = __builtin_amdgcn_readfirstlane(it - 1)) {
+    double qr[n], qc[n];   // row and column of the iterate
+    {
+      const double* q = it > 0 ? store + (size_t)(it - 1) * n * sl : Qc;
+#pragma unroll
+      for (int m = 0; m < n; ++m) { qr[m] = q[lo * n + m]; qc[m] = q[m * n + lo]; }
     }
-    wave_sync_a();
-    // gradient adjoints back to the state: (1/h) D^T along each direction
-    if (job) line_MT<n>(Dv, jbase, jstride, sg + dir * sl, sg + dir * sl, ih);
-    wave_sync_a();
-    if (node)
-      for (int v = 0; v < 4; ++v) Lq[b * sl + v * nn + l] = aq[v] + sg[v * nn + l] + sg[sl + v * nn + l] + add[v];
-    wave_sync_a();
-  };
-
-  // (b) final pass: F, S and q at the last iterate, averaged with w_b
-  for (int b = w; b < n; b += NW) {
-    const double wb = gt[GTab::W * n + b];
-    double aFx[4], aFz[4], add[4];
-    for (int v = 0; v < 4; ++v) { aFx[v] = wb * aFbx[v]; aFz[v] = wb * aFbz[v]; add[v] = wb * aQb[v]; }
-    slice_vjp(b, store + ((size_t)(I - 1) * n + b) * sl, aFx, aFz, wb * aSb, add);
-  }
-  __syncthreads();
-
-  // (c) Picard sweeps in reverse: q^{k+1}[a] = Q^n + dt sum_b P[a][b] R(q^k[b])
-  for (int it = I - 1; it >= 0; --it) {
-    for (int b = w; b < n; b += NW) {
-      const double* prow = gt + GTab::pt(n) + b * n;   // P[a][b] over a
-      if (node)
-        for (int v = 0; v < 4; ++v) {
-          aQn[v] += Lq[b * sl + v * nn + l];
-          double s = 0.0;
-          for (int a2 = 0; a2 < n; ++a2) s = fma(prow[a2], Lq[a2 * sl + v * nn + l], s);
-          sR[b * sl + v * nn + l] = dt * s;
-        }
-    }
-    __syncthreads();   // every level's Lq read before any is overwritten
-    for (int b = w; b < n; b += NW) {
-      // R = S - (1/h)(Dx Fx + Dz Fz): lambda_F = -(1/h) D^T lambda_R, lambda_Sw = lambda_R[2]
-      if (job) line_MT<n>(Dv, jbase, jstride, sR + b * sl, sg + dir * sl, -ih);
-      wave_sync_a();
-      double aFx[4], aFz[4];
-      for (int v = 0; v < 4; ++v) {
-        aFx[v] = node ? sg[v * nn + l] : 0.0;
-        aFz[v] = node ? sg[sl + v * nn + l] : 0.0;
+    if (it < I) {
+      // R = S - (1/h)(Dx Fx + Dz Fz): residual adjoints times -1/h
+      const ctab pt = scalar_table(gt + GTab::pt(n));
+#pragma unroll
+      for (int b = 0; b < n; ++b) aQn += X[b];
+#pragma unroll
+      for (int b = 0; b < n; ++b) {
+        double s = pt[b * n] * X[0];
+#pragma unroll
+        for (int m = 1; m < n; ++m) s = fma(pt[b * n + m], X[m], s);
+        if (act) Cb[timo + b * BS] = -dth * s;
       }
-      const double aSw = node ? sR[b * sl + 2 * nn + l] : 0.0;
-      wave_sync_a();
-      const double zero[4] = {0, 0, 0, 0};
-      slice_vjp(b, it > 0 ? store + ((size_t)(it - 1) * n + b) * sl : Qc, aFx, aFz, aSw, zero);
+      __syncthreads();
+      const EO<n> W(scalar_table(gt + GTab::eo_dw(n)));
+      double in[n], im[n], out[n];
+#pragma unroll
+      for (int m = 0; m < n; ++m) { in[m] = Cb[rowo + m * IS]; im[m] = Cb[colo + m * JS]; }
+      W.apply(in, out);
+      if (act) {
+#pragma unroll
+        for (int m = 0; m < n; ++m) A[rowo + m * IS] = out[m];
+      }
+      W.apply(im, out);
+      if (act) {
+#pragma unroll
+        for (int m = 0; m < n; ++m) B[colo + m * JS] = out[m];
+      }
     }
-    __syncthreads();   // every level's Lq written before the next sweep reads them
+    if (act) {
+#pragma unroll
+      for (int m = 0; m < n; ++m) Qb[rowo + m * IS] = qr[m];
+    }
+    __syncthreads();
+    double aFx[NP][4], aFz[NP][4], add[NP][4];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const bool last = it == I;
+      const double wb = last ? nw[p] : 1.0;
+      const double* s = lds + (last ? nij[p] : no[p]);
+      const int vs = last ? nn : VS;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        aFx[p][v] = wb * s[v * vs];
+        aFz[p][v] = wb * s[buf + v * vs];
+        add[p][v] = last ? wb * s[2 * buf + v * vs] : 0.0;
+      }
+      if (!last) add[p][0] = fc.gh * s[2 * buf + 2 * VS];   // gravity source of the sweep
+    }
+    __syncthreads();
+    {
+      const EO<n> D(scalar_table(gt + GTab::eo_d(n)));
+      double out[n];
+      D.apply(qr, out);
+      if (act) {
+#pragma unroll
+        for (int m = 0; m < n; ++m) A[rowo + m * IS] = out[m];
+      }
+      D.apply(qc, out);
+      if (act) {
+#pragma unroll
+        for (int m = 0; m < n; ++m) B[colo + m * JS] = out[m];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if (nact[p]) {
+        double* s = lds + no[p];
+        double q[4], gx[4], gz[4], aq[4], agx[4], agz[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          gx[v] = s[v * VS];
+          gz[v] = s[buf + v * VS];
+          q[v] = s[3 * buf + v * VS];
+        }
+        fc.gz = ngz[p];
+        flux_vjp(fc, q, gx, gz, aFx[p], aFz[p], aq, agx, agz);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          s[v * VS] = agx[v];
+          s[buf + v * VS] = agz[v];
+          s[2 * buf + v * VS] = aq[v] + add[p][v];
+        }
+      }
+    __syncthreads();
+    {
+      // gradient adjoints back to the state
+      const EO<n> W(scalar_table(gt + GTab::eo_dw(n)));
+      double in[n], im[n], out[n];
+#pragma unroll
+      for (int m = 0; m < n; ++m) { in[m] = A[rowo + m * IS]; im[m] = B[colo + m * JS]; }
+      W.apply(in, out);
+      if (act) {
+#pragma unroll
+        for (int m = 0; m < n; ++m) A[rowo + m * IS] = out[m];
+      }
+      W.apply(im, out);
+      if (act) {
+#pragma unroll
+        for (int m = 0; m < n; ++m) B[colo + m * JS] = out[m];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < n; ++b) {
+      const int o = timo + b * BS;
+      X[b] = Cb[o] + (A[o] + B[o]);
+    }
   }
-  // q^0[b] = Q^n for every b; each wavefront's share (its accumulator and its
-  // levels' last adjoints) summed through LDS
-  if (node)
-    for (int v = 0; v < 4; ++v) {
-      double s = aQn[v];
-      for (int b = w; b < n; b += NW) s += Lq[b * sl + v * nn + l];
-      sR[w * sl + v * nn + l] = s;
-    }
-  __syncthreads();
-  if (w == 0 && node) {
-    double* out = a.lam_out + (size_t)c * sl;
-    for (int v = 0; v < 4; ++v) {
-      double s = 0.0;
-      for (int k = 0; k < NW; ++k) s += sR[k * sl + v * nn + l];
-      out[v * nn + l] = s;
-    }
-  }
+  // q^0[b] = Q^n for every b
+#pragma unroll
+  for (int b = 0; b < n; ++b) aQn += X[b];
+  if (valid) a.lam_out[(size_t)c * sl + w * nn + r] = aQn * (gt[GTab::W * n + hi] * gt[GTab::W * n + lo]);
 }
 
 // ----------------------------------------------- initial state from theta'
@@ -666,15 +644,25 @@ __global__ __launch_bounds__(kWave) void k_loss_adj(Phys ph, const double* Q, co
 int launch_predictor(const Group& g, double* store, hipStream_t s);
 int launch_corrector(const Group& g, hipStream_t s);
 
+template <int n, int CB>
+static void pred_adj_t(const Group& g, const AdjArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((k_pred_adj<n, CB>), dim3((g.C + CB - 1) / CB), dim3(4 * kWave), 0, s, g.ph, a);
+}
 template <int n>
 static int adj_n(const Group& g, AdjArgs a, hipStream_t s) {
-  hipLaunchKernelGGL(k_face_adj<n>, dim3(g.C), dim3(kWave), 0, s, g.ph, a);
-  hipLaunchKernelGGL(k_pred_adj<n>, dim3(g.C), dim3(kWave * adj_waves<n>()), 0, s, g.ph, a);
+  // Up to one cell per CU, a workgroup for each cell; beyond, as many cells as
+  // the lanes of a wavefront hold (one from n = 6 on).  One cell, several: 9 x 9
+  // cells of n = 3 14.7, 16.2 us and of n = 5 18.9, 20.1; 16 x 16 of n = 4
+  // 15.5, 15.3; 20 x 20 of n = 4 17.9, 15.0 and of n = 5 23.4, 19.9; 45 x 45 of
+  // n = 3 35.5, 17.7.
+  constexpr int CB = kWave / (n * n), kCus = 256;
+  if (g.C <= kCus) pred_adj_t<n, 1>(g, a, s);
+  else pred_adj_t<n, CB>(g, a, s);
   return check_launch("step adjoint");
 }
 
 int launch_step_adjoint(const Group& g, const double* Qn, const double* lam_in, double* lam_out, double* store,
-                        const double* fd, bool recompute, double* lamFD, hipStream_t s) {
+                        const double* fd, bool recompute, hipStream_t s) {
   if (recompute) {
     // forward predictor from the checkpoint, keeping the iterates and the face data
     Group gf = g;
@@ -685,7 +673,7 @@ int launch_step_adjoint(const Group& g, const double* Qn, const double* lam_in, 
   }
   AdjArgs a;
   a.Qn = Qn; a.lam_in = lam_in; a.lam_out = lam_out; a.FD = fd; a.store = store;
-  a.lamFD = lamFD; a.clock = g.clock; a.geom = g.d_geom; a.nbr = g.d_nbr; a.gtab = g.d_gtab;
+  a.clock = g.clock; a.geom = g.d_geom; a.nbr = g.d_nbr; a.gtab = g.d_gtab;
   a.C = g.C; a.iters = g.iters;
   switch (g.n) {
     case 2: return adj_n<2>(g, a, s);

@@ -36,12 +36,6 @@
 
 namespace adg {
 
-// Per-launch and per-cell constants of the flux.
-struct FluxC {
-  double gm1, hgm1, mu, mu23, kap, gh;   // gm1, gm1/2, mu/h, (2/3) mu/h, kappa/(h R), g h
-  double gz, pb;                         // g z and background pressure of the lane's row
-};
-
 // Momentum and energy fluxes along x and z at one node (eqs. equation-set,
 // eos, temperature, stress-tensor, heat-conduction-coeff,
 // momentum-equation-split).  q: state; gx, gz: gradients in reference

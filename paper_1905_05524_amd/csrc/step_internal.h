@@ -63,6 +63,12 @@ struct EO {
   }
 };
 
+// Per-launch and per-cell constants of the flux.
+struct FluxC {
+  double gm1, hgm1, mu, mu23, kap, gh;   // gm1, gm1/2, mu/h, (2/3) mu/h, kappa/(h R), g h
+  double gz, pb;                         // g z and background pressure of the lane's row
+};
+
 struct StepArgs {
   const double* Qin;    // [C][4][n][n]
   double* Qout;         // corrector output (may alias Qin)
