@@ -18,7 +18,7 @@ struct Args3 {
   double* dtc;          // [C] CFL candidates
   const double* clock;  // (t, dt, -, steps)
   const double* gtab;   // GTab layout
-  const double* bg;     // [nz][n][2] background density and pressure of the node rows
+  const double* bg;     // [nz][n + 2][2] background density and pressure: node rows, bottom, top
   int nx, ny, nz, C, iters;
   int wall;             // bit f set: domain face f is a wall
   double x0, y0, z0, h;

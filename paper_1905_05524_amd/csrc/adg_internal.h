@@ -84,7 +84,8 @@ struct Group {
   int n = 0, N = 0, iters = 0, C = 0;
   Phys ph{};
   // handle-owned device tables
-  double* d_geom = nullptr;   // [C][4] x0, z0, h, 0
+  double* d_geom = nullptr;   // [C][4] x0, z0, h, 0; the background table behind it
+  double* d_bg = nullptr;     // [C][n + 2][2] background density and pressure: node rows, bottom, top
   int* d_nbr = nullptr;       // [C][4 faces][4] kind, a, b, c (cell indices local to the group)
   double* d_gtab = nullptr;   // GTab layout
   int* d_scen = nullptr;      // [C] scenario index into clock (NULL: all 0)
@@ -270,13 +271,24 @@ __device__ inline double pressure(const Phys& ph, double rho, double mx, double 
   return ph.gm1 * (E - 0.5 * (mx * mx + mz * mz) / rho - geo);
 }
 
-// Energy source of the manufactured advected density wave (T = p/(R rho),
-// S_E = -kappa Lap T).
-__device__ inline double mms_source(const Phys& ph, double x, double z, double t) {
-  double X = x - ph.mms_u * t, Z = z - ph.mms_w * t;
+// Phases of the manufactured advected density wave, kx (x - u t) and
+// kz (z - w t): sine and cosine along x, then along z.
+struct WavePhase {
   double sx, cx, sz, cz;
-  sincos(ph.mms_kx * X, &sx, &cx);
-  sincos(ph.mms_kz * Z, &sz, &cz);
+};
+__device__ inline WavePhase wave_phase(const Phys& ph, double X, double Z) {
+  WavePhase p;
+  sincos(ph.mms_kx * X, &p.sx, &p.cx);
+  sincos(ph.mms_kz * Z, &p.sz, &p.cz);
+  return p;
+}
+// Energy source of the wave (T = p/(R rho), S_E = -kappa Lap T) at a point with
+// phases a, a time later in which the phases decrease by b: n time levels cost
+// one pair of sines for the point and one for each level of a cell, not two
+// for each of the cell's n^3 nodes in space and time.
+__device__ inline double mms_source(const Phys& ph, const WavePhase& a, const WavePhase& b) {
+  const double sx = fma(a.sx, b.cx, -(a.cx * b.sx)), cx = fma(a.cx, b.cx, a.sx * b.sx);
+  const double sz = fma(a.sz, b.cz, -(a.cz * b.sz)), cz = fma(a.cz, b.cz, a.sz * b.sz);
   double rho = 1.0 + ph.mms_amp * sx * sz;
   double rx = ph.mms_amp * ph.mms_kx * cx * sz;
   double rz = ph.mms_amp * ph.mms_kz * sx * cz;

@@ -91,6 +91,7 @@ struct AdjArgs {
   const double* store;   // iterates [C][I][n][4][n][n]
   const double* clock;
   const double* geom;
+  const double* bg;      // [C][n + 2][2]
   const int* nbr;
   const double* gtab;
   int C, iters;
@@ -145,12 +146,13 @@ __device__ inline void eig_grad(const Phys& ph, int d, const double q[4], double
   gv[0] = -ph.lv_coef * ir * ir; gv[1] = 0.0; gv[2] = 0.0; gv[3] = 0.0;
 }
 
-// wall ghost (as in the forward corrector) and its reverse
-__device__ inline void ghost_fwd(const Phys& ph, int d, double zf, const double Qi[4], const double Fi[4], double Qg[4],
-                                 double Fg[4]) {
+// wall ghost (as in the forward corrector) and its reverse; bg: the background
+// at the face node
+__device__ inline void ghost_fwd(const Phys& ph, int d, double zf, const double bg[2], const double Qi[4],
+                                 const double Fi[4], double Qg[4], double Fg[4]) {
   const double u = Qi[1] / Qi[0], w = Qi[2] / Qi[0];
   double rb, pb;
-  if (ph.gravity) background(ph, zf, rb, pb);
+  if (ph.gravity) { rb = bg[0]; pb = bg[1]; }
   else { rb = Qi[0]; pb = pressure(ph, Qi[0], Qi[1], Qi[2], Qi[3], zf); }
   const double geo = ph.gravity ? rb * (ph.g * zf) : 0.0;
   Qg[0] = rb; Qg[1] = -(rb * u); Qg[2] = -(rb * w);
@@ -160,13 +162,13 @@ __device__ inline void ghost_fwd(const Phys& ph, int d, double zf, const double 
 }
 
 // adjoints of the ghost (aQg, aFg) -> adjoints of the interior data
-__device__ inline void ghost_vjp(const Phys& ph, double zf, const double Qi[4], const double aQg[4],
+__device__ inline void ghost_vjp(const Phys& ph, double zf, const double bg[2], const double Qi[4], const double aQg[4],
                                  const double aFg[4], double aQi[4], double aFi[4]) {
   aFi[0] = -aFg[0]; aFi[1] = aFg[1]; aFi[2] = aFg[2]; aFi[3] = -aFg[3];
   const double rho = Qi[0], ir = 1.0 / rho;
   const double u = Qi[1] * ir, w = Qi[2] * ir;
   double rb, pb, brb = 0.0, bpb = 0.0, bu = 0.0, bw = 0.0;
-  if (ph.gravity) background(ph, zf, rb, pb);
+  if (ph.gravity) { rb = bg[0]; pb = bg[1]; }
   else { rb = rho; pb = pressure(ph, Qi[0], Qi[1], Qi[2], Qi[3], zf); }
   // Qg0 = rb ; Qg1 = -rb u ; Qg2 = -rb w ; Qg3 = pb/gm1 + 1/2 rb (u^2+w^2) + rb g z
   brb += aQg[0] - aQg[1] * u - aQg[2] * w + aQg[3] * (0.5 * (u * u + w * w) + (ph.gravity ? ph.g * zf : 0.0));
@@ -195,7 +197,7 @@ __device__ inline void ghost_vjp(const Phys& ph, double zf, const double Qi[4], 
 // `reverse` needs from every node of the face.
 template <int n>
 struct FaceAdj {
-  double Qm[4], Fm[4], Qo[4], Fo[4], aG[4], zf, h;
+  double Qm[4], Fm[4], Qo[4], Fo[4], aG[4], bg[2], zf, h;
   int d, wall;
   bool lower;     // this cell is side R
 
@@ -222,7 +224,9 @@ struct FaceAdj {
         aG[v] += lift_adj_half<n>(a, o, f ^ 1, k, v);
       }
     } else {
-      ghost_fwd(ph, d, zf, Qm, Fm, Qo, Fo);
+      const double* b = a.bg + 2 * ((size_t)c * (n + 2) + (d == 0 ? k : n + (f & 1)));
+      bg[0] = b[0]; bg[1] = b[1];
+      ghost_fwd(ph, d, zf, bg, Qm, Fm, Qo, Fo);
     }
     double l, lv, ds = 0.0;
     eig_a(ph, d, lower ? Qo : Qm, zf, l, lv); sx[k] = l; sx[2 * n + k] = lv;
@@ -271,7 +275,7 @@ struct FaceAdj {
         }
       }
       double aQi[4], aFi[4];
-      ghost_vjp(ph, zf, Qm, aQg, aF, aQi, aFi);
+      ghost_vjp(ph, zf, bg, Qm, aQg, aF, aQi, aFi);
       for (int v = 0; v < 4; ++v) { aQm[v] += aQi[v]; aF[v] += aFi[v]; }
     }
     for (int v = 0; v < 4; ++v) { out[v * n + k] = aQm[v]; out[4 * n + v * n + k] = aF[v]; }
@@ -673,7 +677,7 @@ int launch_step_adjoint(const Group& g, const double* Qn, const double* lam_in, 
   }
   AdjArgs a;
   a.Qn = Qn; a.lam_in = lam_in; a.lam_out = lam_out; a.FD = fd; a.store = store;
-  a.clock = g.clock; a.geom = g.d_geom; a.nbr = g.d_nbr; a.gtab = g.d_gtab;
+  a.clock = g.clock; a.geom = g.d_geom; a.bg = g.d_bg; a.nbr = g.d_nbr; a.gtab = g.d_gtab;
   a.C = g.C; a.iters = g.iters;
   switch (g.n) {
     case 2: return adj_n<2>(g, a, s);

@@ -22,6 +22,7 @@ int launch_tv(const Group& g, int var, double Tr, double Tc, double* tv, int8_t*
 int launch_health(const Group& g, int* flag, hipStream_t s);
 int launch_regrid(int n, int C, const int* ops, const double* Qold, double* Qnew, const double* gtab,
                   hipStream_t s);
+int launch_background(const Group& g, int C, hipStream_t s);   // fills d_bg of C cells
 int launch_step_adjoint(const Group& g, const double* Qn, const double* lam_in, double* lam_out, double* store,
                         const double* fd, bool recompute, hipStream_t s);
 int launch_ic_theta(const Group& g, const double* thp, hipStream_t s);
@@ -378,8 +379,11 @@ static void free_group(Group& g) {
   if (g.d_gtab) (void)hipFree(g.d_gtab);
   if (g.d_scen) (void)hipFree(g.d_scen);
   if (g.d_part) (void)hipFree(g.d_part);
-  g.d_geom = nullptr; g.d_nbr = nullptr; g.d_gtab = nullptr; g.d_scen = nullptr; g.d_part = nullptr;
+  g.d_geom = nullptr; g.d_bg = nullptr; g.d_nbr = nullptr; g.d_gtab = nullptr; g.d_scen = nullptr; g.d_part = nullptr;
 }
+
+// doubles per cell of the geometry and background tables
+static size_t geom_doubles(const Group& g) { return 4 + 2 * ((size_t)g.n + 2); }
 
 // Allocate and upload a group's tables.
 static int upload_group(Group& g, const std::vector<double>& geom, const std::vector<int>& nbr,
@@ -390,7 +394,8 @@ static int upload_group(Group& g, const std::vector<double>& geom, const std::ve
     if (nbr[4 * k] == kFineSide || nbr[4 * k] == kCoarseSide) { g.nc = 1; break; }
   hipError_t e = hipSuccess;
   if (C) {
-    e = hipMalloc(&g.d_geom, sizeof(double) * 4 * C);
+    e = hipMalloc(&g.d_geom, sizeof(double) * geom_doubles(g) * C);
+    g.d_bg = g.d_geom + 4 * C;
     if (e == hipSuccess) e = hipMalloc(&g.d_nbr, sizeof(int) * 16 * C);
     if (e == hipSuccess && scen) e = hipMalloc(&g.d_scen, sizeof(int) * C);
   }
@@ -404,7 +409,11 @@ static int upload_group(Group& g, const std::vector<double>& geom, const std::ve
   }
   if (e == hipSuccess) e = hipMemcpy(g.d_gtab, gtab.data(), sizeof(double) * gtab.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) { free_group(g); return fail(ADG_EHIP, "upload failed"); }
-  return ADG_OK;
+  // the background table is complete before any stream can use the handle
+  int rc = launch_background(g, g.C, nullptr);
+  if (rc == ADG_OK && hipStreamSynchronize(nullptr) != hipSuccess) rc = fail(ADG_EHIP, "background table failed");
+  if (rc) free_group(g);
+  return rc;
 }
 
 static int need_state(adg_mesh* m) {
@@ -743,17 +752,18 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
     if (g.d_nbr) (void)hipFree(g.d_nbr);
     g.d_geom = nullptr; g.d_nbr = nullptr; m->cells_cap = 0;
     const int cap = H.C + H.C / 4 + 16;
-    if (hipMalloc(&g.d_geom, sizeof(double) * 4 * (size_t)cap) != hipSuccess ||
+    if (hipMalloc(&g.d_geom, sizeof(double) * geom_doubles(g) * (size_t)cap) != hipSuccess ||
         hipMalloc(&g.d_nbr, sizeof(int) * 16 * (size_t)cap) != hipSuccess) {
       if (g.d_geom) (void)hipFree(g.d_geom);
       g.d_geom = nullptr; g.C = 0;
       return fail(ADG_ENOMEM, "device allocation failed");
     }
     m->cells_cap = cap;
+    g.d_bg = g.d_geom + 4 * (size_t)cap;
   }
   if (H.C && (hipMemcpyAsync(g.d_geom, st + o_geom, b_geom, hipMemcpyHostToDevice, s) != hipSuccess ||
               hipMemcpyAsync(g.d_nbr, st + o_nbr, b_nbr, hipMemcpyHostToDevice, s) != hipSuccess ||
-              hipStreamSynchronize(s) != hipSuccess)) {
+              launch_background(g, H.C, s) != ADG_OK || hipStreamSynchronize(s) != hipSuccess)) {
     g.C = 0;
     return fail(ADG_EHIP, "upload failed");
   }

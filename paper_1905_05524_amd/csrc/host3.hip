@@ -71,7 +71,7 @@ int adg3_init_mesh(const adg_params* prm, const adg3_mesh_desc* mesh, adg3_mesh*
   m->ph = make_phys(*prm);
   build_basis(m->n, m->basis);
   const size_t tb = sizeof(double) * m->basis.gtab.size();
-  const size_t bb = sizeof(double) * 2 * (size_t)mesh->nz * m->n;
+  const size_t bb = sizeof(double) * 2 * (size_t)mesh->nz * (m->n + 2);
   if (hipMalloc(&m->d_gtab, tb + bb) != hipSuccess) { delete m; return fail(ADG_ENOMEM, "device allocation failed"); }
   m->d_bg = m->d_gtab + m->basis.gtab.size();
   if (hipMemcpy(m->d_gtab, m->basis.gtab.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {

@@ -16,13 +16,14 @@
 // three variables, not four, go through the divergences.
 //
 // What bounds it (counters at 243 x 243 cells, n = 7): the vector units are
-// busy 73 % of the time (8,640 vector instructions per cell), the LDS 63 %.
+// busy 72 % of the time (8,660 vector instructions per cell; 8,400 since the
+// background comes from a table), the LDS 63 %.
 // The kernel before it kept one node per lane and went through LDS for every
 // contraction of one time level at a time (26 writes and 30 reads per node
 // and level against 18 and 22 here, and 28 dependent LDS stages per sweep
 // against 6).  Per launch, before and now: 81 x 81 cells n = 7 190 and
-// 152 us, 243 x 243 1.48 and 1.21 ms; 81 x 81 n = 8 800 and 228 us, n = 6
-// 137 and 90-98 us, n = 5 87 and 45 us, n = 4 58 and 21 us, n = 3 29 and
+// 149 us, 243 x 243 1.47 and 1.17 ms; 81 x 81 n = 8 800 and 228 us, n = 6
+// 137 and 88 us, n = 5 87 and 45 us, n = 4 58 and 21 us, n = 3 29 and
 // 12 us, n = 2 17 and 9 us.
 //
 // LDS strides.  A probe of ds_read2_b64 and ds_write_b64 fits four passes of
@@ -112,9 +113,8 @@ struct RowsLay {
   static constexpr int IS = grid8 ? 55 : n == 8 ? 65 : n == 7 ? 49 : n == 6 ? 41 : n == 5 ? 25 : n == 4 ? 19 : n == 3 ? 10 : 4;
   static constexpr int VS = (n - 1) * (BS + JS + IS) + 1;
   // doubles per cell: the variables, or the three node slices of a single
-  // level and the background of its rows; with several cells the cell stride
-  // sets the banks of the next one
-  static constexpr int cell0 = 4 * VS > 12 * nn + n ? 4 * VS : 12 * nn + n;
+  // level; with several cells the cell stride sets the banks of the next one
+  static constexpr int cell0 = 4 * VS > 12 * nn ? 4 * VS : 12 * nn;
   static constexpr int cell = CB == 1 ? cell0 : n == 7 ? 1377 : n == 6 ? 964 : n == 5 ? 505 : n == 4 ? 292 : n == 3 ? 121 : cell0;
   static_assert(cell >= cell0, "the padded cell holds its arrays");
 };
@@ -161,8 +161,8 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   if constexpr (CB == 1) { fc.mu = uniform(fc.mu); fc.mu23 = uniform(fc.mu23); fc.kap = uniform(fc.kap); fc.gh = uniform(fc.gh); }
   // background at the node of the time column (row j = hi)
   const double zc = z0 + h * gt[GTab::XI * n + hi];
-  double rbc, pbc;
-  background(ph, zc, rbc, pbc);
+  const double* bg = a.bg + (size_t)cc * 2 * (n + 2);
+  const double rbc = bg[2 * hi], pbc = bg[2 * hi + 1];
   const double* Qc = a.Qin + (size_t)cc * sl;
   double* smm = S + L::cell;                           // [n][nn] density wave's source
 
@@ -171,10 +171,17 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   for (int v = 0; v < 4; ++v) X[0][v] = Qc[v * nn + r];
 
   // the density wave's energy source at the n time nodes (state-independent)
-  if (!PW && ms && act) {
-    const double x = x0 + h * gt[GTab::XI * n + lo];
-#pragma unroll 1
-    for (int b = 0; b < n; ++b) smm[b * nn + r] = mms_source(ph, x, zc, t0 + gt[GTab::XI * n + b] * dt);
+  if (!PW && ms) {
+    WavePhase* lev = reinterpret_cast<WavePhase*>(S);   // of the time levels, from the lanes with hi = 0
+    const double xi = gt[GTab::XI * n + lo], tb = xi * dt;
+    if (act && hi == 0) lev[lo] = wave_phase(ph, ph.mms_u * tb, ph.mms_w * tb);
+    sync();
+    if (act) {
+      const WavePhase w = wave_phase(ph, (x0 + h * xi) - ph.mms_u * t0, zc - ph.mms_w * t0);
+#pragma unroll
+      for (int b = 0; b < n; ++b) smm[b * nn + r] = mms_source(ph, w, lev[b]);
+    }
+    sync();
   }
 
   // Where there is one level only (first sweep, volume term) the contractions
@@ -244,12 +251,9 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   for (int b = 0; b < n; ++b)
 #pragma unroll
     for (int v = 0; v < 4; ++v) X[b][v] = R[v];
-  // background of the lane's row (j = lo), from the lanes of that row
-  sync();
-  double rbr = 0.0;
-  if (act) { S[r] = rbc; S[nn + r] = pbc; }
-  sync();
-  if (act) { rbr = S[lo * n]; fc.pb = S[nn + lo * n]; }
+  // background of the lane's row (j = lo)
+  const double rbr = bg[2 * lo];
+  fc.pb = bg[2 * lo + 1];
   fc.gz = ph.geff * (z0 + h * gt[GTab::XI * n + lo]);
   sync();
 
@@ -448,7 +452,6 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
       S[sl + v * nn + r] = v == 0 ? Qb[1] : Fxa[v > 0 ? v - 1 : 0];
       S[2 * sl + v * nn + r] = v == 0 ? Qb[2] : Fza[v > 0 ? v - 1 : 0];
     }
-    S[3 * sl + lo] = rbr;
   }
   sync();
   if (act || all) {
@@ -482,7 +485,7 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   }
   sync();
   if (valid) {
-    double Sb[4] = {0.0, 0.0, -ph.geff * (Qb[0] - S[3 * sl + hi]), 0.0};
+    double Sb[4] = {0.0, 0.0, -ph.geff * (Qb[0] - bg[2 * hi]), 0.0};
     if (!PW && ms) {
 #pragma unroll
       for (int b = 0; b < n; ++b) Sb[3] = fma(gt[GTab::W * n + b], smm[b * nn + r], Sb[3]);
@@ -536,7 +539,7 @@ template <int n>
 struct SplitLay : RowsLay<n, 1, 1> {
   using L = RowsLay<n, 1, 1>;
   static constexpr int buf = 4 * L::VS > 4 * L::nn ? 4 * L::VS : 4 * L::nn;
-  static constexpr int cell = 3 * buf + n;
+  static constexpr int cell = 3 * buf;
 };
 
 template <int n, bool PW>
@@ -557,7 +560,6 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
   double* XR = lds;              // iterate
   double* GX = lds + buf;        // gradients, fluxes and divergence along x
   double* GZ = lds + 2 * buf;    // the same along z
-  double* RB = lds + 3 * buf;    // background density of the rows
   const int rowo = hi * BS + lo * JS, colo = hi * BS + lo * IS, timo = hi * JS + lo * IS;
   const double* gt = a.gtab;
   const int s = a.scen ? a.scen[cell] : 0;
@@ -574,8 +576,9 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
   fc.kap = uniform(ph.kappa * ih * ph.iR);
   fc.gh = uniform(ph.geff * h);
   const double zc = z0 + h * gt[GTab::XI * n + hi];
-  double rbc, pbc;
-  background(ph, zc, rbc, pbc);
+  // background at the time column's node (row hi) and of the lane's row (lo)
+  const double* bg = a.bg + (size_t)cell * 2 * (n + 2);
+  const double rbc = bg[2 * hi], pbc = bg[2 * hi + 1], rbr = bg[2 * lo], pbr = bg[2 * lo + 1];
   // manufactured sources of this wavefront's variable at the node's n times
   double Sm[n];
 #pragma unroll
@@ -588,10 +591,6 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       paper_wave_source(ph, x, zc, t0 + gt[GTab::XI * n + b] * dt, S4);
       Sm[b] = w == 0 ? S4[0] : w == 1 ? S4[1] : w == 2 ? S4[2] : S4[3];
     }
-  } else if (ph.mms && w == 3) {
-    const double x = x0 + h * gt[GTab::XI * n + lo];
-#pragma unroll
-    for (int b = 0; b < n; ++b) Sm[b] = mms_source(ph, x, zc, t0 + gt[GTab::XI * n + b] * dt);
   }
 
   // first sweep: one residual serves all levels (slices [v][j][i])
@@ -622,6 +621,17 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       GZ[r] = fc.gh * (q[0] - rbc);
 #pragma unroll
       for (int v = 1; v < 4; ++v) { GX[v * nn + r] = Fx[v - 1]; GZ[v * nn + r] = Fz[v - 1]; }
+    } else if (!PW && ph.mms && w == 3) {
+      // the density wave's source, while another wavefront has the fluxes
+      const double xi = gt[GTab::XI * n + lo], tb = xi * dt;
+      const WavePhase lev = wave_phase(ph, ph.mms_u * tb, ph.mms_w * tb);   // lane b: level b
+      const WavePhase p = wave_phase(ph, (x0 + h * xi) - ph.mms_u * t0, zc - ph.mms_w * t0);
+#pragma unroll
+      for (int b = 0; b < n; ++b) {
+        const WavePhase l = {__shfl(lev.sx, b, kWave), __shfl(lev.cx, b, kWave), __shfl(lev.sz, b, kWave),
+                             __shfl(lev.cz, b, kWave)};
+        Sm[b] = mms_source(ph, p, l);
+      }
     }
     __syncthreads();
     if (t < 6 * n) {
@@ -636,7 +646,6 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       for (int m = 0; m < n; ++m) d[m * st] = out[m];
     }
   }
-  if (w == 0 && act && lo == 0) RB[hi] = rbc;
   __syncthreads();
   double X[n];
   {
@@ -645,13 +654,8 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
 #pragma unroll
     for (int b = 0; b < n; ++b) X[b] = R;
   }
-  // the lane's row: background density read back, pressure from its height
-  const double rbr = RB[lo];
-  {
-    const int src = L::grid8 ? 8 * lo : n * lo;
-    fc.pb = __shfl(pbc, src, kWave);
-    fc.gz = ph.geff * (z0 + h * gt[GTab::XI * n + lo]);
-  }
+  fc.pb = pbr;
+  fc.gz = ph.geff * (z0 + h * gt[GTab::XI * n + lo]);
 
   // gradients of the iterate: this wavefront's variable along x and z
   auto gradients = [&] {
@@ -810,7 +814,7 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
   __syncthreads();
   if (act) {
     double Sb = 0.0;
-    if (w == 2) Sb = -ph.geff * (XR[r] - RB[hi]);
+    if (w == 2) Sb = -ph.geff * (XR[r] - bg[2 * hi]);
     if (PW || (ph.mms && w == 3)) {
 #pragma unroll
       for (int b = 0; b < n; ++b) Sb = fma(gt[GTab::W * n + b], Sm[b], Sb);
@@ -844,10 +848,12 @@ constexpr int wave_cells(int n) { return n == 2 ? 16 : n == 3 ? 7 : n == 4 ? 4 :
 // The kernel of a launch.  Measured per predictor launch (us):
 //   four wavefronts per cell against one-wavefront workgroups: n = 7,
 //     21x21 25.5 / 30.3, 27x27 31.4 / 34.8, 30x30 43.8 / 35.4; n = 6, 27x27
-//     24.4 / 24.7, 30x30 28.8 / 24.8; n = 5, 15x15 13.2 / 15.8, 24x24
-//     19.0 / 17.1; n = 4, 15x15 9.6 / 11.5, 27x27 13.5 / 11.5.  Three such
-//     workgroups share a CU at n = 6 and 7: up to 768 cells there (one round
-//     of the 256 CUs), up to 384 below.
+//     24.4 / 24.7, 30x30 28.8 / 24.8; n = 5, 15x15 13.2 / 15.8, 22x22
+//     15.0 / 15.1 (16.4 / 17.0 with the density wave's source), 23x23
+//     17.4 / 16.1; n = 4, 15x15 9.6 / 11.5, 20x20 10.1 / 10.7, 23x23
+//     11.6 / 10.8; n = 3, 20x20 6.9 / 7.7, 27x27 7.9 / 7.7; n = 2, 31x31
+//     7.0 / 8.3.  Three such workgroups share a CU at n = 6 and 7: up to 768
+//     cells there (one round of the 256 CUs); up to 512 below, 1024 at n = 2.
 //   n = 6, one cell per wavefront (36 lanes) against three cells on two
 //     (108 of 128): 45x45 39.2 / 39.8, 55x55 53.0 / 44.8, 81x81 110 / 98;
 //     seven cells on four (252 of 256) 243x243 674 / 653, as its larger
@@ -866,7 +872,7 @@ static Kernel pick(const Group& g) {
     if (g.cpw == 1 && g.wpb == 1) return Kernel::kCell;
     return g.cpw == 1 ? Kernel::kPacked : Kernel::kWave;
   }
-  if (g.C <= (g.n >= 6 ? 768 : 384)) return Kernel::kSplit;
+  if (g.C <= (g.n >= 6 ? 768 : g.n == 2 ? 1024 : 512)) return Kernel::kSplit;
   if (g.n == 6) return g.C <= 2048 ? Kernel::kCell : Kernel::kPacked;
   if (g.n == 5) return g.C <= 4096 ? Kernel::kWave : Kernel::kPacked;
   return Kernel::kWave;

@@ -125,12 +125,13 @@ __device__ inline void eig3(const Phys& ph, int d, const double q[5], double zf,
 // (the energy flux around twice the background heat flux kappa g / cp through
 // horizontal walls) and repeats it for the momenta.  Without gravity the
 // interior density and pressure stand in for the background.
-__device__ inline void wall_ghost3(const Phys& ph, int d, double zf, const double Qi[5], const double Fi[5],
-                                   double Qg[5], double Fg[5]) {
+// bg: the background at the face node.
+__device__ inline void wall_ghost3(const Phys& ph, int d, double zf, const double bg[2], const double Qi[5],
+                                   const double Fi[5], double Qg[5], double Fg[5]) {
   const double ir = 1.0 / Qi[0];
   const double u[3] = {Qi[1] * ir, Qi[2] * ir, Qi[3] * ir};
   double rb, pb;
-  if (ph.gravity) background(ph, zf, rb, pb);
+  if (ph.gravity) { rb = bg[0]; pb = bg[1]; }
   else { rb = Qi[0]; pb = pressure3(ph, Qi, zf); }
   const double geo = ph.gravity ? rb * (ph.g * zf) : 0.0;
   Qg[0] = rb;
@@ -144,15 +145,16 @@ __device__ inline void wall_ghost3(const Phys& ph, int d, double zf, const doubl
   Fg[4] = 2.0 * qbg - Fi[4];
 }
 
-// Background density and pressure at the node rows of every layer of cells,
-// once per handle: the predictor would spend a tenth of its instructions on
+// Background density and pressure at the node rows, the bottom and the top of
+// every layer of cells, once per handle: the predictor would spend a tenth of its instructions on
 // the power function (250 of 2,500 to 4,500 per node at n = 2 to 4).
 __global__ void k_background3(Phys ph, Args3 a, int n, double* bg) {
   const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= (long long)a.nz * n) return;
-  const int ck = (int)(g / n), k = (int)(g % n);
+  if (g >= (long long)a.nz * (n + 2)) return;
+  const int ck = (int)(g / (n + 2)), k = (int)(g % (n + 2));
+  const double zc = a.z0 + ck * a.h;
   double rb, pb;
-  background(ph, (a.z0 + ck * a.h) + a.h * a.gtab[GTab::XI * n + k], rb, pb);
+  background(ph, k < n ? zc + a.h * a.gtab[GTab::XI * n + k] : (k > n ? zc + a.h : zc), rb, pb);
   bg[2 * g] = rb;
   bg[2 * g + 1] = pb;
 }
@@ -251,10 +253,10 @@ __global__ __launch_bounds__(kThreads3) void k_pred3(Phys ph, Tab<n> tb, Args3 a
   const double h = a.h;
   const int ck = c / (a.nx * a.ny);
   const double z = (a.z0 + ck * h) + h * a.gtab[GTab::XI * n + k];
-  const double rb = a.bg[2 * (ck * n + k)];
+  const double rb = a.bg[2 * (ck * (n + 2) + k)];
   FluxC3 fc = flux_consts3(ph, h);
   fc.gz = ph.geff * z;
-  fc.pb = a.bg[2 * (ck * n + k) + 1];
+  fc.pb = a.bg[2 * (ck * (n + 2) + k) + 1];
   const double dt = a.clock[1], sdt = -dt / h;
   double Di[n], Dj[n], Dk[n];
 #pragma unroll
@@ -446,10 +448,10 @@ __global__ __launch_bounds__(kWave * kW64Cells, 3) void k_pred3_w64(Phys ph, Tab
   const double h = a.h;
   const int ck = c / (a.nx * a.ny);
   const double z = (a.z0 + ck * h) + h * a.gtab[GTab::XI * n + k];
-  const double rb = a.bg[2 * (ck * n + k)];
+  const double rb = a.bg[2 * (ck * (n + 2) + k)];
   FluxC3 fc = flux_consts3(ph, h);
   fc.gz = ph.geff * z;
-  fc.pb = a.bg[2 * (ck * n + k) + 1];
+  fc.pb = a.bg[2 * (ck * (n + 2) + k) + 1];
   const double dt = a.clock[1], ih = 1.0 / h;
   const Tab4 D = tab4(a.gtab + GTab::d(n), r);
   const double one = (r & 3) == (r >> 4) ? 1.0 : 0.0;
@@ -650,8 +652,8 @@ __global__ __launch_bounds__(Rows3<n>::NT, n == 6 ? 1 : 2) void k_pred3_rows(Phy
   double* xp = lds + xb * L::SB + xk * L::SK + xj * L::SJ;
   FluxC3 fc = flux_consts3(ph, h);
   fc.gz = ph.geff * ((a.z0 + layer * h) + h * a.gtab[GTab::XI * n + xk]);
-  const double rb = a.bg[2 * (layer * n + xk)];
-  fc.pb = a.bg[2 * (layer * n + xk) + 1];
+  const double rb = a.bg[2 * (layer * (n + 2) + xk)];
+  fc.pb = a.bg[2 * (layer * (n + 2) + xk) + 1];
   // planes: of all variables, and of the four with a flux to contract
   const int pb5 = tid / (5 * n), pb4 = tid / (4 * n);
   double* p5 = lds + pb5 * L::SB + (tid / n) % 5 * VS + tid % n * L::SI;
@@ -888,7 +890,7 @@ __global__ __launch_bounds__(Rows3<n>::NT, n == 6 ? 1 : 2) void k_pred3_rows(Phy
       Wj[m] = a.gtab[GTab::dw(n) + j * n + m];
       Wk[m] = a.gtab[GTab::dw(n) + k * n + m];
     }
-    const double Sb = -ph.geff * (Qb[0] - a.bg[2 * (layer * n + k)]);
+    const double Sb = -ph.geff * (Qb[0] - a.bg[2 * (layer * (n + 2) + k)]);
     double* Qsc = a.Qs + (size_t)c * 5 * nd + r;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
@@ -946,7 +948,7 @@ __global__ __launch_bounds__(kThreads3) void k_corr3(Phys ph, Args3 a) {
     if (outside && !wall) np = np < 0 ? np + dim : np - dim;
     const double zf = f == 4 ? zc : (f == 5 ? zc + h : zc + h * a.gtab[GTab::XI * n + s]);
     if (wall) {
-      wall_ghost3(ph, d, zf, Qo, Fo, Qn, Fn);
+      wall_ghost3(ph, d, zf, a.bg + 2 * (ck * (n + 2) + (d == 2 ? n + hi : s)), Qo, Fo, Qn, Fn);
     } else {
       const int o = d == 0 ? (ck * a.ny + cj) * a.nx + np
                            : (d == 1 ? (ck * a.ny + np) * a.nx + ci : (np * a.ny + cj) * a.nx + ci);
@@ -1162,7 +1164,7 @@ int launch_dt3(const Phys& ph, int n, const Args3& a, hipStream_t s) {
   ADG3_DISPATCH(dt3_n, n, ph, a, s);
 }
 int launch_background3(const Phys& ph, int n, const Args3& a, double* bg, hipStream_t s) {
-  const long long tot = (long long)a.nz * n;
+  const long long tot = (long long)a.nz * (n + 2);
   hipLaunchKernelGGL(k_background3, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, ph, a, n, bg);
   return check_launch("background3");
 }

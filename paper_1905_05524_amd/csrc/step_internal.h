@@ -78,6 +78,7 @@ struct StepArgs {
   double* clock;        // [S][4]: t, dt, (unused), steps
   const int* scen;      // [C] scenario of each cell (NULL: scenario 0)
   const double* geom;   // [C][4]
+  const double* bg;     // [C][n + 2][2]
   const int* nbr;       // [C][4][4]
   const double* gtab;
   double* iter_store;   // optional [C][iters][n][4][n][n]: Picard iterates q^1..q^I (adjoint)
