@@ -39,7 +39,7 @@ int launch_dt3(const Phys& ph, int n, const Args3& a, hipStream_t s);
 int launch_init3(const Phys& ph, int n, const Args3& a, int kind, const Bubbles3& B, double t0, double* Q,
                  hipStream_t s);
 int launch_health3(const Phys& ph, int n, const Args3& a, int* flag, hipStream_t s);
-int launch_clock(double* clock, const double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
+int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
                  int update, hipStream_t s);
 
 }  // namespace adg

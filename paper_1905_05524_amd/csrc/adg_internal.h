@@ -350,11 +350,35 @@ __device__ inline double recip(double x) {
   return fma(r, e, r);
 }
 
-// max over the 64 lanes of a wavefront (butterfly, fixed order)
+// Lane exchange within rows of 16 lanes through the data-parallel primitives
+// (no LDS round trip).
+template <int ctrl>
+__device__ inline double dpp(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, ctrl, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), ctrl, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ inline double lane_value(double v, int lane) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// max over groups of 4 lanes, of 16 lanes, and over the wavefront: lane xor 1
+// and 2 (quad permutations), mirrors within 8 and 16 lanes, then the four rows
+__device__ inline double quad_max(double v) {
+  v = fmax(v, dpp<0xB1>(v));
+  return fmax(v, dpp<0x4E>(v));
+}
+__device__ inline double row_max(double v) {
+  v = quad_max(v);
+  v = fmax(v, dpp<0x141>(v));
+  return fmax(v, dpp<0x140>(v));
+}
 __device__ inline double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-  return v;
+  v = row_max(v);
+  return fmax(fmax(lane_value(v, 0), lane_value(v, 16)), fmax(lane_value(v, 32), lane_value(v, 48)));
 }
 __device__ inline double wave_sum(double v) {
 #pragma unroll

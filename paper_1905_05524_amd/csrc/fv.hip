@@ -39,7 +39,7 @@
 
 namespace adg {
 
-int launch_clock(double* clock, const double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
+int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
                  int update, hipStream_t s);
 
 constexpr int kFvThreads = 256;

@@ -12,7 +12,7 @@ namespace adg {
 int launch_predictor(const Group& g, double* store, hipStream_t s);
 int launch_corrector(const Group& g, hipStream_t s);
 int launch_cell_dt(const Group& g, hipStream_t s);
-int launch_clock(double* clock, const double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
+int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
                  int update, hipStream_t s);
 int max_cpw(int n);
 int launch_init_state(const Group& g, int c0, int count, int kind, int nbub, const double* d_bub, double t0,

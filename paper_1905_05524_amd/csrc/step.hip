@@ -6,7 +6,7 @@
 // region, synchronised at wavefront level only.  In a cell, lane (slot, l)
 // with l < n*n owns spatial node (j, i) = (l / n, l % n); in the face phase
 // lane (slot, f, k) handles face f at node k.  CPW and WPB are template
-// parameters picked by the launch shape.
+// parameters picked by order, or by the caller's launch shape.
 #include "step_internal.h"
 
 namespace adg {
@@ -43,10 +43,13 @@ __device__ inline void wall_ghost(const Phys& ph, int d, double zf, const double
   Fg[3] = 2.0 * qbg - Fi[3];
 }
 
-__device__ inline void eig(const Phys& ph, int d, const double q[4], double zf, double& lam, double& lv) {
-  const double ir = 1.0 / q[0];
-  const double p = pressure(ph, q[0], q[1], q[2], q[3], zf);
-  lam = fabs(q[1 + d] * ir) + sqrt(ph.gamma * p * ir);
+// |v| + c and lambda_v for the larger of the momenta ma, mb (one twice: the
+// normal speed of a face)
+__device__ inline void eig(const Phys& ph, const double q[4], double ma, double mb, double z, double& lam, double& lv) {
+  const double ir = recip(q[0]);
+  const double ke = fma(q[1], q[1], q[2] * q[2]) * ir;                        // rho |v|^2
+  const double p = ph.gm1 * (fma(-0.5, ke, q[3]) - q[0] * (ph.geff * z));
+  lam = fmax(fabs(ma), fabs(mb)) * ir + sqrt(ph.gamma * p * ir);
   lv = ph.lv_coef * ir;
 }
 
@@ -74,12 +77,6 @@ __device__ inline void prolong_face(const double* FD, const double* gt, int cf, 
   }
 }
 
-__device__ inline void rusanov_flux(double s, const double QL[4], const double FL[4], const double QR[4],
-                                    const double FR[4], double G[4]) {
-#pragma unroll
-  for (int v = 0; v < 4; ++v) G[v] = 0.5 * (FL[v] + FR[v]) - 0.5 * s * (QR[v] - QL[v]);
-}
-
 // Per cell: lanes (slot, f, k) handle face f at node k.  The Rusanov speed s
 // is one value per (sub-)face: max over the face nodes of both sides of the
 // normal eigenvalue bound, plus the viscous penalty 2 eta max lambda_v with
@@ -93,7 +90,8 @@ __global__ __launch_bounds__(kWave * WPB) void k_corrector(Phys ph, StepArgs a) 
   using L = Lay<n, CPW>;
   constexpr int nn = L::nn, sl = L::sl;
   extern __shared__ double lds[];
-  __shared__ double slam[WPB][2][kWave];
+  constexpr bool by_lds = CPW > 1 && nn != 4 && nn != 16;   // maxima over a cell's nodes
+  __shared__ double slam[by_lds ? WPB : 1][2][by_lds ? kWave : 1];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   double* wl = lds + (size_t)wave * CPW * L::corr_cell;
   const int cell0 = (blockIdx.x * WPB + wave) * CPW;
@@ -126,8 +124,19 @@ __global__ __launch_bounds__(kWave * WPB) void k_corrector(Phys ph, StepArgs a) 
   const bool lower = (f & 1) == 0;   // face on the lower side: this cell is R
   int kind = kWall, nb1 = 0, nb2 = 0, nb3 = 0;
   double hf = 1.0, z0f = 0.0;
-  double Qm[4], Fm[4], Qo[4], Fo[4];
+  // Rusanov flux G = S/2 - (s/2) J from the flux sums S and the jumps J of the
+  // face (three sub-faces on the coarse side)
+  constexpr int NF = NC ? 3 : 1;
+  double Sf[NF][4], Jf[NF][4];
+  auto sides = [&](int s, const double Qm[4], const double Fm[4], const double Qo[4], const double Fo[4]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      Sf[s][v] = Fm[v] + Fo[v];
+      Jf[s][v] = lower ? Qm[v] - Qo[v] : Qo[v] - Qm[v];
+    }
+  };
   if (fl) {
+    double Qm[4], Fm[4], Qo[4], Fo[4], l1, v1, l2, v2;
     const int* nb = a.nbr + (size_t)fc * 16 + f * 4;
     kind = nb[0]; nb1 = nb[1]; nb2 = nb[2]; nb3 = nb[3];
     hf = a.geom[4 * fc + 2]; z0f = a.geom[4 * fc + 1];
@@ -137,21 +146,21 @@ __global__ __launch_bounds__(kWave * WPB) void k_corrector(Phys ph, StepArgs a) 
       if (kind == kConforming) load_face<n>(a.FD, nb1, f ^ 1, k, Qo, Fo);
       else if (NC && kind == kFineSide) prolong_face<n>(a.FD, gt, nb1, f ^ 1, nb2, k, Qo, Fo);
       else wall_ghost(ph, d, zf, a.bg + 2 * ((size_t)fc * (n + 2) + (d == 0 ? k : n + (f & 1))), Qm, Fm, Qo, Fo);
-      double l1, v1, l2, v2;
-      eig(ph, d, Qm, zf, l1, v1);
-      eig(ph, d, Qo, zf, l2, v2);
+      eig(ph, Qm, Qm[1 + d], Qm[1 + d], zf, l1, v1);
+      eig(ph, Qo, Qo[1 + d], Qo[1 + d], zf, l2, v2);
+      sides(0, Qm, Fm, Qo, Fo);
       sL[(f * 3) * n + k] = fmax(l1, l2);
       sV[(f * 3) * n + k] = fmax(v1, v2);
     } else if constexpr (NC) {
+#pragma unroll
       for (int s = 0; s < 3; ++s) {
         const int fine = s == 0 ? nb1 : (s == 1 ? nb2 : nb3);
         const double zf = (d == 0) ? z0f + hf * (s + gt[GTab::XI * n + k]) / 3.0 : z0f + ((f & 1) ? hf : 0.0);
-        double Qp[4], Fp[4], Qx[4], Fx[4];
-        prolong_face<n>(a.FD, gt, fc, f, s, k, Qp, Fp);
-        load_face<n>(a.FD, fine, f ^ 1, k, Qx, Fx);
-        double l1, v1, l2, v2;
-        eig(ph, d, Qp, zf, l1, v1);
-        eig(ph, d, Qx, zf, l2, v2);
+        prolong_face<n>(a.FD, gt, fc, f, s, k, Qm, Fm);
+        load_face<n>(a.FD, fine, f ^ 1, k, Qo, Fo);
+        eig(ph, Qm, Qm[1 + d], Qm[1 + d], zf, l1, v1);
+        eig(ph, Qo, Qo[1 + d], Qo[1 + d], zf, l2, v2);
+        sides(s, Qm, Fm, Qo, Fo);
         sL[(f * 3 + s) * n + k] = fmax(l1, l2);
         sV[(f * 3 + s) * n + k] = fmax(v1, v2);
       }
@@ -164,25 +173,18 @@ __global__ __launch_bounds__(kWave * WPB) void k_corrector(Phys ph, StepArgs a) 
 #pragma unroll
       for (int m = 1; m < n; ++m) { lam = fmax(lam, sL[(f * 3) * n + m]); lv = fmax(lv, sV[(f * 3) * n + m]); }
       const double s = lam + 2.0 * (eta0 / hf) * lv;
-      double G[4];
-      if (lower) rusanov_flux(s, Qo, Fo, Qm, Fm, G);
-      else rusanov_flux(s, Qm, Fm, Qo, Fo, G);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) sG[(f * 4 + v) * n + k] = G[v];
+      for (int v = 0; v < 4; ++v) sG[(f * 4 + v) * n + k] = 0.5 * Sf[0][v] - 0.5 * s * Jf[0][v];
     } else if constexpr (NC) {
       const double hfine = hf / 3.0;
+#pragma unroll
       for (int s = 0; s < 3; ++s) {
-        const int fine = s == 0 ? nb1 : (s == 1 ? nb2 : nb3);
         double lam = sL[(f * 3 + s) * n], lv = sV[(f * 3 + s) * n];
+#pragma unroll
         for (int m = 1; m < n; ++m) { lam = fmax(lam, sL[(f * 3 + s) * n + m]); lv = fmax(lv, sV[(f * 3 + s) * n + m]); }
         const double sp = lam + 2.0 * (eta0 / hfine) * lv;
-        double Qp[4], Fp[4], Qx[4], Fx[4], G[4];
-        prolong_face<n>(a.FD, gt, fc, f, s, k, Qp, Fp);
-        load_face<n>(a.FD, fine, f ^ 1, k, Qx, Fx);
-        if (lower) rusanov_flux(sp, Qx, Fx, Qp, Fp, G);
-        else rusanov_flux(sp, Qp, Fp, Qx, Fx, G);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sGs[((f * 3 + s) * 4 + v) * n + k] = G[v];
+        for (int v = 0; v < 4; ++v) sGs[((f * 3 + s) * 4 + v) * n + k] = 0.5 * Sf[s][v] - 0.5 * sp * Jf[s][v];
       }
     }
   }
@@ -225,11 +227,7 @@ __global__ __launch_bounds__(kWave * WPB) void k_corrector(Phys ph, StepArgs a) 
     }
     if (!ph.fixed_dt) {
       const double zz = z0 + h * gt[GTab::XI * n + jz];
-      double l0, lv0, l1, lv1;
-      eig(ph, 0, q, zz, l0, lv0);
-      eig(ph, 1, q, zz, l1, lv1);
-      lam_n = fmax(l0, l1);
-      lv_n = lv0;
+      eig(ph, q, q[1], q[2], zz, lam_n, lv_n);
     }
   }
   if (!ph.fixed_dt) {
@@ -239,6 +237,12 @@ __global__ __launch_bounds__(kWave * WPB) void k_corrector(Phys ph, StepArgs a) 
     if constexpr (CPW == 1) {
       lm = wave_max(lam_n);   // lanes without a node hold 0
       vm = wave_max(lv_n);
+    } else if constexpr (nn == 4) {
+      lm = quad_max(lam_n);
+      vm = quad_max(lv_n);
+    } else if constexpr (nn == 16) {
+      lm = row_max(lam_n);
+      vm = row_max(lv_n);
     } else {
       slam[wave][0][lane] = lam_n;
       slam[wave][1][lane] = lv_n;
@@ -276,11 +280,7 @@ __global__ __launch_bounds__(kWave) void k_cell_dt(Phys ph, StepArgs a) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) q[v] = Qc[v * nn + lane];
     const double z = z0 + h * a.gtab[GTab::XI * n + jz];
-    double l0, lv0, l1, lv1;
-    eig(ph, 0, q, z, l0, lv0);
-    eig(ph, 1, q, z, l1, lv1);
-    lam = fmax(l0, l1);
-    lvm = lv0;
+    eig(ph, q, q[1], q[2], z, lam, lvm);
   }
   lam = wave_max(lam);
   lvm = wave_max(lvm);
@@ -293,9 +293,11 @@ __global__ __launch_bounds__(kWave) void k_cell_dt(Phys ph, StepArgs a) {
 // Clock update, one workgroup per scenario: if advance, t += dt and
 // steps += 1; if update, dt <- min of the CFL candidates of the scenario's
 // cells [beg[s], end[s]) (min is exact, so the result is order independent).
+// Every stride-th entry of dtc is read.
 constexpr int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void k_clock(double* clock, const double* dtc, const int* beg,
-                                                           const int* end, int C, int advance, int update) {
+                                                           const int* end, int C, int stride, int advance,
+                                                           int update) {
   __shared__ double sm[kReduceThreads / kWave];
   const int s = blockIdx.x, t = threadIdx.x;
   const int b0 = beg ? beg[s] : 0, b1 = end ? end[s] : C;
@@ -307,11 +309,12 @@ __global__ __launch_bounds__(kReduceThreads) void k_clock(double* clock, const d
     // four independent loads in flight per thread
     int c = b0 + t;
     for (; c + 3 * kReduceThreads < b1; c += 4 * kReduceThreads) {
-      const double a0 = dtc[c], a1 = dtc[c + kReduceThreads], a2 = dtc[c + 2 * kReduceThreads],
-                   a3 = dtc[c + 3 * kReduceThreads];
+      const double* p = dtc + (size_t)c * stride;
+      const double a0 = p[0], a1 = p[(size_t)kReduceThreads * stride], a2 = p[(size_t)2 * kReduceThreads * stride],
+                   a3 = p[(size_t)3 * kReduceThreads * stride];
       m = fmin(m, fmin(fmin(a0, a1), fmin(a2, a3)));
     }
-    for (; c < b1; c += kReduceThreads) m = fmin(m, dtc[c]);
+    for (; c < b1; c += kReduceThreads) m = fmin(m, dtc[(size_t)c * stride]);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) m = fmin(m, __shfl_xor(m, o, kWave));
@@ -322,6 +325,24 @@ __global__ __launch_bounds__(kReduceThreads) void k_clock(double* clock, const d
     for (int k = 1; k < kReduceThreads / kWave; ++k) r = fmin(r, sm[k]);
     if (advance) { clock[4 * s + 0] = t_old + dt_old; clock[4 * s + 3] = n_old + 1.0; }
     if (update) clock[4 * s + 1] = r;
+  }
+}
+
+// Minimum of every chunk of len candidates, left in the chunk's first entry.
+constexpr int kChunkThreads = 256;
+__global__ __launch_bounds__(kChunkThreads) void k_chunk_min(double* dtc, int C, int len) {
+  __shared__ double sm[kChunkThreads / kWave];
+  const int t = threadIdx.x;
+  const long long b0 = (long long)blockIdx.x * len, b1 = min(b0 + len, (long long)C);
+  double m = __builtin_inf();
+  for (long long c = b0 + t; c < b1; c += kChunkThreads) m = fmin(m, dtc[c]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) m = fmin(m, __shfl_xor(m, o, kWave));
+  if ((t & (kWave - 1)) == 0) sm[t / kWave] = m;
+  __syncthreads();   // every candidate of the chunk read before its first is overwritten
+  if (t == 0) {
+    for (int k = 1; k < kChunkThreads / kWave; ++k) m = fmin(m, sm[k]);
+    dtc[b0] = m;
   }
 }
 
@@ -385,10 +406,19 @@ static int corr_w(const Group& g, hipStream_t s) {
     default: return fail(ADG_EINVAL, "waves per block must be 1, 2 or 4");
   }
 }
-// cells per wavefront: 1, 2 or 4 (while CPW * n^2 <= 64)
+// Cells per wavefront of a launch without a shape of its own: as many as have
+// a lane for every node and every face node.  One cell for each wavefront
+// takes 50 us for 200 x 200 cells at every n up to 6 (1.2 ns a cell, the rate
+// of the wavefronts); with them packed, corrector and clock take 19 us at
+// n = 2, 23 at n = 3, 28 at n = 4 and 38 at n = 5, near the time of their
+// memory traffic, and no mesh of 81 to 3,600 cells gets slower.  At n = 6 and 7
+// (51 and 53 us) the traffic bounds one cell per wavefront already.
+constexpr int corr_cells(int n) { return n == 2 ? 8 : n == 3 ? 5 : n == 4 ? 4 : n == 5 ? 2 : 1; }
+// cells per wavefront of a launch shape: 1, 2 or 4 (while CPW * n^2 <= 64)
 template <int n>
 static int corr_n(const Group& g, hipStream_t s) {
   constexpr int nn = n * n;
+  if (g.lv < 0) return launch_corr_t<n, corr_cells(n), 1>(g, s);
   if (g.cpw == 1) return corr_w<n, 1>(g, s);
   if constexpr (2 * nn <= kWave) { if (g.cpw == 2) return corr_w<n, 2>(g, s); }
   if constexpr (4 * nn <= kWave) { if (g.cpw == 4) return corr_w<n, 4>(g, s); }
@@ -416,10 +446,22 @@ static int dt_n(const Group& g, hipStream_t s) {
 int launch_corrector(const Group& g, hipStream_t s) { ADG_DISPATCH_N(corr_n, g, s); }
 int launch_cell_dt(const Group& g, hipStream_t s) { ADG_DISPATCH_N(dt_n, g, s); }
 
-int launch_clock(double* clock, const double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
-                 int update, hipStream_t s) {
+int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance, int update,
+                 hipStream_t s) {
   if (nscen <= 0) return ADG_OK;
-  hipLaunchKernelGGL(k_clock, dim3(nscen), dim3(kReduceThreads), 0, s, clock, dtc, beg, end, C, advance, update);
+  // One mesh of many cells: one workgroup reads no more than 50 GB/s, so 256
+  // of them reduce chunks first.  Corrector and clock in one stage and in two:
+  // 22,500 cells of n = 2 12.2 and 11.9 us (a step 32.1 and 32.5), 32,400 17.3
+  // and 15.6, 62,500 26.6 and 22.5, 531,441 of n = 7 868 and 791.
+  constexpr int kChunks = 256, kOneStage = 24576;
+  int stride = 1;
+  if (!beg && update && C > kOneStage) {
+    stride = (C + kChunks - 1) / kChunks;
+    const int chunks = (C + stride - 1) / stride;
+    hipLaunchKernelGGL(k_chunk_min, dim3(chunks), dim3(kChunkThreads), 0, s, dtc, C, stride);
+    C = chunks;
+  }
+  hipLaunchKernelGGL(k_clock, dim3(nscen), dim3(kReduceThreads), 0, s, clock, dtc, beg, end, C, stride, advance, update);
   return check_launch("clock");
 }
 
