@@ -350,6 +350,21 @@ __device__ inline double recip(double x) {
   return fma(r, e, r);
 }
 
+// Square root: the hardware estimate of 1/sqrt(x), one coupled Newton step for
+// root and half reciprocal and a last correction of the root (within an ulp);
+// 0 and infinity as they are.  Without the library's scaling for the smallest
+// numbers, 12 instructions instead of 20.
+__device__ inline double root(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, x), h, g);
+  g = fma(fma(-g, g, x), h, g);
+  return __builtin_amdgcn_class(x, 0x260) ? x : g;   // +-0, +infinity
+}
+
 // Lane exchange within rows of 16 lanes through the data-parallel primitives
 // (no LDS round trip).
 template <int ctrl>

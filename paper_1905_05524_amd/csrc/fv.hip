@@ -9,7 +9,7 @@
 //                 a fifth wavefront the ring of cells around the tile
 //                 (only the face value the tile needs); the evolved face
 //                 values meet in LDS; every face of the tile gets its
-//                 Rusanov flux once (one job per face, 2.25 per cell); each
+//                 Rusanov flux once (2.125 per cell); each
 //                 thread then updates its cell and writes the new value: in
 //                 place for the tile's interior cells, to a second buffer
 //                 for its two outer layers (the only cells neighbouring tiles
@@ -82,7 +82,7 @@ __device__ inline double fv_flux(const Phys& ph, const double q[4], double z, do
   F[1] = q[1] * un + (d == 0 ? pm : 0.0);
   F[2] = q[2] * un + (d == 1 ? pm : 0.0);
   F[3] = un * (q[3] + p);
-  return fabs(un) + sqrt(ph.gamma * p * ir);
+  return fabs(un) + root(ph.gamma * p * ir);
 }
 
 // wall ghost state of q at height z (background rb, pb there)
@@ -99,8 +99,10 @@ __device__ inline void fv_ghost(const Phys& ph, const double q[4], double z, dou
 }
 
 __device__ inline double van_albada(double a, double b) {
-  if (!(a * b > 0.0)) return 0.0;
-  return a * b * (a + b) * recip(a * a + b * b);
+  // both results formed and one selected: eight branches per cell would run
+  // one after the other
+  const double ab = a * b, r = ab * (a + b) * recip(fma(a, a, b * b));
+  return ab > 0.0 ? r : 0.0;
 }
 
 // G = (F_L + F_R)/2 - s/2 (Q_R - Q_L), s the larger of the two signal speeds
@@ -115,24 +117,17 @@ __device__ inline void load4(const double* p, double q[4]) {
   q[0] = a.x; q[1] = a.y; q[2] = b.x; q[3] = b.y;
 }
 
-// Steps 1-2 of the scheme for cell (i, j) inside the domain: the evolved
-// face values fv[W, E, S, N][var] and the half-step density increment.  One
-// direction at a time (its two neighbours, then its two face fluxes), so few
+// Steps 1-2 of the scheme for a cell of row j: the evolved face values fv[W, E,
+// S, N][var] and the half-step density increment, from the cell's value q and
+// those of its neighbours.  x(nw, ne) and z(ns, nn) supply the neighbours, one
+// direction at a time (its neighbours, then its two face fluxes), so few
 // values are live at once.
-__device__ inline void fv_predict_cell(const Phys& ph, const FvArgs& a, int i, int j, double dt, double fv[4][4],
-                                       double& inc0) {
-  const int c = j * a.nx + i;
-  const double* bg = a.bg + 15 * j;
-  double q[4];
-  load4(a.Q + 4 * (size_t)c, q);
-  {  // x: west and east neighbours (wall ghost or periodic image at the domain edge)
+template <class X, class Z>
+__device__ inline void fv_predict_from(const Phys& ph, const FvArgs& a, const double* bg, double dt, const double q[4],
+                                       X x, Z z, double fv[4][4], double& inc0) {
+  {
     double nw[4], ne[4];
-    if (i > 0) load4(a.Q + 4 * (size_t)(c - 1), nw);
-    else if (a.wall & 1) fv_ghost(ph, q, bg[3 * kBgC], bg[3 * kBgC + 1], bg[3 * kBgC + 2], nw);
-    else load4(a.Q + 4 * (size_t)(c + a.nx - 1), nw);
-    if (i < a.nx - 1) load4(a.Q + 4 * (size_t)(c + 1), ne);
-    else if (a.wall & 2) fv_ghost(ph, q, bg[3 * kBgC], bg[3 * kBgC + 1], bg[3 * kBgC + 2], ne);
-    else load4(a.Q + 4 * (size_t)(c - a.nx + 1), ne);
+    x(nw, ne);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const double sx = van_albada(q[v] - nw[v], ne[v] - q[v]);
@@ -140,14 +135,9 @@ __device__ inline void fv_predict_cell(const Phys& ph, const FvArgs& a, int i, i
       fv[1][v] = q[v] + 0.5 * sx;
     }
   }
-  {  // z: south and north neighbours
+  {
     double ns[4], nn[4];
-    if (j > 0) load4(a.Q + 4 * (size_t)(c - a.nx), ns);
-    else if (a.wall & 4) fv_ghost(ph, q, bg[3 * kBgGS], bg[3 * kBgGS + 1], bg[3 * kBgGS + 2], ns);
-    else load4(a.Q + 4 * ((size_t)(a.nz - 1) * a.nx + i), ns);
-    if (j < a.nz - 1) load4(a.Q + 4 * (size_t)(c + a.nx), nn);
-    else if (a.wall & 8) fv_ghost(ph, q, bg[3 * kBgGN], bg[3 * kBgGN + 1], bg[3 * kBgGN + 2], nn);
-    else load4(a.Q + 4 * (size_t)i, nn);
+    z(ns, nn);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const double sz = van_albada(q[v] - ns[v], nn[v] - q[v]);
@@ -183,6 +173,33 @@ __device__ inline void fv_predict_cell(const Phys& ph, const FvArgs& a, int i, i
   }
 }
 
+// The same for cell (i, j) inside the domain, neighbours from memory (wall
+// ghost or periodic image at the domain edge).
+__device__ inline void fv_predict_cell(const Phys& ph, const FvArgs& a, int i, int j, double dt, double fv[4][4],
+                                       double& inc0) {
+  const int c = j * a.nx + i;
+  const double* bg = a.bg + 15 * j;
+  double q[4];
+  load4(a.Q + 4 * (size_t)c, q);
+  auto x = [&](double nw[4], double ne[4]) {
+    if (i > 0) load4(a.Q + 4 * (size_t)(c - 1), nw);
+    else if (a.wall & 1) fv_ghost(ph, q, bg[3 * kBgC], bg[3 * kBgC + 1], bg[3 * kBgC + 2], nw);
+    else load4(a.Q + 4 * (size_t)(c + a.nx - 1), nw);
+    if (i < a.nx - 1) load4(a.Q + 4 * (size_t)(c + 1), ne);
+    else if (a.wall & 2) fv_ghost(ph, q, bg[3 * kBgC], bg[3 * kBgC + 1], bg[3 * kBgC + 2], ne);
+    else load4(a.Q + 4 * (size_t)(c - a.nx + 1), ne);
+  };
+  auto z = [&](double ns[4], double nn[4]) {
+    if (j > 0) load4(a.Q + 4 * (size_t)(c - a.nx), ns);
+    else if (a.wall & 4) fv_ghost(ph, q, bg[3 * kBgGS], bg[3 * kBgGS + 1], bg[3 * kBgGS + 2], ns);
+    else load4(a.Q + 4 * ((size_t)(a.nz - 1) * a.nx + i), ns);
+    if (j < a.nz - 1) load4(a.Q + 4 * (size_t)(c + a.nx), nn);
+    else if (a.wall & 8) fv_ghost(ph, q, bg[3 * kBgGN], bg[3 * kBgGN + 1], bg[3 * kBgGN + 2], nn);
+    else load4(a.Q + 4 * (size_t)i, nn);
+  };
+  fv_predict_from(ph, a, bg, dt, q, x, z, fv, inc0);
+}
+
 // Steps 3-4 for cell (i, j): Rusanov flux of its four faces from its own
 // evolved face value and the facing value of the neighbour (or the wall
 // ghost where the face is a wall), and the update.  fetch(f, own, nb) loads
@@ -208,7 +225,7 @@ __device__ inline void fv_update_cell(const Phys& ph, const FvArgs& a, int i, in
       fv_ghost(ph, own, zf, rbf, pbf, Qn);
       Fn[0] = -Fo[0]; Fn[1] = Fo[1]; Fn[2] = Fo[2]; Fn[3] = -Fo[3];
       const double pg = fv_pressure(ph, Qn, zf), irg = recip(Qn[0]);
-      sn = fabs(Qn[1 + d] * irg) + sqrt(ph.gamma * pg * irg);
+      sn = fabs(Qn[1 + d] * irg) + root(ph.gamma * pg * irg);
     } else {
       sn = fv_flux(ph, Qn, zf, pbf, d, Fn);
     }
@@ -236,7 +253,7 @@ __device__ inline void fv_update_cell(const Phys& ph, const FvArgs& a, int i, in
 // largest signal speed max(|u|,|w|) + c of a cell value at height z
 __device__ inline double fv_lambda(const Phys& ph, const double q[4], double z) {
   const double ir = recip(q[0]);
-  const double cs = sqrt(ph.gamma * fv_pressure(ph, q, z) * ir);
+  const double cs = root(ph.gamma * fv_pressure(ph, q, z) * ir);
   return fmax(fabs(q[1]), fabs(q[2])) * ir + cs;
 }
 
@@ -297,40 +314,26 @@ __global__ __launch_bounds__(kFvThreads) void k_fv_correct(Phys ph, FvArgs a) {
 }
 
 // Rusanov flux of one face along d (0: x, 1: z) at height zf from the
-// evolved values lo and hi on its low (west or south) and high side; d may
-// differ between lanes (selects, no branches).  out = 1: the low side is a
-// wall, its value is the wall ghost of hi; out = 2: the high side is a wall.
-// The same arithmetic as the face loop of fv_update_cell.
-__device__ inline double fv_flux_sel(const Phys& ph, const double q[4], double z, double pb, int d, double F[4]) {
-  const double ir = recip(q[0]);
-  const double u = q[1] * ir, w = q[2] * ir;
-  const double p = ph.gm1 * (q[3] - 0.5 * (q[1] * u + q[2] * w) - q[0] * (ph.geff * z));
-  const double pm = p - pb;
-  const double un = d ? w : u;
-  F[0] = d ? q[2] : q[1];
-  F[1] = q[1] * un + (d == 0 ? pm : 0.0);
-  F[2] = q[2] * un + (d == 1 ? pm : 0.0);
-  F[3] = un * (q[3] + p);
-  return fabs(un) + sqrt(ph.gamma * p * ir);
-}
-
+// evolved values lo and hi on its low (west or south) and high side.  out = 1:
+// the low side is a wall, its value is the wall ghost of hi; out = 2: the high
+// side is a wall.  The same arithmetic as the face loop of fv_update_cell.
 __device__ inline void fv_face(const Phys& ph, int d, double zf, double rbf, double pbf, int out, const double lo[4],
                                const double hi[4], double G[4]) {
   if (out == 0) {
     double Fl[4], Fh[4];
-    const double sl = fv_flux_sel(ph, lo, zf, pbf, d, Fl);
-    const double sh = fv_flux_sel(ph, hi, zf, pbf, d, Fh);
+    const double sl = fv_flux(ph, lo, zf, pbf, d, Fl);
+    const double sh = fv_flux(ph, hi, zf, pbf, d, Fh);
     rusanov_fv(fmax(sl, sh), lo, Fl, hi, Fh, G);
   } else {
     const double* in = out == 1 ? hi : lo;
     double qi[4], Fo[4], g[4], Fg[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) qi[v] = in[v];
-    const double so = fv_flux_sel(ph, qi, zf, pbf, d, Fo);
+    const double so = fv_flux(ph, qi, zf, pbf, d, Fo);
     fv_ghost(ph, qi, zf, rbf, pbf, g);
     Fg[0] = -Fo[0]; Fg[1] = Fo[1]; Fg[2] = Fo[2]; Fg[3] = -Fo[3];
     const double pg = fv_pressure(ph, g, zf), irg = recip(g[0]);
-    const double sg = fabs((d ? g[2] : g[1]) * irg) + sqrt(ph.gamma * pg * irg);
+    const double sg = fabs((d ? g[2] : g[1]) * irg) + root(ph.gamma * pg * irg);
     const double sp = fmax(so, sg);
     if (out == 1) rusanov_fv(sp, g, Fg, qi, Fo, G);
     else rusanov_fv(sp, qi, Fo, g, Fg, G);
@@ -338,111 +341,125 @@ __device__ inline void fv_face(const Phys& ph, int d, double zf, double rbf, dou
 }
 
 // One step fused into one kernel on tiles of kTX x kTZ cells: every thread
-// predicts its cell, the first threads also the ring of cells around the
-// tile (each only for the face value the tile needs); the evolved face
-// values meet in LDS; the update goes to Qn (other tiles still read Q), and
-// the workgroup's time-step bound of the new values goes to dtb[tile].
+// predicts its cell, a fifth wavefront the ring of cells around the tile (only
+// the face value the tile needs); east and north face values meet in LDS; the
+// update goes to Qn where other tiles still read Q, and the workgroup's
+// time-step bound of the new values goes to dtb[tile].
+//
+// Bound by instruction issue: per wavefront some 640 vector instructions, 470
+// of them FP64, for a state that moves in 6 us of the copy rate at 630 x 630.
+// All neighbours are loaded at once (one direction after the other cost two
+// round trips), the limiter selects instead of branching, each thread works
+// on its own west and south face (a list of 544 face jobs spent as many
+// instructions on indices as on a third of its fluxes).  A step at 630 x 630
+// 27.3 us before, 24.0 now, 900 x 900 46.7 and 39, 1600 x 1600 123 and 101,
+// 100 x 100 9.9 and 9.1.  Marching wavefronts of 60 columns and four rows with
+// every neighbour in registers take 24.7, 40 and 88 us, 15.7 at 100 x 100: they
+// recompute half of the rows' predictions.
 constexpr int kTX = 16, kTZ = 16, kFT = kTX * kTZ;   // tile (one thread per tile cell)
 constexpr int kRing = 2 * (kTX + kTZ), kFTR = kFT + kRing;   // workgroup: tile cells, then the ring
 static_assert(kFT % kWave == 0 && kRing % kWave == 0, "tile and ring fill whole wavefronts");
 
 __global__ __launch_bounds__(kFTR) void k_fv_fused(Phys ph, FvArgs a, double* Qn) {
-  // evolved face values by face type, variable, row, column; each array is
-  // padded by one in the direction of the neighbour that reads it:
-  // west values of columns 0..kTX (kTX: east ring), east values of columns
-  // -1..kTX-1 (stored at column + 1), south values of rows 0..kTZ (kTZ:
-  // north ring), north values of rows -1..kTZ-1 (stored at row + 1)
-  __shared__ double sWv[4][kTZ][kTX + 1], sEv[4][kTZ][kTX + 1];
-  __shared__ double sSv[4][kTZ + 1][kTX], sNv[4][kTZ + 1][kTX];
-  const int t = threadIdx.x, tx = t % kTX, tz = t / kTX;
+  // east and north face values of every cell by variable, row, column (the
+  // west and south ones stay with their thread), with those of the ring's left
+  // column and bottom row in front: east at column + 1, north at row + 1
+  __shared__ double sEv[4][kTZ][kTX + 1], sNv[4][kTZ + 1][kTX];
+  const int t = threadIdx.x;
+  const bool tile = t < kFT;   // whole wavefronts: tile cells, then the ring
   const int x0 = blockIdx.x * kTX, z0 = blockIdx.y * kTZ;
   const int ew = min(kTX, a.nx - x0), eh = min(kTZ, a.nz - z0);   // extent of the tile inside the domain
   const double dt = a.clock[1];
-  const bool inside = t < kFT && tx < ew && tz < eh;
-  // ring (threads kFT..kFTR-1, wavefronts of their own): left and right
-  // columns (the face towards the tile), bottom and top rows
-  if (t >= kFT) {
-    const int q = t - kFT;
-    int rx, rz, f;
-    if (q < kTZ) { rx = -1; rz = q; f = 1; }
-    else if (q < 2 * kTZ) { rx = ew; rz = q - kTZ; f = 0; }
-    else if (q < 2 * kTZ + kTX) { rx = q - 2 * kTZ; rz = -1; f = 3; }
-    else { rx = q - 2 * kTZ - kTX; rz = eh; f = 2; }
-    const bool used = (f < 2) ? rz < eh : rx < ew;
-    int gi = x0 + rx, gj = z0 + rz;
-    bool ok = used;
-    if (gi < 0 || gi >= a.nx) { ok = ok && !(a.wall & 3); gi = gi < 0 ? gi + a.nx : gi - a.nx; }
-    if (gj < 0 || gj >= a.nz) { ok = ok && !(a.wall & 12); gj = gj < 0 ? gj + a.nz : gj - a.nz; }
-    if (ok) {
-      double rv[4][4], rinc;
-      fv_predict_cell(ph, a, gi, gj, dt, rv, rinc);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        // f is known only at run time: select with constant indices so rv stays in registers
-        if (f == 1) sEv[v][rz][0] = rv[1][v];
-        else if (f == 0) sWv[v][rz][ew] = rv[0][v];
-        else if (f == 3) sNv[v][0][rx] = rv[3][v];
-        else sSv[v][eh][rx] = rv[2][v];
-      }
-    }
+  // the thread's cell: of the tile, or of the ring around it (left and right
+  // columns, bottom and top rows; the face value towards the tile)
+  int tx = t % kTX, tz = t / kTX;
+  const int side = tile ? 0 : (t - kFT) / kTX;   // ring: 0 left, 1 right, 2 bottom, 3 top
+  static_assert(kTX == kTZ, "one ring group per side");
+  const int along = t % kTX;                     // position along the side
+  if (!tile) {
+    tx = side == 0 ? -1 : side == 1 ? ew : along;
+    tz = side == 2 ? -1 : side == 3 ? eh : along;
   }
-  double inc0 = 0.0;
-  if (inside) {
-    double fv[4][4];
-    fv_predict_cell(ph, a, x0 + tx, z0 + tz, dt, fv, inc0);
+  const bool inside = tile && tx < ew && tz < eh;
+  int i = x0 + tx, j = z0 + tz;
+  bool ok = tile ? inside : (side < 2 ? along < eh : along < ew);
+  if (i < 0 || i >= a.nx) { ok = ok && !(a.wall & 3); i = i < 0 ? a.nx - 1 : 0; }
+  if (j < 0 || j >= a.nz) { ok = ok && !(a.wall & 12); j = j < 0 ? a.nz - 1 : 0; }
+  if (!ok) { i = x0; j = z0; }                   // a cell to read
+  const double* bg = a.bg + 15 * j;
+  const double* Qc = a.Q + 4 * ((size_t)j * a.nx + i);
+  double q[4], fv[4][4], inc0;
+  load4(Qc, q);
+  {
+    // all neighbours at once; a wall's is replaced by the ghost
+    double nw[4], ne[4], ns[4], nn[4];
+    load4(Qc + 4 * (i > 0 ? -1 : a.nx - 1), nw);
+    load4(Qc + 4 * (i < a.nx - 1 ? 1 : 1 - a.nx), ne);
+    load4(Qc + 4 * (long long)a.nx * (j > 0 ? -1 : a.nz - 1), ns);
+    load4(Qc + 4 * (long long)a.nx * (j < a.nz - 1 ? 1 : 1 - a.nz), nn);
+    if (x0 == 0 || x0 + kTX + 1 >= a.nx) {
+      if ((a.wall & 1) && i == 0) fv_ghost(ph, q, bg[3 * kBgC], bg[3 * kBgC + 1], bg[3 * kBgC + 2], nw);
+      if ((a.wall & 2) && i == a.nx - 1) fv_ghost(ph, q, bg[3 * kBgC], bg[3 * kBgC + 1], bg[3 * kBgC + 2], ne);
+    }
+    if (z0 == 0 || z0 + kTZ + 1 >= a.nz) {
+      if ((a.wall & 4) && j == 0) fv_ghost(ph, q, bg[3 * kBgGS], bg[3 * kBgGS + 1], bg[3 * kBgGS + 2], ns);
+      if ((a.wall & 8) && j == a.nz - 1) fv_ghost(ph, q, bg[3 * kBgGN], bg[3 * kBgGN + 1], bg[3 * kBgGN + 2], nn);
+    }
+    auto x = [&](double w[4], double e[4]) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) { w[v] = nw[v]; e[v] = ne[v]; }
+    };
+    auto z = [&](double lo[4], double hi[4]) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) { lo[v] = ns[v]; hi[v] = nn[v]; }
+    };
+    fv_predict_from(ph, a, bg, dt, q, x, z, fv, inc0);
+  }
+  if (inside || (!tile && ok)) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      sWv[v][tz][tx] = fv[0][v];
-      sEv[v][tz][tx + 1] = fv[1][v];
-      sSv[v][tz][tx] = fv[2][v];
-      sNv[v][tz + 1][tx] = fv[3][v];
+      if (inside || side == 0) sEv[v][tz][tx + 1] = fv[1][v];
+      if (inside || side == 2) sNv[v][tz + 1][tx] = fv[3][v];
     }
   }
   __syncthreads();
-  // every face of the tile once: z faces (rows 0..eh, the south face of each
-  // row of cells and the tile's top), then x faces (columns 0..ew); a job's
-  // flux replaces the low side's value, which only this job reads
-  constexpr int kZJobs = (kTZ + 1) * kTX, kXJobs = kTZ * (kTX + 1);
-  constexpr int zvs = (kTZ + 1) * kTX, xvs = kTZ * (kTX + 1);   // variable strides of the two array shapes
-  for (int k = t; k < kZJobs + kXJobs; k += kFTR) {
-    const bool zj = k < kZJobs;
-    const int kk = zj ? k : k - kZJobs;
-    const int r = zj ? kk / kTX : kk / (kTX + 1), col = zj ? kk % kTX : kk % (kTX + 1);
-    if (!(zj ? (r <= eh && col < ew) : (r < eh && col <= ew))) continue;
-    const int d = zj ? 1 : 0, vs = zj ? zvs : xvs;
-    double* plo = zj ? &sNv[0][r][col] : &sEv[0][r][col];
-    const double* phi = zj ? &sSv[0][r][col] : &sWv[0][r][col];
-    const int gj = z0 + r;
-    // face height: x faces at the row centre; z faces at the south face of
-    // row gj, the tile's top face at the north face of the row below it
-    const double* bf = !zj ? a.bg + 15 * gj + 3 * kBgC
-                           : (r < eh ? a.bg + 15 * gj + 3 * kBgS : a.bg + 15 * (gj - 1) + 3 * kBgN);
-    int out = 0;
-    if (zj) {
-      if (r == 0 && z0 == 0 && (a.wall & 4)) out = 1;
-      else if (r == eh && z0 + eh == a.nz && (a.wall & 8)) out = 2;
-    } else {
-      if (col == 0 && x0 == 0 && (a.wall & 1)) out = 1;
-      else if (col == ew && x0 + ew == a.nx && (a.wall & 2)) out = 2;
-    }
-    double lo[4], hi[4], G[4];
+  // every face of the tile once: each cell its west and its south face, the
+  // ring's right and top groups the tile's east and north faces; the flux
+  // replaces the low side's value, which only its face reads.  At a wall the
+  // missing side's value is whatever the thread or the LDS holds; the face
+  // does not use it.
+  double Gx[4], Gz[4];
+  if (inside || (!tile && side == 1 && along < eh)) {
+    const double* bf = a.bg + 15 * (z0 + tz) + 3 * kBgC;
+    const int out = (a.wall & 1) && x0 + tx == 0 ? 1 : ((a.wall & 2) && x0 + tx == a.nx ? 2 : 0);
+    double lo[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) { lo[v] = plo[v * vs]; hi[v] = phi[v * vs]; }
-    fv_face(ph, d, bf[0], bf[1], bf[2], out, lo, hi, G);
+    for (int v = 0; v < 4; ++v) lo[v] = sEv[v][tz][tx];
+    fv_face(ph, 0, bf[0], bf[1], bf[2], out, lo, fv[0], Gx);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) plo[v * vs] = G[v];
+    for (int v = 0; v < 4; ++v) sEv[v][tz][tx] = Gx[v];
+  }
+  if (inside || (!tile && side == 3 && along < ew)) {
+    // face height: the south face of the row above, the tile's top the north
+    // face of its last row
+    const double* bf = tz < eh ? a.bg + 15 * (z0 + tz) + 3 * kBgS : a.bg + 15 * (z0 + tz - 1) + 3 * kBgN;
+    const int out = (a.wall & 4) && z0 + tz == 0 ? 1 : ((a.wall & 8) && z0 + tz == a.nz ? 2 : 0);
+    double lo[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) lo[v] = sNv[v][tz][tx];
+    fv_face(ph, 1, bf[0], bf[1], bf[2], out, lo, fv[2], Gz);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sNv[v][tz][tx] = Gz[v];
   }
   __syncthreads();
   double lam = 0.0;
   if (inside) {
-    const int i = x0 + tx, j = z0 + tz;
-    double q[4], out[4];
-    load4(a.Q + 4 * ((size_t)j * a.nx + i), q);
-    const double Sh = -ph.geff * ((q[0] + inc0) - a.bg[15 * j + 3 * kBgC + 1]);
+    double out[4];
+    const double Sh = -ph.geff * ((q[0] + inc0) - bg[3 * kBgC + 1]);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const double dx = sEv[v][tz][tx + 1] - sEv[v][tz][tx];   // G_east - G_west
-      const double dz = sNv[v][tz + 1][tx] - sNv[v][tz][tx];   // G_north - G_south
+      const double dx = sEv[v][tz][tx + 1] - Gx[v];   // G_east - G_west
+      const double dz = sNv[v][tz + 1][tx] - Gz[v];   // G_north - G_south
       out[v] = q[v] - dt * a.ih * (dx + dz);
       if (v == 2) out[v] += dt * Sh;
     }
@@ -453,13 +470,13 @@ __global__ __launch_bounds__(kFTR) void k_fv_fused(Phys ph, FvArgs a, double* Qn
     double2* o = reinterpret_cast<double2*>((edge ? Qn : a.Q) + 4 * ((size_t)j * a.nx + i));
     o[0] = make_double2(out[0], out[1]);
     o[1] = make_double2(out[2], out[3]);
-    lam = fv_lambda(ph, out, a.bg[15 * j]);
+    lam = fv_lambda(ph, out, bg[3 * kBgC]);
   }
   fv_block_bound<kFTR>(ph, a, lam, blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // Q <- Qn on the two outer layers of every tile of the fused step (workgroup
-// b >= 1: tile b - 1, one thread per cell); workgroup 0 instead reduces the
+// b >= 1: tile b - 1, one thread per edge cell); workgroup 0 instead reduces the
 // tiles' time-step bounds and advances the clock (t += dt, steps += 1, then
 // dt <- the minimum unless update is 0), the work of k_clock, beside the copy.
 __global__ __launch_bounds__(kFT) void k_fv_commit(const double* __restrict__ Qn, double* __restrict__ Q,
@@ -494,15 +511,30 @@ __global__ __launch_bounds__(kFT) void k_fv_commit(const double* __restrict__ Qn
   const int tiles_x = (nx + kTX - 1) / kTX, b = blockIdx.x - 1;
   const int x0 = (b % tiles_x) * kTX, z0 = (b / tiles_x) * kTZ;
   const int ew = min(kTX, nx - x0), eh = min(kTZ, nz - z0);
-  const int tx = t % kTX, tz = t / kTX;
-  if (tx >= ew || tz >= eh) return;
-  if (!(tx <= 1 || tx >= ew - 2 || tz <= 1 || tz >= eh - 2)) return;
-  const size_t c = (size_t)(z0 + tz) * nx + x0 + tx;
-  const double2* src = reinterpret_cast<const double2*>(Qn + 4 * c);
-  double2* dst = reinterpret_cast<double2*>(Q + 4 * c);
-  const double2 v0 = src[0], v1 = src[1];
-  dst[0] = v0;
-  dst[1] = v1;
+  // the tile's two lowest and two highest rows, then the outer columns of the others
+  const int rows = min(eh, 4), cols = min(ew, 4), ne = rows * ew + (eh - rows) * cols;
+  static_assert(4 * (kTX + kTZ) <= kFT, "a thread per edge cell");
+  if (t < ne) {
+    const int e = t;
+    int tx, tz;
+    if (e < rows * ew) {
+      tz = e / ew;
+      tx = e - tz * ew;
+      if (tz >= 2) tz = eh - rows + tz;
+    } else {
+      const int k = e - rows * ew;
+      tz = k / cols;
+      tx = k - tz * cols;
+      tz += 2;
+      if (tx >= 2) tx = ew - cols + tx;
+    }
+    const size_t c = (size_t)(z0 + tz) * nx + x0 + tx;
+    const double2* src = reinterpret_cast<const double2*>(Qn + 4 * c);
+    double2* dst = reinterpret_cast<double2*>(Q + 4 * c);
+    const double2 v0 = src[0], v1 = src[1];
+    dst[0] = v0;
+    dst[1] = v1;
+  }
 }
 
 // time-step bound of every workgroup of cells from the current Q
