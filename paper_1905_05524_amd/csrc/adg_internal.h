@@ -126,32 +126,26 @@ struct HostBasis {
 // 2^62 boxes).  Lookups outside the grid of their level find nothing.
 struct LeafIndex {
   static constexpr long long kDenseBoxes = 1LL << 22;
-  int nx, nz, L;
+  struct Level { long long nx, nz, off; };   // boxes along x and z, start of the level's table
+  int L;
   bool dense = false;
-  std::vector<long long> off;   // per level: start of its table
+  std::vector<Level> lev;
   std::vector<int> tab;
   std::unordered_map<long long, int> map;
-  LeafIndex(int nx_, int nz_, int L_, size_t n_leaves) : nx(nx_), nz(nz_), L(L_), off(L_ + 1, 0) {
+  LeafIndex(int nx, int nz, int L_, size_t n_leaves) : L(L_), lev(L_ + 1) {
     long long total = 0, s = 1;
     for (int l = 0; l <= L; ++l, s *= 3) {
-      off[l] = total;
-      total += (long long)nx * s * nz * s;
+      lev[l] = {nx * s, nz * s, total};
+      total += lev[l].nx * lev[l].nz;
     }
     dense = total <= kDenseBoxes;
     if (dense) tab.assign((size_t)total, -1);
     else map.reserve(n_leaves * 2);
   }
   bool in_grid(int l, int i, int j) const {
-    if (l < 0 || l > L || i < 0 || j < 0) return false;
-    long long s = 1;
-    for (int k = 0; k < l; ++k) s *= 3;
-    return i < nx * s && j < nz * s;
+    return l >= 0 && l <= L && i >= 0 && j >= 0 && i < lev[l].nx && j < lev[l].nz;
   }
-  long long slot(int l, int i, int j) const {
-    long long s = 1;
-    for (int k = 0; k < l; ++k) s *= 3;
-    return off[l] + (long long)j * nx * s + i;
-  }
+  long long slot(int l, int i, int j) const { return lev[l].off + (long long)j * lev[l].nx + i; }
   // records leaf c at (l, i, j); false if the box is outside the grid or
   // holds a leaf already
   bool insert(int l, int i, int j, int c) {

@@ -12,16 +12,41 @@
 // Transfer: copy; prolongation to a child by exact interpolation of the
 // parent polynomial; restriction of nine children by L2 projection.
 #include <algorithm>
-#include <map>
-#include <set>
 #include <tuple>
-#include <unordered_map>
 
 #include "adg_internal.h"
 
 namespace adg {
 
 enum RegridOp { kCopy = 0, kProlong = 1, kRestrict = 2 };
+
+// Copies a multiple of 16 bytes from pinned host memory; src and dst 16-byte
+// aligned.  One launch for what three copies would move: a copy of some tens of
+// kilobytes costs 10 us of its own.
+struct StagedCopy {
+  const uint4* src[3];
+  uint4* dst[3];
+  long long n[3];   // 16-byte words
+};
+__global__ __launch_bounds__(256) void k_stage(StagedCopy a) {
+  const long long step = (long long)gridDim.x * blockDim.x, t0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    for (long long t = t0; t < a.n[k]; t += step) a.dst[k][t] = a.src[k][t];
+}
+int launch_stage(const void* const src[3], void* const dst[3], const size_t bytes[3], hipStream_t s) {
+  StagedCopy a;
+  long long most = 0;
+  for (int k = 0; k < 3; ++k) {
+    a.src[k] = static_cast<const uint4*>(src[k]);
+    a.dst[k] = static_cast<uint4*>(dst[k]);
+    a.n[k] = (long long)(bytes[k] / 16);
+    most = std::max(most, a.n[k]);
+  }
+  if (most == 0) return ADG_OK;
+  hipLaunchKernelGGL(k_stage, dim3((unsigned)std::min<long long>((most + 255) / 256, 1024)), dim3(256), 0, s, a);
+  return check_launch("stage");
+}
 
 // ops[c][12] = op, a, b, src[9]
 template <int n>
@@ -187,11 +212,16 @@ int regrid_plan(const std::vector<int>& lev, const std::vector<int>& ci, const s
   // new level: +1 refine, -1 accepted coarsening (coded 2 below)
   std::vector<int> coarsen(C, 0);
   auto nl = [&](int c) { return lev[c] + (eff[c] == 1 ? 1 : 0) - coarsen[c]; };
+  // The highest new level (the closure refines leaves below it only): a leaf or
+  // parent at least one below it can have no neighbour two levels finer, so
+  // meshes of one level skip both searches.
+  int top = 0;
+  for (int c = 0; c < C; ++c) top = std::max(top, lev[c] + (eff[c] == 1 ? 1 : 0));
   // refinement closure
   for (bool changed = true; changed;) {
     changed = false;
     for (int c = 0; c < C; ++c) {
-      if (eff[c] == 1) continue;
+      if (eff[c] == 1 || lev[c] + 1 >= top) continue;
       for (int f = 0; f < 4; ++f)
         if (across_face(M, nl, lev[c], ci[c], cj[c], f, L) > lev[c] + 1) {
           eff[c] = 1;
@@ -202,12 +232,17 @@ int regrid_plan(const std::vector<int>& lev, const std::vector<int>& ci, const s
   }
   // coarsening candidates: families whose nine children are leaves flagged coarsen
   // (parents in (level, i, j) order)
-  std::map<Box, int> cnt;
-  for (int c = 0; c < C; ++c)
-    if (lev[c] > 0 && eff[c] == -1) cnt[Box(lev[c] - 1, ci[c] / 3, cj[c] / 3)] += 1;
   std::vector<Box> fams;
-  for (const auto& kv : cnt)
-    if (kv.second == 9) fams.push_back(kv.first);
+  for (int c = 0; c < C; ++c) {
+    if (lev[c] == 0 || eff[c] != -1 || ci[c] % 3 || cj[c] % 3) continue;   // the family's first child
+    bool all = true;
+    for (int k = 1; k < 9 && all; ++k) {
+      const int kid = M.find(lev[c], ci[c] + k % 3, cj[c] + k / 3);
+      all = kid >= 0 && eff[kid] == -1;
+    }
+    if (all) fams.emplace_back(lev[c] - 1, ci[c] / 3, cj[c] / 3);
+  }
+  std::sort(fams.begin(), fams.end());
   auto family = [&](const Box& pk, int* out) {
     // the nine children (row by row) of parent box pk, as leaf indices
     const auto [pl, pi, pj] = pk;
@@ -225,7 +260,7 @@ int regrid_plan(const std::vector<int>& lev, const std::vector<int>& ci, const s
     for (const Box& pk : fams) {
       int kids[9];
       auto [pl, pi, pj] = family(pk, kids);
-      if (!coarsen[kids[0]]) continue;
+      if (!coarsen[kids[0]] || pl + 1 >= top) continue;
       bool ok = true;
       for (int f = 0; f < 4 && ok; ++f)
         if (across_face(M, nl, pl, pi, pj, f, L) > pl + 1) ok = false;
@@ -235,8 +270,11 @@ int regrid_plan(const std::vector<int>& lev, const std::vector<int>& ci, const s
       }
     }
   }
-  std::set<Box> emitted;
+  size_t total = 0;   // new leaves, at most
+  for (int c = 0; c < C; ++c) total += eff[c] == 1 ? 9 : 1;
+  std::vector<char> emitted(C, 0);   // children whose parent is in the new list
   nlev.clear(); nci.clear(); ncj.clear(); ops.clear();
+  nlev.reserve(total); nci.reserve(total); ncj.reserve(total); ops.reserve(12 * total);
   auto emit = [&](int l, int i, int j, int op, int a, int b, const int* src, int ns) {
     nlev.push_back(l); nci.push_back(i); ncj.push_back(j);
     int rec[12] = {op, a, b, -1, -1, -1, -1, -1, -1, -1, -1, -1};
@@ -246,10 +284,10 @@ int regrid_plan(const std::vector<int>& lev, const std::vector<int>& ci, const s
   for (int c = 0; c < C; ++c) {
     const int l = lev[c], i = ci[c], j = cj[c];
     if (coarsen[c]) {
-      const Box pk(l - 1, i / 3, j / 3);
-      if (!emitted.insert(pk).second) continue;
+      if (emitted[c]) continue;
       int src[9];
-      family(pk, src);
+      family(Box(l - 1, i / 3, j / 3), src);
+      for (int k = 0; k < 9; ++k) emitted[src[k]] = 1;
       emit(l - 1, i / 3, j / 3, kRestrict, 0, 0, src, 9);
       continue;
     }

@@ -23,6 +23,7 @@ int launch_health(const Group& g, int* flag, hipStream_t s);
 int launch_regrid(int n, int C, const int* ops, const double* Qold, double* Qnew, const double* gtab,
                   hipStream_t s);
 int launch_background(const Group& g, int C, hipStream_t s);   // fills d_bg of C cells
+int launch_stage(const void* const src[3], void* const dst[3], const size_t bytes[3], hipStream_t s);
 int launch_step_adjoint(const Group& g, const double* Qn, const double* lam_in, double* lam_out, double* store,
                         const double* fd, bool recompute, hipStream_t s);
 int launch_ic_theta(const Group& g, const double* thp, hipStream_t s);
@@ -715,7 +716,7 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
   }
   // the uploads go through a grow-only pinned staging buffer: operations,
   // geometry, neighbours (an apply ends with a stream synchronisation, so no
-  // earlier copy from it is in flight)
+  // earlier read of it is in flight)
   const size_t b_ops = sizeof(int) * nops, b_geom = sizeof(double) * 4 * (size_t)H.C,
                b_nbr = sizeof(int) * 16 * (size_t)H.C;
   const size_t o_geom = align256(b_ops), o_nbr = o_geom + align256(b_geom), need = o_nbr + align256(b_nbr);
@@ -733,14 +734,8 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
     m->stage_cap = need + need / 4;
   }
   char* st = static_cast<char*>(m->h_stage);
-  if (nops) {
-    std::memcpy(st, m->plan_ops.data(), b_ops);
-    if (hipMemcpyAsync(m->d_ops, st, b_ops, hipMemcpyHostToDevice, s) != hipSuccess)
-      return fail(ADG_EHIP, "upload ops");
-  }
-  rc = launch_regrid(m->g.n, Cn, m->d_ops, m->Q, Q_new, m->g.d_gtab, s);
-  if (rc) return rc;
-  std::memcpy(st + o_geom, H.geom.data(), b_geom);   // staged while the transfer kernel runs
+  if (nops) std::memcpy(st, m->plan_ops.data(), b_ops);
+  std::memcpy(st + o_geom, H.geom.data(), b_geom);
   std::memcpy(st + o_nbr, H.nbr.data(), b_nbr);
   // every kernel that reads the old tables (on any stream) is done before
   // they are overwritten or freed
@@ -761,18 +756,23 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
     m->cells_cap = cap;
     g.d_bg = g.d_geom + 4 * (size_t)cap;
   }
-  if (H.C && (hipMemcpyAsync(g.d_geom, st + o_geom, b_geom, hipMemcpyHostToDevice, s) != hipSuccess ||
-              hipMemcpyAsync(g.d_nbr, st + o_nbr, b_nbr, hipMemcpyHostToDevice, s) != hipSuccess ||
-              launch_background(g, H.C, s) != ADG_OK || hipStreamSynchronize(s) != hipSuccess)) {
+  // one kernel reads the staging buffer (records of 48, 32 and 64 bytes)
+  const void* src[3] = {st, st + o_geom, st + o_nbr};
+  void* dst[3] = {m->d_ops, g.d_geom, g.d_nbr};
+  const size_t bytes[3] = {b_ops, b_geom, b_nbr};
+  rc = launch_stage(src, dst, bytes, s);
+  if (!rc) rc = launch_background(g, H.C, s);
+  if (!rc) rc = launch_regrid(m->g.n, Cn, m->d_ops, m->Q, Q_new, m->g.d_gtab, s);
+  if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = fail(ADG_EHIP, "regrid failed");
+  if (rc) {
     g.C = 0;
-    return fail(ADG_EHIP, "upload failed");
+    return rc;
   }
   g.C = H.C;
   g.nc = 0;
   for (size_t k = 0; k < 4 * (size_t)H.C; ++k)
     if (H.nbr[4 * k] == kFineSide || H.nbr[4 * k] == kCoarseSide) { g.nc = 1; break; }
-  m->hm = std::move(H);
-  m->plan_mesh = HostMesh();
+  std::swap(m->hm, m->plan_mesh);   // the old one's arrays serve the next plan
   m->plan_ready = false;
   layout_workspace(m);
   return adg_set_state(m, Q_new, workspace_new, clock);
