@@ -508,22 +508,26 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   }
 }
 
-// Up to n = 7 the kernel is held to 168 VGPRs, three wavefronts per SIMD (at
-// n = 7 that spills 32 of them outside the inner phases and still measured
-// 1.21 against 1.28 ms at 243 x 243 cells with two per SIMD); at n = 8 two.
-template <int n, int CB, int WV, bool PW>
-__global__ __launch_bounds__(kWave * WV, (n <= 7 ? 3 : 2)) void k_predict_rows(Phys ph, StepArgs a, int ms) {
+// Up to n = 7 the kernel is held to 168 VGPRs, three wavefronts per SIMD; at
+// n = 8 two.  At n = 7 that spills some 20 of them outside the inner phases:
+// meshes of up to 2048 cells, which have no third wavefront for a SIMD, take
+// the variant that holds 183.  Two, three per SIMD at n = 7: 30 x 30 cells 31.6
+// and 34.7 us, 45 x 45 51.1 and 52.5, 48 x 48 72.8 and 66.2, 243 x 243 1.28 and
+// 1.17 ms.
+template <int n, int CB, int WV, bool PW, int OCC>
+__global__ __launch_bounds__(kWave * WV, OCC) void k_predict_rows(Phys ph, StepArgs a, int ms) {
   extern __shared__ double lds[];
   predict_rows<n, CB, WV, PW>(ph, a, lds, ms, blockIdx.x * CB);
 }
 
-template <int n, int CB, int WV, bool PW = false>
+template <int n, int CB, int WV, bool PW = false, int OCC = (n <= 7 ? 3 : 2)>
 static int rows_t(const Group& g, double* store, hipStream_t s) {
   StepArgs a = make_args(g);
   a.iter_store = store;
   const int ms = g.ph.mms == 1 ? n * n * n : 0;
   const size_t lds = sizeof(double) * (size_t)CB * (RowsLay<n, CB, WV>::cell + ms);
-  hipLaunchKernelGGL((k_predict_rows<n, CB, WV, PW>), dim3((g.C + CB - 1) / CB), dim3(kWave * WV), lds, s, g.ph, a, ms);
+  hipLaunchKernelGGL((k_predict_rows<n, CB, WV, PW, OCC>), dim3((g.C + CB - 1) / CB), dim3(kWave * WV), lds, s, g.ph, a,
+                     ms);
   return check_launch("predictor (rows)");
 }
 
@@ -885,6 +889,7 @@ static int predict_n(const Group& g, double* store, hipStream_t s) {
   if (k == Kernel::kSplit) return split_n<n>(g, store, s);
   // the paper's manufactured solution runs one cell per wavefront
   if (g.ph.mms == 2) return rows_t<n, 1, 1, true>(g, store, s);
+  if constexpr (n == 7) { if (g.C <= 2048) return rows_t<n, 1, 1, false, 2>(g, store, s); }
   if (k == Kernel::kCell) return rows_t<n, 1, 1>(g, store, s);
   if constexpr (n == 5) { if (k == Kernel::kPacked) return rows_t<n, 5, 2>(g, store, s); }
   if constexpr (n == 6) { if (k == Kernel::kPacked) return rows_t<n, 3, 2>(g, store, s); }

@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 
 # cells per workgroup of the packings: 16, 7, 4, 2 or 5, 3, 1, 1
 EDGES = {1: (1, 15, 17), 2: (1, 6, 8), 3: (3, 5), 4: (1, 4, 6, 11), 5: (2, 4, 7), 6: (1, 2), 7: (1, 3)}
-RULE = [(1, 384), (1, 385), (4, 385), (4, 4097), (5, 768), (5, 769), (5, 2048), (5, 2049), (7, 769)]
+RULE = [(1, 384), (1, 385), (1, 1024), (1, 1025), (3, 512), (3, 513), (4, 385), (4, 512), (4, 513), (4, 4097),
+        (6, 769), (6, 2048), (6, 2049), (5, 768), (5, 769), (5, 2048), (5, 2049), (7, 769)]
 
 
 def strip(N, C, flow):
