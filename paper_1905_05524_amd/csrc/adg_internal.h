@@ -265,6 +265,17 @@ __device__ inline double pressure(const Phys& ph, double rho, double mx, double 
   return ph.gm1 * (E - 0.5 * (mx * mx + mz * mz) / rho - geo);
 }
 
+// Reciprocal of a positive normal double: the hardware estimate refined by
+// two Newton steps r <- r + r (1 - x r) (quadratic convergence; the result
+// is within an ulp or so of 1/x, not necessarily correctly rounded).
+__device__ inline double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  double e = fma(-x, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-x, r, 1.0);
+  return fma(r, e, r);
+}
+
 // Phases of the manufactured advected density wave, kx (x - u t) and
 // kz (z - w t): sine and cosine along x, then along z.
 struct WavePhase {
@@ -287,7 +298,7 @@ __device__ inline double mms_source(const Phys& ph, const WavePhase& a, const Wa
   double rx = ph.mms_amp * ph.mms_kx * cx * sz;
   double rz = ph.mms_amp * ph.mms_kz * sx * cz;
   double lap = -(ph.mms_kx * ph.mms_kx + ph.mms_kz * ph.mms_kz) * ph.mms_amp * sx * sz;
-  double ir = 1.0 / rho;
+  double ir = recip(rho);
   double lapT = ph.mms_p * ph.iR * (-lap * ir * ir + 2.0 * (rx * rx + rz * rz) * ir * ir * ir);
   return -ph.kappa * lapT;
 }
@@ -331,17 +342,6 @@ __device__ inline void paper_wave_source(const Phys& ph, double x, double z, dou
   S[1] = k * (2.0 * mu1 + p1) - om * m1 - (8.0 / 3.0) * ph.mu * kk * u2;
   S[2] = S[1];
   S[3] = 2.0 * k * H1 - om * E1 - (16.0 / 3.0) * ph.mu * kk * (u1 * u1 + u * u2) - 2.0 * ph.kappa * kk * T2;
-}
-
-// Reciprocal of a positive normal double: the hardware estimate refined by
-// two Newton steps r <- r + r (1 - x r) (quadratic convergence; the result
-// is within an ulp or so of 1/x, not necessarily correctly rounded).
-__device__ inline double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
 }
 
 // Square root: the hardware estimate of 1/sqrt(x), one coupled Newton step for

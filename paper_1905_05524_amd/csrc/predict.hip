@@ -542,8 +542,9 @@ constexpr int kSplit = 4;
 template <int n>
 struct SplitLay : RowsLay<n, 1, 1> {
   using L = RowsLay<n, 1, 1>;
-  static constexpr int buf = 4 * L::VS > 4 * L::nn ? 4 * L::VS : 4 * L::nn;
+  static constexpr int buf = 4 * L::VS;
   static constexpr int cell = 3 * buf;
+  static_assert(buf >= 6 * L::nn && buf >= 4 * L::nn + 4 * n, "the density wave's phases fit behind the slices");
 };
 
 template <int n, bool PW>
@@ -600,6 +601,18 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
   // first sweep: one residual serves all levels (slices [v][j][i])
   if (act) XR[w * nn + r] = qn;
   __syncthreads();
+  // The density wave's source runs beside the first sweep, on the wavefronts
+  // that have no part in it: the phases of the nodes along x and z and those of
+  // the levels, through the free end of the buffers, then the levels' sources.
+  const bool wave = !PW && ph.mms;
+  double *phx = XR + 4 * nn, *phz = GX + 4 * nn, *phl = GZ + 4 * nn;   // [nn][2], [nn][2], [2][n][2]
+  auto sources = [&](int b0, int b1) {
+    const double xs = phx[2 * r], xc = phx[2 * r + 1], zs = phz[2 * r], zco = phz[2 * r + 1];
+#pragma unroll
+    for (int b = 0; b < n; ++b)
+      if (b >= b0 && b < b1)
+        Sm[b] = mms_source(ph, {xs, xc, zs, zco}, {phl[2 * b], phl[2 * b + 1], phl[2 * (n + b)], phl[2 * (n + b) + 1]});
+  };
   {
     const EO<n> D(eo_table(gt));
     if (t < 8 * n) {
@@ -612,6 +625,20 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       double* d = (dir ? GZ : GX) + base;
 #pragma unroll
       for (int m = 0; m < n; ++m) d[m * st] = out[m];
+    } else if (wave && w > 0) {
+      const int lev = lane & 31;   // w = 3: lanes 0.. the levels along x, 32.. along z
+      const double xi = gt[GTab::XI * n + min(lev, n - 1)];
+      double ang;
+      if (w == 1) ang = ph.mms_kx * ((x0 + h * gt[GTab::XI * n + lo]) - ph.mms_u * t0);
+      else if (w == 2) ang = ph.mms_kz * (zc - ph.mms_w * t0);
+      else ang = lane < 32 ? ph.mms_kx * (ph.mms_u * (xi * dt)) : ph.mms_kz * (ph.mms_w * (xi * dt));
+      double sn, cs;
+      sincos(ang, &sn, &cs);
+      if (w < 3 ? act : lev < n) {
+        double* o = w == 1 ? phx + 2 * r : w == 2 ? phz + 2 * r : phl + 2 * ((lane >> 5) * n + lev);
+        o[0] = sn;
+        o[1] = cs;
+      }
     }
     __syncthreads();
     if (w == 0 && act) {
@@ -625,17 +652,8 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       GZ[r] = fc.gh * (q[0] - rbc);
 #pragma unroll
       for (int v = 1; v < 4; ++v) { GX[v * nn + r] = Fx[v - 1]; GZ[v * nn + r] = Fz[v - 1]; }
-    } else if (!PW && ph.mms && w == 3) {
-      // the density wave's source, while another wavefront has the fluxes
-      const double xi = gt[GTab::XI * n + lo], tb = xi * dt;
-      const WavePhase lev = wave_phase(ph, ph.mms_u * tb, ph.mms_w * tb);   // lane b: level b
-      const WavePhase p = wave_phase(ph, (x0 + h * xi) - ph.mms_u * t0, zc - ph.mms_w * t0);
-#pragma unroll
-      for (int b = 0; b < n; ++b) {
-        const WavePhase l = {__shfl(lev.sx, b, kWave), __shfl(lev.cx, b, kWave), __shfl(lev.sz, b, kWave),
-                             __shfl(lev.cz, b, kWave)};
-        Sm[b] = mms_source(ph, p, l);
-      }
+    } else if (wave && w == 3) {
+      sources(0, (n + 1) / 2);
     }
     __syncthreads();
     if (t < 6 * n) {
@@ -648,6 +666,8 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       D.apply(in, out);
 #pragma unroll
       for (int m = 0; m < n; ++m) d[m * st] = out[m];
+    } else if (wave && w == 3) {
+      sources((n + 1) / 2, n);
     }
   }
   __syncthreads();
