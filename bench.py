@@ -29,7 +29,8 @@ FP64_PEAK_TFLOPS = 78.6     # 256 CU * 4 SIMD * 16 lanes * 2 flop * 2.4 GHz
 HBM_PEAK_GBS = 8000.0
 TV_EVERY = 10
 SAMPLE_EVERY = 10   # headline steps between the launches timed with events
-KERNEL_SOURCES = ("paper_1905_05524_amd/csrc/step.hip", "paper_1905_05524_amd/csrc/adg_internal.h",
+KERNEL_SOURCES = ("paper_1905_05524_amd/csrc/predict.hip", "paper_1905_05524_amd/csrc/step.hip",
+                  "paper_1905_05524_amd/csrc/step_internal.h", "paper_1905_05524_amd/csrc/adg_internal.h",
                   "paper_1905_05524_amd/build.py")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_bubble81_N6.json")
 
@@ -744,7 +745,7 @@ def main():
                      "frac": achieved / FP64_PEAK_TFLOPS,
                      "traffic": measured_traffic(f"k_predictor<{N + 1}"),
                      "traffic_unit": "bytes per launch (FETCH_SIZE x2 + WRITE_SIZE x1, copy-calibrated)",
-                     "kernel": f"k_predictor<{N + 1}>", "kernel_ms": pred_ms, "kernel_launches_timed": len(ev),
+                     "kernel": f"k_predict_rows<{N + 1}>", "kernel_ms": pred_ms, "kernel_launches_timed": len(ev),
                      "flops_per_launch": pflops},
         "extra": {"corrector_ms": corr_ms,
                   "corrector_GBps": cbytes / (corr_ms / 1e3) / 1e9,

@@ -20,12 +20,6 @@
 
 namespace adg {
 
-__device__ inline void wave_sync_a() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // --------------------------------------------------------- pointwise VJP
 // Reverse of the predictor's fluxes at one node.  q: state; gx, gz: gradients
 // in reference coordinates; aFx, aFz: adjoints of the fluxes.  Returns the

@@ -44,7 +44,8 @@ __device__ inline void wall_ghost(const Phys& ph, int d, double zf, const double
 }
 
 // |v| + c and lambda_v for the larger of the momenta ma, mb (one twice: the
-// normal speed of a face)
+// normal speed of a face): one reciprocal and one square root, where the two
+// directions of a node apart took four divisions and two roots
 __device__ inline void eig(const Phys& ph, const double q[4], double ma, double mb, double z, double& lam, double& lv) {
   const double ir = recip(q[0]);
   const double ke = fma(q[1], q[1], q[2] * q[2]) * ir;                        // rho |v|^2
