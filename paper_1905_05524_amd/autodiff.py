@@ -29,19 +29,22 @@ class ThetaRollout(torch.autograd.Function):
             # the adjoint differentiates steps of one frozen length
             raise ValueError("theta_rollout needs a mesh created with fixed_dt=True")
         th = theta_prime.detach().contiguous()
-        m.ic_theta(th)
         # checkpoints Q^0 .. Q^K: the loss adjoint reads the rollout's own end
         # state, whatever the mesh is used for between forward and backward
         ck = torch.empty((steps + 1,) + tuple(m.Q.shape), dtype=torch.float64, device=m.device)
-        m.clock[0], m.clock[1] = float(t0), float(dt)
+        # fills: assigning a Python number copies it from pageable memory, and
+        # that copy waits until the device has done all earlier work
+        m.clock[0:1].fill_(float(t0))
+        m.clock[1:2].fill_(float(dt))
         stores = fds = None
         if keep:
             sb, fb = m.keep_bytes()
             stores = torch.empty((steps, sb // 8), dtype=torch.float64, device=m.device)
             fds = torch.empty((steps, fb // 8), dtype=torch.float64, device=m.device)
         # each step reads checkpoint k (bound) and writes checkpoint k + 1
-        ck[0].copy_(m.Q)
         try:
+            m.bind_state(ck[0])
+            m.ic_theta(th)
             for k in range(steps):
                 m.bind_state(ck[k])
                 if keep:
