@@ -162,8 +162,9 @@ int adg_step(adg_mesh* m, void* stream);
  * 6), one per GPU, held until the process ends.  Allocates nothing and does
  * not use the buffers bound by adg_set_state.  Must be called with the
  * handle's device current.  EINVAL if Q or clock is null or misaligned, if
- * the mesh's workspace (adg_workspace_bytes) exceeds the buffer, or if the
- * current device is not the handle's; EHIP if the buffer's device address
+ * the mesh's workspace (adg_workspace_bytes, not counting the room above
+ * 24,576 cells for the stages of the time-step minimum) exceeds the buffer, or
+ * if the current device is not the handle's; EHIP if the buffer's device address
  * could not be looked up when the handle was created.  Every call on one
  * GPU shares the buffer, which keeps the last call's contents (nothing in
  * it must start at zero: each step writes every entry it reads): calls that

@@ -68,7 +68,8 @@ int adg3_workspace_bytes(const adg3_mesh* m, size_t* bytes);
  * Q* [C][5][n][n][n], then the face data [C][6][2][5][n][n] (per face: the
  * time-averaged state and normal flux extrapolated to the face, nodes
  * ordered by the two tangential directions in (z, y, x) order), then the
- * per-cell time-step candidates [C], then a health flag. */
+ * per-cell time-step candidates [C], then a health flag, then (above 24,576
+ * cells) room for the stages of the candidates' minimum. */
 int adg3_set_state(adg3_mesh* m, double* Q, void* workspace, double* clock);
 
 /* Initial state by nodal interpolation.  kind 0: the hydrostatic background

@@ -83,7 +83,8 @@ int adg_fv_workspace_bytes(const adg_fv* m, size_t* bytes);
  * double[4].  Workspace layout (offsets rounded up to 256 bytes): evolved
  * face values [4 faces (west, east, south, north)][4 vars][C], half-step
  * density increments [C], one time-step bound per workgroup of the
- * corrector or tile of adg_fv_step, a health flag. */
+ * corrector or tile of adg_fv_step, a health flag, and (above 24,576
+ * workgroups) room for the stages of the bounds' minimum. */
 int adg_fv_set_state(adg_fv* m, double* Q, void* workspace, double* clock);
 
 /* Initial cell values at the centres.  kind 0: the hydrostatic background

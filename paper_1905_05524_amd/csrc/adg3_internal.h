@@ -16,6 +16,7 @@ struct Args3 {
   double* Qs;           // [C][5][nd] Q*
   double* FD;           // [C][6][2][5][nn] face data
   double* dtc;          // [C] CFL candidates
+  double* dtmin;        // chunk minima of the candidates, or NULL
   const double* clock;  // (t, dt, -, steps)
   const double* gtab;   // GTab layout
   const double* bg;     // [nz][n + 2][2] background density and pressure: node rows, bottom, top
@@ -39,8 +40,8 @@ int launch_dt3(const Phys& ph, int n, const Args3& a, hipStream_t s);
 int launch_init3(const Phys& ph, int n, const Args3& a, int kind, const Bubbles3& B, double t0, double* Q,
                  hipStream_t s);
 int launch_health3(const Phys& ph, int n, const Args3& a, int* flag, hipStream_t s);
-int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
-                 int update, hipStream_t s);
+int launch_clock(double* clock, const double* dtc, double* part, const int* beg, const int* end, int nscen, int C,
+                 int advance, int update, hipStream_t s);
 
 }  // namespace adg
 
@@ -57,5 +58,5 @@ struct adg3_mesh {
   void* ws = nullptr;
   double* clock = nullptr;
   // workspace partition (byte offsets)
-  size_t off_qs = 0, off_fd = 0, off_dtc = 0, off_health = 0, ws_bytes = 0;
+  size_t off_qs = 0, off_fd = 0, off_dtc = 0, off_health = 0, off_min = 0, ws_bytes = 0;
 };

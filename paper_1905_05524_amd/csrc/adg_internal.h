@@ -94,6 +94,7 @@ struct Group {
   double* Qs = nullptr;       // [C][4][n][n]
   double* FD = nullptr;       // [C][4][2][4][n]
   double* dtc = nullptr;      // [C]
+  double* dtmin = nullptr;    // chunk minima of dtc, or NULL (reduced in one stage)
   double* clock = nullptr;    // [S][4]
   // launch shape: cells per wavefront, wavefronts per workgroup
   int cpw = 1, wpb = 1;
@@ -111,6 +112,11 @@ struct Group {
 
 // TV statistics over many cells: at most kStatParts per-workgroup partials
 constexpr int kStatParts = 512;
+// The minimum of more than kOneStage time-step candidates is taken in two
+// stages: of kChunks chunks, whose minima go to the end of the workspace, then of
+// those.  The section's doubles for C candidates:
+constexpr int kChunks = 256, kOneStage = 24576;
+constexpr size_t chunk_minima(size_t C) { return C > kOneStage ? kChunks : 0; }
 constexpr int kTvPartDoubles = 3 * kStatParts + 3;
 
 // Host copies of the basis of one order.
@@ -192,7 +198,7 @@ struct adg_mesh {
   void* ws = nullptr;
   double* clock = nullptr;
   // workspace partition (byte offsets)
-  size_t off_qs = 0, off_fd = 0, off_dtc = 0, off_health = 0, ws_bytes = 0;
+  size_t off_qs = 0, off_fd = 0, off_dtc = 0, off_health = 0, off_min = 0, ws_bytes = 0;
   // pending regrid (from adg_regrid_plan): new leaves, transfer operations
   // and the new mesh tables
   bool plan_ready = false;

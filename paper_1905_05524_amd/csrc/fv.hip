@@ -39,8 +39,8 @@
 
 namespace adg {
 
-int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
-                 int update, hipStream_t s);
+int launch_clock(double* clock, const double* dtc, double* part, const int* beg, const int* end, int nscen, int C,
+                 int advance, int update, hipStream_t s);
 
 constexpr int kFvThreads = 256;
 constexpr int kFvBubbles = 16;
@@ -605,7 +605,7 @@ struct adg_fv {
   double* Q = nullptr;
   void* ws = nullptr;
   double* clock = nullptr;
-  size_t off_e = 0, off_inc = 0, off_dtb = 0, off_h = 0, ws_bytes = 0;
+  size_t off_e = 0, off_inc = 0, off_dtb = 0, off_h = 0, off_min = 0, ws_bytes = 0;
 };
 
 namespace {
@@ -652,6 +652,11 @@ FvArgs fv_args(const adg_fv* m) {
   for (int f = 0; f < 4; ++f)
     if (m->desc.bc[f] == ADG_BC_WALL) a.wall |= 1 << f;
   return a;
+}
+
+// room for the chunk minima of the time-step bounds, or NULL
+double* fv_minima(const adg_fv* m) {
+  return chunk_minima((size_t)m->blocks) ? reinterpret_cast<double*>(static_cast<char*>(m->ws) + m->off_min) : nullptr;
 }
 
 int fv_need_state(adg_fv* m) {
@@ -708,6 +713,7 @@ int adg_fv_init(const adg_params* prm, const adg_fv_desc* mesh, adg_fv** out) {
   m->off_inc = off; off = align256_fv(off + sizeof(double) * C);
   m->off_dtb = off; off = align256_fv(off + sizeof(double) * std::max(m->blocks, m->tiles));
   m->off_h = off; off = align256_fv(off + sizeof(int));
+  m->off_min = off; off = align256_fv(off + sizeof(double) * chunk_minima((size_t)m->blocks));
   m->ws_bytes = off;
   *out = m;
   return ADG_OK;
@@ -770,7 +776,7 @@ int adg_fv_compute_dt(adg_fv* m, void* stream) {
   hipLaunchKernelGGL(k_fv_dt, dim3(m->blocks), dim3(kFvThreads), 0, s, m->ph, a);
   rc = check_launch("fv_dt");
   if (rc) return rc;
-  return launch_clock(m->clock, a.dtb, nullptr, nullptr, 1, m->blocks, 0, 1, s);
+  return launch_clock(m->clock, a.dtb, fv_minima(m), nullptr, nullptr, 1, m->blocks, 0, 1, s);
 }
 
 int adg_fv_predictor(adg_fv* m, void* stream) {
@@ -788,7 +794,7 @@ int adg_fv_corrector(adg_fv* m, void* stream) {
   hipLaunchKernelGGL(k_fv_correct, dim3(m->blocks), dim3(kFvThreads), 0, s, m->ph, a);
   rc = check_launch("fv_correct");
   if (rc) return rc;
-  return launch_clock(m->clock, a.dtb, nullptr, nullptr, 1, m->blocks, 1, m->prm.fixed_dt ? 0 : 1, s);
+  return launch_clock(m->clock, a.dtb, fv_minima(m), nullptr, nullptr, 1, m->blocks, 1, m->prm.fixed_dt ? 0 : 1, s);
 }
 
 int adg_fv_step(adg_fv* m, void* stream) {

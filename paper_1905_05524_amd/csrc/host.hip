@@ -12,8 +12,8 @@ namespace adg {
 int launch_predictor(const Group& g, double* store, hipStream_t s);
 int launch_corrector(const Group& g, hipStream_t s);
 int launch_cell_dt(const Group& g, hipStream_t s);
-int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance,
-                 int update, hipStream_t s);
+int launch_clock(double* clock, const double* dtc, double* part, const int* beg, const int* end, int nscen, int C,
+                 int advance, int update, hipStream_t s);
 int max_cpw(int n);
 int launch_init_state(const Group& g, int c0, int count, int kind, int nbub, const double* d_bub, double t0,
                       hipStream_t s);
@@ -46,7 +46,7 @@ int launch_corrector_clock(Group g, double* clock, hipStream_t s) {
   }
   int rc = launch_corrector(g, s);
   if (rc) return rc;
-  return launch_clock(clock, g.dtc, nullptr, nullptr, 1, g.C, 1, 1, s);
+  return launch_clock(clock, g.dtc, g.dtmin, nullptr, nullptr, 1, g.C, 1, 1, s);
 }
 
 void set_error(const std::string& msg) { g_err = msg; }
@@ -499,19 +499,21 @@ static int autotune_group(Group& g, hipStream_t s, int reps, float* best_ms) {
   return check_launch("autotune");
 }
 
-// workspace: Q* [C][4][n][n], face data [C][4][2][4][n], CFL candidates, health flag
-static size_t workspace_size(int C_, int n, size_t* off_qs, size_t* off_fd, size_t* off_dtc, size_t* off_h) {
+// workspace: Q* [C][4][n][n], face data [C][4][2][4][n], CFL candidates, health flag, chunk minima of the candidates
+static size_t workspace_size(int C_, int n, size_t* off_qs, size_t* off_fd, size_t* off_dtc, size_t* off_h,
+                             size_t* off_min) {
   const size_t C = (size_t)C_;
   size_t off = 0;
   *off_qs = off; off = align256(off + sizeof(double) * C * 4 * n * n);
   *off_fd = off; off = align256(off + sizeof(double) * C * 32 * n);
   *off_dtc = off; off = align256(off + sizeof(double) * C);
   *off_h = off; off = align256(off + sizeof(int));
+  *off_min = off; off = align256(off + sizeof(double) * chunk_minima(C));
   return off;
 }
 
 static void layout_workspace(adg_mesh* m) {
-  m->ws_bytes = workspace_size(m->g.C, m->g.n, &m->off_qs, &m->off_fd, &m->off_dtc, &m->off_health);
+  m->ws_bytes = workspace_size(m->g.C, m->g.n, &m->off_qs, &m->off_fd, &m->off_dtc, &m->off_health, &m->off_min);
 }
 
 }  // namespace adg
@@ -585,6 +587,7 @@ int adg_set_state(adg_mesh* m, double* Q, void* workspace, double* clock) {
   m->g.Qs = reinterpret_cast<double*>(ws + m->off_qs);
   m->g.FD = reinterpret_cast<double*>(ws + m->off_fd);
   m->g.dtc = reinterpret_cast<double*>(ws + m->off_dtc);
+  m->g.dtmin = chunk_minima((size_t)m->g.C) ? reinterpret_cast<double*>(ws + m->off_min) : nullptr;
   m->g.clock = clock;
   return ADG_OK;
 }
@@ -602,7 +605,7 @@ int adg_compute_dt(adg_mesh* m, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   rc = launch_cell_dt(m->g, s);
   if (rc) return rc;
-  return launch_clock(m->clock, m->g.dtc, nullptr, nullptr, 1, m->g.C, 0, 1, s);
+  return launch_clock(m->clock, m->g.dtc, m->g.dtmin, nullptr, nullptr, 1, m->g.C, 0, 1, s);
 }
 
 int adg_predictor(adg_mesh* m, void* stream) {
@@ -682,9 +685,9 @@ int adg_regrid_plan(adg_mesh* m, const int8_t* flags_host, int* n_cells_new, siz
   d.leaf_level = m->plan_lev.data(); d.leaf_i = m->plan_ci.data(); d.leaf_j = m->plan_cj.data();
   rc = build_mesh(d, m->plan_mesh);   // kept for adg_regrid_apply
   if (rc) return fail(ADG_EUNSUPPORTED, std::string("regrid result is not a valid mesh: ") + g_err);
-  size_t a, b, c, e;
+  size_t a, b, c, e, f;
   if (n_cells_new) *n_cells_new = d.n_leaves;
-  if (ws_bytes_new) *ws_bytes_new = workspace_size(d.n_leaves, m->g.n, &a, &b, &c, &e);
+  if (ws_bytes_new) *ws_bytes_new = workspace_size(d.n_leaves, m->g.n, &a, &b, &c, &e, &f);
   m->plan_ready = true;
   return ADG_OK;
 }
@@ -1000,7 +1003,7 @@ static int batch_enqueue_step(adg_batch* b, hipStream_t s) {
     if (hipEventRecord(b->events[1 + g], gs) != hipSuccess) return fail(ADG_EHIP, "event record");
     if (hipStreamWaitEvent(s, b->events[1 + g], 0) != hipSuccess) return fail(ADG_EHIP, "stream wait");
   }
-  return launch_clock(b->clock, b->dtc, b->d_beg, b->d_end, b->S, b->C_total, 1, b->prm0.fixed_dt ? 0 : 1, s);
+  return launch_clock(b->clock, b->dtc, nullptr, b->d_beg, b->d_end, b->S, b->C_total, 1, b->prm0.fixed_dt ? 0 : 1, s);
 }
 
 }  // namespace adg
@@ -1182,7 +1185,7 @@ int adg_batch_compute_dt(adg_batch* b, void* stream) {
     rc = launch_cell_dt(g, s);
     if (rc) return rc;
   }
-  return launch_clock(b->clock, b->dtc, b->d_beg, b->d_end, b->S, b->C_total, 0, 1, s);
+  return launch_clock(b->clock, b->dtc, nullptr, b->d_beg, b->d_end, b->S, b->C_total, 0, 1, s);
 }
 
 int adg_batch_step(adg_batch* b, void* stream) {

@@ -32,6 +32,7 @@ static Args3 args_of(const adg3_mesh* m) {
   a.Qs = ws ? reinterpret_cast<double*>(ws + m->off_qs) : nullptr;
   a.FD = ws ? reinterpret_cast<double*>(ws + m->off_fd) : nullptr;
   a.dtc = ws ? reinterpret_cast<double*>(ws + m->off_dtc) : nullptr;
+  a.dtmin = ws && chunk_minima((size_t)m->C) ? reinterpret_cast<double*>(ws + m->off_min) : nullptr;
   a.clock = m->clock; a.gtab = m->d_gtab; a.bg = m->d_bg;
   a.nx = m->desc.nx; a.ny = m->desc.ny; a.nz = m->desc.nz; a.C = m->C; a.iters = m->iters;
   a.wall = 0;
@@ -92,6 +93,7 @@ int adg3_init_mesh(const adg_params* prm, const adg3_mesh_desc* mesh, adg3_mesh*
   m->off_fd = off; off = align256_3(off + sizeof(double) * C * 60 * nn);
   m->off_dtc = off; off = align256_3(off + sizeof(double) * C);
   m->off_health = off; off = align256_3(off + sizeof(int));
+  m->off_min = off; off = align256_3(off + sizeof(double) * chunk_minima(C));
   m->ws_bytes = off;
   *out = m;
   return ADG_OK;
@@ -152,7 +154,7 @@ int adg3_compute_dt(adg3_mesh* m, void* stream) {
   const Args3 a = args_of(m);
   rc = launch_dt3(m->ph, m->n, a, s);
   if (rc) return rc;
-  return launch_clock(m->clock, a.dtc, nullptr, nullptr, 1, m->C, 0, 1, s);
+  return launch_clock(m->clock, a.dtc, a.dtmin, nullptr, nullptr, 1, m->C, 0, 1, s);
 }
 
 int adg3_predictor(adg3_mesh* m, void* stream) {
@@ -168,7 +170,7 @@ int adg3_corrector(adg3_mesh* m, void* stream) {
   const Args3 a = args_of(m);
   rc = launch_corr3(m->ph, m->n, a, s);
   if (rc) return rc;
-  return launch_clock(m->clock, a.dtc, nullptr, nullptr, 1, m->C, 1, m->ph.fixed_dt ? 0 : 1, s);
+  return launch_clock(m->clock, a.dtc, a.dtmin, nullptr, nullptr, 1, m->C, 1, m->ph.fixed_dt ? 0 : 1, s);
 }
 
 int adg3_step(adg3_mesh* m, void* stream) {

@@ -294,11 +294,9 @@ __global__ __launch_bounds__(kWave) void k_cell_dt(Phys ph, StepArgs a) {
 // Clock update, one workgroup per scenario: if advance, t += dt and
 // steps += 1; if update, dt <- min of the CFL candidates of the scenario's
 // cells [beg[s], end[s]) (min is exact, so the result is order independent).
-// Every stride-th entry of dtc is read.
 constexpr int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void k_clock(double* clock, const double* dtc, const int* beg,
-                                                           const int* end, int C, int stride, int advance,
-                                                           int update) {
+                                                           const int* end, int C, int advance, int update) {
   __shared__ double sm[kReduceThreads / kWave];
   const int s = blockIdx.x, t = threadIdx.x;
   const int b0 = beg ? beg[s] : 0, b1 = end ? end[s] : C;
@@ -310,12 +308,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_clock(double* clock, const d
     // four independent loads in flight per thread
     int c = b0 + t;
     for (; c + 3 * kReduceThreads < b1; c += 4 * kReduceThreads) {
-      const double* p = dtc + (size_t)c * stride;
-      const double a0 = p[0], a1 = p[(size_t)kReduceThreads * stride], a2 = p[(size_t)2 * kReduceThreads * stride],
-                   a3 = p[(size_t)3 * kReduceThreads * stride];
+      const double a0 = dtc[c], a1 = dtc[c + kReduceThreads], a2 = dtc[c + 2 * kReduceThreads],
+                   a3 = dtc[c + 3 * kReduceThreads];
       m = fmin(m, fmin(fmin(a0, a1), fmin(a2, a3)));
     }
-    for (; c < b1; c += kReduceThreads) m = fmin(m, dtc[(size_t)c * stride]);
+    for (; c < b1; c += kReduceThreads) m = fmin(m, dtc[c]);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) m = fmin(m, __shfl_xor(m, o, kWave));
@@ -329,9 +326,9 @@ __global__ __launch_bounds__(kReduceThreads) void k_clock(double* clock, const d
   }
 }
 
-// Minimum of every chunk of len candidates, left in the chunk's first entry.
+// Minimum of every chunk of len candidates.
 constexpr int kChunkThreads = 256;
-__global__ __launch_bounds__(kChunkThreads) void k_chunk_min(double* dtc, int C, int len) {
+__global__ __launch_bounds__(kChunkThreads) void k_chunk_min(const double* dtc, double* part, int C, int len) {
   __shared__ double sm[kChunkThreads / kWave];
   const int t = threadIdx.x;
   const long long b0 = (long long)blockIdx.x * len, b1 = min(b0 + len, (long long)C);
@@ -340,10 +337,10 @@ __global__ __launch_bounds__(kChunkThreads) void k_chunk_min(double* dtc, int C,
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) m = fmin(m, __shfl_xor(m, o, kWave));
   if ((t & (kWave - 1)) == 0) sm[t / kWave] = m;
-  __syncthreads();   // every candidate of the chunk read before its first is overwritten
+  __syncthreads();
   if (t == 0) {
     for (int k = 1; k < kChunkThreads / kWave; ++k) m = fmin(m, sm[k]);
-    dtc[b0] = m;
+    part[blockIdx.x] = m;
   }
 }
 
@@ -447,22 +444,21 @@ static int dt_n(const Group& g, hipStream_t s) {
 int launch_corrector(const Group& g, hipStream_t s) { ADG_DISPATCH_N(corr_n, g, s); }
 int launch_cell_dt(const Group& g, hipStream_t s) { ADG_DISPATCH_N(dt_n, g, s); }
 
-int launch_clock(double* clock, double* dtc, const int* beg, const int* end, int nscen, int C, int advance, int update,
-                 hipStream_t s) {
+int launch_clock(double* clock, const double* dtc, double* part, const int* beg, const int* end, int nscen, int C,
+                 int advance, int update, hipStream_t s) {
   if (nscen <= 0) return ADG_OK;
-  // One mesh of many cells: one workgroup reads no more than 50 GB/s, so 256
-  // of them reduce chunks first.  Corrector and clock in one stage and in two:
+  // One mesh of many cells with room for the chunks' minima (part: the
+  // candidates themselves stay, callers read them): one workgroup reads no more
+  // than 50 GB/s, so 256 of them reduce chunks first.  Corrector and clock in one stage and in two:
   // 22,500 cells of n = 2 12.2 and 11.9 us (a step 32.1 and 32.5), 32,400 17.3
   // and 15.6, 62,500 26.6 and 22.5, 531,441 of n = 7 868 and 791.
-  constexpr int kChunks = 256, kOneStage = 24576;
-  int stride = 1;
-  if (!beg && update && C > kOneStage) {
-    stride = (C + kChunks - 1) / kChunks;
-    const int chunks = (C + stride - 1) / stride;
-    hipLaunchKernelGGL(k_chunk_min, dim3(chunks), dim3(kChunkThreads), 0, s, dtc, C, stride);
+  if (part && !beg && update && C > kOneStage) {
+    const int len = (C + kChunks - 1) / kChunks, chunks = (C + len - 1) / len;
+    hipLaunchKernelGGL(k_chunk_min, dim3(chunks), dim3(kChunkThreads), 0, s, dtc, part, C, len);
+    dtc = part;
     C = chunks;
   }
-  hipLaunchKernelGGL(k_clock, dim3(nscen), dim3(kReduceThreads), 0, s, clock, dtc, beg, end, C, stride, advance, update);
+  hipLaunchKernelGGL(k_clock, dim3(nscen), dim3(kReduceThreads), 0, s, clock, dtc, beg, end, C, advance, update);
   return check_launch("clock");
 }
 

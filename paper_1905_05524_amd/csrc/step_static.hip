@@ -51,8 +51,9 @@ extern "C" int adg_step_static(adg_mesh* m, double* Q, double* clock, void* stre
   if (!Q || !clock) return fail(ADG_EINVAL, "null buffer");
   if (((uintptr_t)Q & 7) != 0 || ((uintptr_t)clock & 7) != 0) return fail(ADG_EINVAL, "misaligned buffer");
   if (m->g.C == 0) return fail(ADG_ESTATE, "mesh has no cells");
-  if (m->ws_bytes > kStaticScratchBytes)
-    return fail(ADG_EINVAL, "mesh needs " + std::to_string(m->ws_bytes) + " bytes of workspace; the static scratch holds " +
+  // (without room for the chunk minima the time step is reduced in one stage)
+  if (m->off_min > kStaticScratchBytes)
+    return fail(ADG_EINVAL, "mesh needs " + std::to_string(m->off_min) + " bytes of workspace; the static scratch holds " +
                                 std::to_string(kStaticScratchBytes));
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return fail(ADG_EHIP, "no current device");
@@ -67,6 +68,8 @@ extern "C" int adg_step_static(adg_mesh* m, double* Q, double* clock, void* stre
   g.Qs = reinterpret_cast<double*>(ws + m->off_qs);
   g.FD = reinterpret_cast<double*>(ws + m->off_fd);
   g.dtc = reinterpret_cast<double*>(ws + m->off_dtc);
+  g.dtmin = chunk_minima((size_t)g.C) && m->ws_bytes <= kStaticScratchBytes
+                ? reinterpret_cast<double*>(ws + m->off_min) : nullptr;
   g.clock = clock;
   hipStream_t s = static_cast<hipStream_t>(stream);
   int rc = launch_predictor(g, nullptr, s);
