@@ -350,19 +350,25 @@ __device__ inline void paper_wave_source(const Phys& ph, double x, double z, dou
   S[3] = 2.0 * k * H1 - om * E1 - (16.0 / 3.0) * ph.mu * kk * (u1 * u1 + u * u2) - 2.0 * ph.kappa * kk * T2;
 }
 
-// Square root: the hardware estimate of 1/sqrt(x), one coupled Newton step for
-// root and half reciprocal and a last correction of the root (within an ulp);
-// 0 and infinity as they are.  Without the library's scaling for the smallest
-// numbers, 12 instructions instead of 20.
+// Square root, correctly rounded.  Goldschmidt's coupled iteration for the root
+// g and the half reciprocal h from the hardware estimate of 1/sqrt(x), then two
+// Newton corrections of g with the residual x - g^2 formed by one fused
+// multiply-add (Markstein, Computation of elementary functions on the IBM RISC
+// System/6000 processor, 1990).  Below 2^-767 that residual would lose bits to
+// underflow: those numbers, negative ones, infinity and NaN (by one comparison
+// of the high word) take the library's root, which scales its argument.  12
+// instructions and a branch that wavefronts of ordinary states jump over,
+// instead of 20.
 __device__ inline double root(double x) {
+  constexpr unsigned lo = 0x10000000u, inf = 0x7ff00000u;   // high words of 2^-767 and infinity
+  if ((unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32) - lo >= inf - lo) return sqrt(x);
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
   const double r = fma(-h, g, 0.5);
   g = fma(g, r, g);
   h = fma(h, r, h);
   g = fma(fma(-g, g, x), h, g);
-  g = fma(fma(-g, g, x), h, g);
-  return __builtin_amdgcn_class(x, 0x260) ? x : g;   // +-0, +infinity
+  return fma(fma(-g, g, x), h, g);
 }
 
 // Lane exchange within rows of 16 lanes through the data-parallel primitives

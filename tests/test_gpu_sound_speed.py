@@ -1,0 +1,32 @@
+"""The square root of the wave speeds over the whole range of doubles.  With
+gamma = 2, rho = 1 and no motion the speed of a 3D cell of energy E is the root
+of 2 E with no rounding before it, and its time-step candidate is cfl h / (9
+root): it has to be the one of the correctly rounded root, bit for bit, at
+every exponent, the subnormal numbers among them."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1905_05524_amd import adg
+from paper_1905_05524_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def test_root_is_correctly_rounded():
+    rng = np.random.default_rng(1)
+    nx = 24000
+    phys = dict(I.CFD, gamma=2.0, N=1, picard_iters=1, mu=0.0, mms=0, cfl=0.5)
+    m = adg.Mesh3(phys, dict(nx=nx, ny=1, nz=1, h=1.0, bc=[I.BC_PERIODIC] * 6))
+    E = np.ldexp(1.0 + rng.random(nx), rng.integers(-1074, 1022, nx))
+    E[:8] = [0.0, 5e-324, 2.0 ** -1022, 2.0 ** -767, 2.0 ** -768, 2.0 ** -769, np.inf, -1.0]
+    E[8:64] = np.nextafter(2.0 ** np.arange(-28.0, 28.0), 0.0)   # just below a square, or twice one
+    m.Q.zero_()
+    m.Q[:, 0] = 1.0
+    m.Q[:, 4] = torch.as_tensor(E, device="cuda").view(nx, 1, 1, 1)
+    m.compute_dt()
+    got = m.cell_dt().cpu().numpy()
+    with np.errstate(all="ignore"):
+        want = 0.5 / (9.0 * np.sqrt(2.0 * E))
+    assert np.array_equal(got, want, equal_nan=True), [(E[k], got[k], want[k]) for k in np.flatnonzero(got != want)[:8]]
