@@ -338,6 +338,7 @@ class Mesh:
         _check(lib().adg_regrid_apply(self.h, ctypes.c_void_p(Qn.data_ptr()), ctypes.c_void_p(wsn.data_ptr()),
                                       ctypes.c_void_p(self.clock.data_ptr()), _stream_ptr(stream)))
         self.Q, self.ws, self.C, self.ws_bytes = Qn, wsn, nc.value, wb.value
+        self._adj_ws = None   # sized for the old cells
         return self.C
 
     # -- adjoint ---------------------------------------------------------------
