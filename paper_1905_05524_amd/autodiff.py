@@ -32,10 +32,6 @@ class ThetaRollout(torch.autograd.Function):
         # checkpoints Q^0 .. Q^K: the loss adjoint reads the rollout's own end
         # state, whatever the mesh is used for between forward and backward
         ck = torch.empty((steps + 1,) + tuple(m.Q.shape), dtype=torch.float64, device=m.device)
-        # fills: assigning a Python number copies it from pageable memory, and
-        # that copy waits until the device has done all earlier work
-        m.clock[0:1].fill_(float(t0))
-        m.clock[1:2].fill_(float(dt))
         stores = fds = None
         if keep:
             sb, fb = m.keep_bytes()
@@ -44,7 +40,11 @@ class ThetaRollout(torch.autograd.Function):
         # each step reads checkpoint k (bound) and writes checkpoint k + 1
         try:
             m.bind_state(ck[0])
-            m.ic_theta(th)
+            m.ic_theta(th)   # a refusal leaves state and clock as they were
+            # fills: assigning a Python number copies it from pageable memory,
+            # and that copy waits until the device has done all earlier work
+            m.clock[0:1].fill_(float(t0))
+            m.clock[1:2].fill_(float(dt))
             for k in range(steps):
                 m.bind_state(ck[k])
                 if keep:
