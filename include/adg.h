@@ -229,9 +229,10 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
 
 /* Launch shape of the predictor and corrector: cells per wavefront (1, 2 or
  * 4, with cells_per_wave * n^2 <= 64) and wavefronts per workgroup (1, 2 or
- * 4).  The corrector takes the shape as it is.  The predictor gives n^2 lanes
- * to a cell and takes from the shape which of its kernels runs: 1, 1 one cell
- * per wavefront; 1 with 2 or 4 the packing of the order that spans
+ * 4).  The corrector takes the shape as it is (with cells_per_wave 0 its
+ * default, as many cells as a wavefront has lanes for).  The predictor gives
+ * n^2 lanes to a cell and takes from the shape which of its kernels runs: 1, 1
+ * one cell per wavefront; 1 with 2 or 4 the packing of the order that spans
  * wavefronts (orders 4 and 5; else as many cells as a wavefront holds); 2 or
  * 4 as many cells as a wavefront holds; cells_per_wave 0 (waves_per_block 1,
  * 2 or 4, all the same) four wavefronts per cell, for meshes too small to
@@ -241,9 +242,11 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
  * adg_autotune reports four wavefronts per cell as 0, 1. */
 int adg_set_launch(adg_mesh* m, int cells_per_wave, int waves_per_block);
 
-/* Time every launch shape on the bound state (reps predictor + corrector
- * pairs each; the corrector writes into the workspace so Q and clock are left
- * unchanged), keep the fastest and return it.  Synchronises the stream. */
+/* Time the default and every launch shape on the bound state (reps predictor
+ * + corrector pairs each; the corrector writes into the workspace so Q and
+ * clock are left unchanged), keep the fastest and return it.  For the default
+ * that is the shape with the same predictor kernel: set on another handle it
+ * gives that handle's corrector the shape too.  Synchronises the stream. */
 int adg_autotune(adg_mesh* m, int reps, void* stream, int* cells_per_wave, int* waves_per_block);
 
 /* --------------------------------------------------------------- adjoint

@@ -10,6 +10,7 @@
 namespace adg {
 
 int launch_predictor(const Group& g, double* store, hipStream_t s);
+void predictor_shape(const Group& g, int* cpw, int* wpb);
 int launch_corrector(const Group& g, hipStream_t s);
 int launch_cell_dt(const Group& g, hipStream_t s);
 int launch_clock(double* clock, const double* dtc, double* part, const int* beg, const int* end, int nscen, int C,
@@ -463,15 +464,18 @@ static int autotune_group(Group& g, hipStream_t s, int reps, float* best_ms) {
   if (g.C == 0) return ADG_OK;
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return fail(ADG_EHIP, "event");
-  // candidates: (lv, cpw, wpb); lv = 1 is the predictor with four wavefronts
-  // per cell (its corrector shape is the default one)
+  // candidates: (lv, cpw, wpb); lv = 1 the predictor with four wavefronts per
+  // cell (and the default corrector), lv = 0 the shapes, lv = -1 the defaults
+  // of both: last, as the first ones run before the clocks have settled (timed
+  // first, the default of 200 x 200 cells of order 4, 233 us a step, lost to a
+  // shape of 247)
   const int cpws[3] = {1, 2, 4}, wpbs[3] = {1, 2, 4};
   int bl = g.lv, bc = g.cpw, bw = g.wpb;
   float best = 1e30f;
-  for (int k = -1; k < 9; ++k) {
+  for (int k = -1; k < 10; ++k) {
     Group t = g;
-    if (k < 0) {
-      t.lv = 1; t.cpw = 1; t.wpb = 1;
+    if (k < 0 || k == 9) {
+      t.lv = k < 0 ? 1 : -1; t.cpw = 1; t.wpb = 1;
     } else {
       t.lv = 0; t.cpw = cpws[k / 3]; t.wpb = wpbs[k % 3];
       if (t.cpw > max_cpw(g.n)) continue;
@@ -926,8 +930,10 @@ int adg_autotune(adg_mesh* m, int reps, void* stream, int* cells_per_wave, int* 
   if (reps < 1) return fail(ADG_EINVAL, "reps < 1");
   rc = autotune_group(m->g, (hipStream_t)stream, reps, nullptr);
   if (rc) return rc;
-  if (cells_per_wave) *cells_per_wave = m->g.lv == 1 ? 0 : m->g.cpw;
-  if (waves_per_block) *waves_per_block = m->g.lv == 1 ? 1 : m->g.wpb;
+  int cpw, wpb;
+  predictor_shape(m->g, &cpw, &wpb);
+  if (cells_per_wave) *cells_per_wave = cpw;
+  if (waves_per_block) *waves_per_block = wpb;
   return ADG_OK;
 }
 
@@ -1229,11 +1235,10 @@ int adg_batch_autotune(adg_batch* b, int reps, void* stream, int* cells_per_wave
   for (size_t gi = 0; gi < b->groups.size(); ++gi) {
     rc = autotune_group(b->groups[gi], (hipStream_t)stream, reps, nullptr);
     if (rc) return rc;
-    if (cells_per_wave) cells_per_wave[gi] = b->groups[gi].lv == 1 ? 0 : b->groups[gi].cpw;
-    if (waves_per_block) {
-      const Group& gg = b->groups[gi];
-      waves_per_block[gi] = gg.lv == 1 ? 1 : gg.wpb;
-    }
+    int cpw, wpb;
+    predictor_shape(b->groups[gi], &cpw, &wpb);
+    if (cells_per_wave) cells_per_wave[gi] = cpw;
+    if (waves_per_block) waves_per_block[gi] = wpb;
   }
   if (b->exec) { (void)hipGraphExecDestroy(b->exec); b->exec = nullptr; }
   if (b->graph) { (void)hipGraphDestroy(b->graph); b->graph = nullptr; }

@@ -902,6 +902,14 @@ static Kernel pick(const Group& g) {
   return Kernel::kWave;
 }
 
+// the launch shape of a group; one that runs the same kernel for a group without
+void predictor_shape(const Group& g, int* cpw, int* wpb) {
+  const Kernel k = pick(g);
+  if (g.lv == 0) { *cpw = g.cpw; *wpb = g.wpb; return; }
+  *cpw = k == Kernel::kSplit ? 0 : k == Kernel::kWave ? max_cpw_c(g.n) : 1;
+  *wpb = k == Kernel::kPacked ? 2 : 1;
+}
+
 template <int n>
 static int predict_n(const Group& g, double* store, hipStream_t s) {
   if (g.C == 0) return ADG_OK;

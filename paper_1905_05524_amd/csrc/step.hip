@@ -416,7 +416,7 @@ constexpr int corr_cells(int n) { return n == 2 ? 8 : n == 3 ? 5 : n == 4 ? 4 : 
 template <int n>
 static int corr_n(const Group& g, hipStream_t s) {
   constexpr int nn = n * n;
-  if (g.lv < 0) return launch_corr_t<n, corr_cells(n), 1>(g, s);
+  if (g.lv != 0) return launch_corr_t<n, corr_cells(n), 1>(g, s);
   if (g.cpw == 1) return corr_w<n, 1>(g, s);
   if constexpr (2 * nn <= kWave) { if (g.cpw == 2) return corr_w<n, 2>(g, s); }
   if constexpr (4 * nn <= kWave) { if (g.cpw == 4) return corr_w<n, 4>(g, s); }
