@@ -406,16 +406,18 @@ static int upload_group(Group& g, const std::vector<double>& geom, const std::ve
   if (e != hipSuccess) { free_group(g); return fail(ADG_ENOMEM, "device allocation failed"); }
   if (C) {
     e = hipMemcpy(g.d_geom, geom.data(), sizeof(double) * 4 * C, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(g.d_nbr, nbr.data(), sizeof(int) * 16 * C, hipMemcpyHostToDevice);
     if (e == hipSuccess && scen) e = hipMemcpy(g.d_scen, scen->data(), sizeof(int) * C, hipMemcpyHostToDevice);
   }
   if (e == hipSuccess) e = hipMemcpy(g.d_gtab, gtab.data(), sizeof(double) * gtab.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) {
+    // the background table, complete before any stream can use the handle: the
+    // last upload follows it on the same stream and is waited for anyway
+    const int rc = launch_background(g, g.C, nullptr);
+    if (rc) { free_group(g); return rc; }
+    if (C) e = hipMemcpy(g.d_nbr, nbr.data(), sizeof(int) * 16 * C, hipMemcpyHostToDevice);
+  }
   if (e != hipSuccess) { free_group(g); return fail(ADG_EHIP, "upload failed"); }
-  // the background table is complete before any stream can use the handle
-  int rc = launch_background(g, g.C, nullptr);
-  if (rc == ADG_OK && hipStreamSynchronize(nullptr) != hipSuccess) rc = fail(ADG_EHIP, "background table failed");
-  if (rc) free_group(g);
-  return rc;
+  return ADG_OK;
 }
 
 static int need_state(adg_mesh* m) {

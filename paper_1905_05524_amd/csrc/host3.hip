@@ -71,21 +71,25 @@ int adg3_init_mesh(const adg_params* prm, const adg3_mesh_desc* mesh, adg3_mesh*
   m->iters = prm->picard_iters > 0 ? prm->picard_iters : m->n;
   m->ph = make_phys(*prm);
   build_basis(m->n, m->basis);
-  const size_t tb = sizeof(double) * m->basis.gtab.size();
-  const size_t bb = sizeof(double) * 2 * (size_t)mesh->nz * (m->n + 2);
-  if (hipMalloc(&m->d_gtab, tb + bb) != hipSuccess) { delete m; return fail(ADG_ENOMEM, "device allocation failed"); }
+  // basis tables, then the background: zeros without gravity
+  std::vector<double> tab(m->basis.gtab);
+  tab.resize(tab.size() + 2 * (size_t)mesh->nz * (m->n + 2), 0.0);
+  const size_t tb = sizeof(double) * tab.size();
+  if (hipMalloc(&m->d_gtab, tb) != hipSuccess) { delete m; return fail(ADG_ENOMEM, "device allocation failed"); }
   m->d_bg = m->d_gtab + m->basis.gtab.size();
-  if (hipMemcpy(m->d_gtab, m->basis.gtab.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
+  if (hipMemcpy(m->d_gtab, tab.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(m->d_gtab);
     delete m;
     return fail(ADG_EHIP, "upload failed");
   }
-  // the table is complete before any stream can use the handle
-  rc = launch_background3(m->ph, m->n, args_of(m), m->d_bg, nullptr);
-  if (rc || hipStreamSynchronize(nullptr) != hipSuccess) {
-    (void)hipFree(m->d_gtab);
-    delete m;
-    return rc ? rc : fail(ADG_EHIP, "background table failed");
+  if (m->prm.gravity) {
+    // the table is complete before any stream can use the handle
+    rc = launch_background3(m->ph, m->n, args_of(m), m->d_bg, nullptr);
+    if (rc || hipStreamSynchronize(nullptr) != hipSuccess) {
+      (void)hipFree(m->d_gtab);
+      delete m;
+      return rc ? rc : fail(ADG_EHIP, "background table failed");
+    }
   }
   const size_t C = (size_t)m->C, nd = (size_t)m->n * m->n * m->n, nn = (size_t)m->n * m->n;
   size_t off = 0;
