@@ -45,12 +45,13 @@ __device__ inline void wall_ghost(const Phys& ph, int d, double zf, const double
 
 // |v| + c and lambda_v for the larger of the momenta ma, mb (one twice: the
 // normal speed of a face): one reciprocal and one square root, where the two
-// directions of a node apart took four divisions and two roots
+// directions of a node apart took four divisions and two roots (|1/rho|: the
+// velocity's magnitude also where a flow has driven rho below zero)
 __device__ inline void eig(const Phys& ph, const double q[4], double ma, double mb, double z, double& lam, double& lv) {
   const double ir = recip(q[0]);
   const double ke = fma(q[1], q[1], q[2] * q[2]) * ir;                        // rho |v|^2
   const double p = ph.gm1 * (fma(-0.5, ke, q[3]) - q[0] * (ph.geff * z));
-  lam = fmax(fabs(ma), fabs(mb)) * ir + sqrt(ph.gamma * p * ir);
+  lam = fmax(fabs(ma), fabs(mb)) * fabs(ir) + sqrt(ph.gamma * p * ir);
   lv = ph.lv_coef * ir;
 }
 
