@@ -236,7 +236,7 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
  * wavefronts (orders 4 and 5; else as many cells as a wavefront holds); 2 or
  * 4 as many cells as a wavefront holds; cells_per_wave 0 (waves_per_block 1,
  * 2 or 4, all the same) four wavefronts per cell, for meshes too small to
- * fill the GPU with one.  Results do not depend on the shape.
+ * fill the GPU with one.  Results do not depend on the shape, to the last bit.
  * Default: by order and cells (four wavefronts per cell up to 768 cells at
  * orders 5 and up and 384 below, then the packing measured fastest).
  * adg_autotune reports four wavefronts per cell as 0, 1. */
@@ -349,12 +349,9 @@ int adg_batch_set_launch(adg_batch* b, int group, int cells_per_wave, int waves_
  * of resident wavefronts that take work items (one wavefront's cells) from
  * a device counter (reset by the grid's last wavefront), each order's grid
  * sized by its share of the modelled predictor work (cells x (N+1)^4).
- * Its bits are those of the per-order mode with one wavefront per cell
- * (adg_batch_set_launch with cells_per_wave >= 1); a group that the
- * per-order mode runs with one wavefront per time level (small groups, by
- * default) sums the levels in another order and agrees to rounding.  The
- * persistent mode measured slower (its loop
- * around the order-6 body spills registers) and exists for comparison.
+ * Its bits are those of the per-order mode.  The persistent mode measured
+ * slower (its loop around the order-6 body spills registers) and exists for
+ * comparison.
  * Drops a captured graph; EUNSUPPORTED for the paper's manufactured
  * solution in persistent mode. */
 enum { ADG_BATCH_PER_ORDER = 0, ADG_BATCH_PERSISTENT = 1 };

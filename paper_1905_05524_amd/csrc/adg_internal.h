@@ -300,12 +300,12 @@ __device__ inline WavePhase wave_phase(const Phys& ph, double X, double Z) {
 __device__ inline double mms_source(const Phys& ph, const WavePhase& a, const WavePhase& b) {
   const double sx = fma(a.sx, b.cx, -(a.cx * b.sx)), cx = fma(a.cx, b.cx, a.sx * b.sx);
   const double sz = fma(a.sz, b.cz, -(a.cz * b.sz)), cz = fma(a.cz, b.cz, a.sz * b.sz);
-  double rho = 1.0 + ph.mms_amp * sx * sz;
+  double rho = fma(ph.mms_amp * sx, sz, 1.0);
   double rx = ph.mms_amp * ph.mms_kx * cx * sz;
   double rz = ph.mms_amp * ph.mms_kz * sx * cz;
-  double lap = -(ph.mms_kx * ph.mms_kx + ph.mms_kz * ph.mms_kz) * ph.mms_amp * sx * sz;
+  double lap = -fma(ph.mms_kx, ph.mms_kx, ph.mms_kz * ph.mms_kz) * ph.mms_amp * sx * sz;
   double ir = recip(rho);
-  double lapT = ph.mms_p * ph.iR * (-lap * ir * ir + 2.0 * (rx * rx + rz * rz) * ir * ir * ir);
+  double lapT = ph.mms_p * ph.iR * fma(-lap * ir, ir, 2.0 * fma(rx, rx, rz * rz) * ir * ir * ir);
   return -ph.kappa * lapT;
 }
 
@@ -327,27 +327,29 @@ __device__ inline void paper_wave_state(const Phys& ph, double x, double z, doub
 // S = dQ/dt + div F, from the derivatives of the fields along xi (primes):
 // the stress tensor gives sigma_xx = sigma_zz = -(2/3) mu k u',
 // sigma_xz = -2 mu k u'; the heat flux -kappa k T' with T = p/(R rho), whose
-// second derivative follows from differentiating R rho T = p twice.
+// second derivative follows from differentiating R rho T = p twice.  (Fused
+// operations spelt out: the predictors that call it agree bit for bit.)
 __device__ inline void paper_wave_source(const Phys& ph, double x, double z, double t, double S[4]) {
   constexpr double k = kWaveK, om = kWaveOm;
   double sn, cs;
-  sincos(k * (x + z) - om * t, &sn, &cs);
-  const double rho = 1.0 + 0.5 * sn, r1 = 0.5 * cs, r2 = -0.5 * sn;
-  const double p = 1.0 / ph.gamma + 0.1 * cs, p1 = -0.1 * sn, p2 = -0.1 * cs;
+  sincos(fma(k, x + z, -(om * t)), &sn, &cs);
+  const double rho = fma(0.5, sn, 1.0), r1 = 0.5 * cs, r2 = -0.5 * sn;
+  const double p = fma(0.1, cs, 1.0 / ph.gamma), p1 = -0.1 * sn;
   const double u = 0.25 * sn, u1 = 0.25 * cs, u2 = -0.25 * sn;
   const double ir = 1.0 / rho;
-  const double m1 = r1 * u + rho * u1;                 // (rho u)'
-  const double mu1 = u * (r1 * u + 2.0 * rho * u1);    // (rho u^2)'
-  const double E = p / ph.gm1 + rho * u * u, E1 = p1 / ph.gm1 + mu1;
-  const double H1 = u1 * (E + p) + u * (E1 + p1);      // (u (E + p))'
+  const double m1 = fma(r1, u, rho * u1);              // (rho u)'
+  const double h1 = fma(r1, u, 2.0 * rho * u1);        // (rho u^2)' / u
+  const double E = fma(rho * u, u, p / ph.gm1), E1 = fma(u, h1, p1 / ph.gm1);
+  const double H1 = fma(u1, E + p, u * fma(-0.1, sn, E1));   // (u (E + p))', p' = -sin(xi)/10
   const double T = p * ir * ph.iR;
-  const double T1 = (p1 * ph.iR - r1 * T) * ir;
-  const double T2 = (p2 * ph.iR - r2 * T - 2.0 * r1 * T1) * ir;
+  const double T1 = fma(p1, ph.iR, -(r1 * T)) * ir;
+  const double T2 = fma(-2.0 * r1, T1, fma(-0.1 * cs, ph.iR, -(r2 * T))) * ir;
   const double kk = k * k;
-  S[0] = 2.0 * k * m1 - om * r1;
-  S[1] = k * (2.0 * mu1 + p1) - om * m1 - (8.0 / 3.0) * ph.mu * kk * u2;
+  S[0] = fma(2.0 * k, m1, -(om * r1));
+  S[1] = fma((-8.0 / 3.0) * ph.mu * kk, u2, fma(k, fma(2.0 * u, h1, p1), -(om * m1)));
   S[2] = S[1];
-  S[3] = 2.0 * k * H1 - om * E1 - (16.0 / 3.0) * ph.mu * kk * (u1 * u1 + u * u2) - 2.0 * ph.kappa * kk * T2;
+  S[3] = fma(-2.0 * ph.kappa * kk, T2,
+             fma((-16.0 / 3.0) * ph.mu * kk, fma(u1, u1, u * u2), fma(2.0 * k, H1, -(om * E1))));
 }
 
 // Square root, correctly rounded.  Goldschmidt's coupled iteration for the root

@@ -43,7 +43,8 @@ namespace adg {
 // coordinates (the 1/h sits in mu, kap and gh).  The mass fluxes are the
 // momenta themselves and are left out.  With a = rho du/dx etc. the
 // divisions by rho collect in ir; the two shear fluxes mx w + sxz and
-// mz u + sxz are one number.
+// mz u + sxz are one number.  Every product that meets a sum does so in an
+// explicit fused operation: the kernels' results agree bit for bit.
 __device__ inline void flux_xz(const FluxC& c, const double q[4], const double gx[4], const double gz[4],
                                double Fx[3], double Fz[3]) {
   const double rho = q[0], mx = q[1], mz = q[2], E = q[3];
@@ -59,17 +60,17 @@ __device__ inline void flux_xz(const FluxC& c, const double q[4], const double g
   const double dx = fma(-w, cx, fma(-u, ax, fma(-hv, gx[0], gx[3])));    // dp / gm1
   const double dz = fma(-c.gh, rho, fma(-w, cz, fma(-u, az, fma(-hv, gz[0], gz[3]))));
   const double m23 = c.mu23 * ir;
-  const double sxx = m23 * fma(-2.0, ax, cz), szz = m23 * fma(-2.0, cz, ax);
+  const double exx = fma(-2.0, ax, cz), ezz = fma(-2.0, cz, ax);         // sxx = m23 exx, szz = m23 ezz
   const double sxz = -(c.mu * ir) * (az + cx);
   const double k = c.kap * ir;
   const double qx = fma(-pir, gx[0], c.gm1 * dx), qz = fma(-pir, gz[0], c.gm1 * dz);
   const double H = E + p;
-  Fx[0] = fma(mx, u, pm + sxx);
+  Fx[0] = fma(mx, u, fma(m23, exx, pm));
   Fx[1] = fma(mx, w, sxz);
-  Fx[2] = fma(-k, qx, fma(w, sxz, u * (H + sxx)));
+  Fx[2] = fma(-k, qx, fma(w, sxz, u * fma(m23, exx, H)));
   Fz[0] = Fx[1];
-  Fz[1] = fma(mz, w, pm + szz);
-  Fz[2] = fma(-k, qz, fma(u, sxz, w * (H + szz)));
+  Fz[1] = fma(mz, w, fma(m23, ezz, pm));
+  Fz[2] = fma(-k, qz, fma(u, sxz, w * fma(m23, ezz, H)));
 }
 
 // Instructions do not move across this line: it bounds how many loads the
@@ -160,7 +161,7 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   fc.gh = ph.geff * h;
   if constexpr (CB == 1) { fc.mu = uniform(fc.mu); fc.mu23 = uniform(fc.mu23); fc.kap = uniform(fc.kap); fc.gh = uniform(fc.gh); }
   // background at the node of the time column (row j = hi)
-  const double zc = z0 + h * gt[GTab::XI * n + hi];
+  const double zc = fma(h, gt[GTab::XI * n + hi], z0);
   const double* bg = a.bg + (size_t)cc * 2 * (n + 2);
   const double rbc = bg[2 * hi], pbc = bg[2 * hi + 1];
   const double* Qc = a.Qin + (size_t)cc * sl;
@@ -177,7 +178,7 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
     if (act && hi == 0) lev[lo] = wave_phase(ph, ph.mms_u * tb, ph.mms_w * tb);
     sync();
     if (act) {
-      const WavePhase w = wave_phase(ph, (x0 + h * xi) - ph.mms_u * t0, zc - ph.mms_w * t0);
+      const WavePhase w = wave_phase(ph, fma(-ph.mms_u, t0, fma(h, xi, x0)), fma(-ph.mms_w, t0, zc));
 #pragma unroll
       for (int b = 0; b < n; ++b) smm[b * nn + r] = mms_source(ph, w, lev[b]);
     }
@@ -222,7 +223,7 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
     fc.pb = pbc;
     flux_xz(fc, X[0], gx, gz, Fx, Fz);
     R[0] = gx[1] + gz[2];
-    R[2] = fc.gh * (X[0][0] - rbc);
+    R[2] = X[0][0] - rbc;
 #pragma unroll
     for (int v = 1; v < 4; ++v) { S[sl + v * nn + r] = Fx[v - 1]; S[2 * sl + v * nn + r] = Fz[v - 1]; }
   }
@@ -245,7 +246,10 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   sync();
   if (act) {
 #pragma unroll
-    for (int v = 1; v < 4; ++v) R[v] += S[sl + v * nn + r] + S[2 * sl + v * nn + r];
+    for (int v = 1; v < 4; ++v) {
+      const double div = S[sl + v * nn + r] + S[2 * sl + v * nn + r];
+      R[v] = v == 2 ? fma(fc.gh, R[2], div) : div;   // -h times the gravity source
+    }
   }
 #pragma unroll
   for (int b = 0; b < n; ++b)
@@ -254,7 +258,7 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
   // background of the lane's row (j = lo)
   const double rbr = bg[2 * lo];
   fc.pb = bg[2 * lo + 1];
-  fc.gz = ph.geff * (z0 + h * gt[GTab::XI * n + lo]);
+  fc.gz = ph.geff * fma(h, gt[GTab::XI * n + lo], z0);
   sync();
 
   double Qb[4] = {0.0, 0.0, 0.0, 0.0}, Fxa[3] = {0.0, 0.0, 0.0}, Fza[3] = {0.0, 0.0, 0.0};
@@ -264,11 +268,11 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
     // X holds the scaled residuals R' (time columns): manufactured sources,
     // then X <- Q^n - (dt/h) K1^{-1} W R' by forward and back substitution
     if constexpr (PW) {
-      const double x = x0 + h * gt[GTab::XI * n + lo];
+      const double x = fma(h, gt[GTab::XI * n + lo], x0);
 #pragma unroll
       for (int b = 0; b < n; ++b) {
         double Sm[4];
-        paper_wave_source(ph, x, zc, t0 + gt[GTab::XI * n + b] * dt, Sm);
+        paper_wave_source(ph, x, zc, fma(gt[GTab::XI * n + b], dt, t0), Sm);
 #pragma unroll
         for (int v = 0; v < 4; ++v) X[b][v] = fma(-h, Sm[v], X[b][v]);
       }
@@ -353,7 +357,7 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
         }
 #pragma unroll
         for (int v = 1; v < 4; ++v) g[v][i] = Fx[v - 1];
-        q[0][i] = fc.gh * (q[0][i] - rbr);                 // -h times the gravity source
+        q[0][i] -= rbr;
         fence_schedule();
       }
     }
@@ -367,7 +371,7 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
 #pragma unroll
       for (int v = 1; v < 4; ++v)
 #pragma unroll
-        for (int i = 0; i < n; ++i) rowp[v * VS + i * IS] += v == 2 ? g[v][i] + q[0][i] : g[v][i];
+        for (int i = 0; i < n; ++i) rowp[v * VS + i * IS] += v == 2 ? fma(fc.gh, q[0][i], g[v][i]) : g[v][i];
     }
     sync();
 #pragma unroll
@@ -491,11 +495,11 @@ __device__ __forceinline__ void predict_rows(const Phys& ph, const StepArgs& a, 
       for (int b = 0; b < n; ++b) Sb[3] = fma(gt[GTab::W * n + b], smm[b * nn + r], Sb[3]);
     }
     if constexpr (PW) {
-      const double x = x0 + h * gt[GTab::XI * n + lo];
+      const double x = fma(h, gt[GTab::XI * n + lo], x0);
 #pragma unroll 1
       for (int b = 0; b < n; ++b) {
         double Sm[4];
-        paper_wave_source(ph, x, zc, t0 + gt[GTab::XI * n + b] * dt, Sm);
+        paper_wave_source(ph, x, zc, fma(gt[GTab::XI * n + b], dt, t0), Sm);
         const double wb = gt[GTab::W * n + b];
 #pragma unroll
         for (int v = 0; v < 4; ++v) Sb[v] = fma(wb, Sm[v], Sb[v]);
@@ -580,7 +584,7 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
   fc.mu23 = uniform(fc.mu * (2.0 / 3.0));
   fc.kap = uniform(ph.kappa * ih * ph.iR);
   fc.gh = uniform(ph.geff * h);
-  const double zc = z0 + h * gt[GTab::XI * n + hi];
+  const double zc = fma(h, gt[GTab::XI * n + hi], z0);
   // background at the time column's node (row hi) and of the lane's row (lo)
   const double* bg = a.bg + (size_t)cell * 2 * (n + 2);
   const double rbc = bg[2 * hi], pbc = bg[2 * hi + 1], rbr = bg[2 * lo], pbr = bg[2 * lo + 1];
@@ -589,11 +593,11 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
 #pragma unroll
   for (int b = 0; b < n; ++b) Sm[b] = 0.0;
   if constexpr (PW) {
-    const double x = x0 + h * gt[GTab::XI * n + lo];
+    const double x = fma(h, gt[GTab::XI * n + lo], x0);
 #pragma unroll
     for (int b = 0; b < n; ++b) {
       double S4[4];
-      paper_wave_source(ph, x, zc, t0 + gt[GTab::XI * n + b] * dt, S4);
+      paper_wave_source(ph, x, zc, fma(gt[GTab::XI * n + b], dt, t0), S4);
       Sm[b] = w == 0 ? S4[0] : w == 1 ? S4[1] : w == 2 ? S4[2] : S4[3];
     }
   }
@@ -629,8 +633,8 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       const int lev = lane & 31;   // w = 3: lanes 0.. the levels along x, 32.. along z
       const double xi = gt[GTab::XI * n + min(lev, n - 1)];
       double ang;
-      if (w == 1) ang = ph.mms_kx * ((x0 + h * gt[GTab::XI * n + lo]) - ph.mms_u * t0);
-      else if (w == 2) ang = ph.mms_kz * (zc - ph.mms_w * t0);
+      if (w == 1) ang = ph.mms_kx * fma(-ph.mms_u, t0, fma(h, gt[GTab::XI * n + lo], x0));
+      else if (w == 2) ang = ph.mms_kz * fma(-ph.mms_w, t0, zc);
       else ang = lane < 32 ? ph.mms_kx * (ph.mms_u * (xi * dt)) : ph.mms_kz * (ph.mms_w * (xi * dt));
       double sn, cs;
       sincos(ang, &sn, &cs);
@@ -649,7 +653,7 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
       fc.pb = pbc;
       flux_xz(fc, q, gx, gz, Fx, Fz);
       GX[r] = gx[1] + gz[2];
-      GZ[r] = fc.gh * (q[0] - rbc);
+      GZ[r] = q[0] - rbc;
 #pragma unroll
       for (int v = 1; v < 4; ++v) { GX[v * nn + r] = Fx[v - 1]; GZ[v * nn + r] = Fz[v - 1]; }
     } else if (wave && w == 3) {
@@ -673,13 +677,13 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
   __syncthreads();
   double X[n];
   {
-    const double base = w == 2 ? GZ[r] : 0.0;
-    const double R = w == 0 ? GX[r] : base + (GX[w * nn + r] + GZ[w * nn + r]);
+    const double div = GX[w * nn + r] + GZ[w * nn + r];
+    const double R = w == 0 ? GX[r] : w == 2 ? fma(fc.gh, GZ[r], div) : div;   // -h times the gravity source
 #pragma unroll
     for (int b = 0; b < n; ++b) X[b] = R;
   }
   fc.pb = pbr;
-  fc.gz = ph.geff * (z0 + h * gt[GTab::XI * n + lo]);
+  fc.gz = ph.geff * fma(h, gt[GTab::XI * n + lo], z0);
 
   // gradients of the iterate: this wavefront's variable along x and z
   auto gradients = [&] {
@@ -699,7 +703,7 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
     }
   };
   // fluxes at this wavefront's nodes, over the gradients; with res the mass
-  // residual and the gravity source go to the free mass slots
+  // residual and the density perturbation go to the free mass slots
   auto fluxes = [&](bool res) {
 #pragma unroll
     for (int i = 0; i < n; i += kSplit) {
@@ -712,7 +716,7 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
         if (act) {
           if (res) {
             GX[o] = gx[1] + gz[2];
-            GZ[o] = fc.gh * (q[0] - rbr);
+            GZ[o] = q[0] - rbr;
           }
 #pragma unroll
           for (int v = 1; v < 4; ++v) { GX[v * VS + o] = Fx[v - 1]; GZ[v * VS + o] = Fz[v - 1]; }
@@ -781,11 +785,12 @@ __device__ __forceinline__ void predict_split(const Phys& ph, const StepArgs& a,
     for (int b = 0; b < n; ++b) {
       const int o = timo + b * BS;
       if (w == 0) X[b] = GX[o];
-      else if (w == 2) X[b] = GZ[2 * VS + o] + (GX[2 * VS + o] + GZ[o]);
+      else if (w == 2) X[b] = GZ[2 * VS + o] + fma(fc.gh, GZ[o], GX[2 * VS + o]);
       else X[b] = GZ[w * VS + o] + GX[w * VS + o];
     }
-    // (the next writes to the gradient buffers come two barriers later, those
-    // to the iterate's touch no value read here)
+    // (the iterate's buffer, written next, holds no value read here; the
+    // gradient buffers, whose mass slots other wavefronts read here, are written
+    // after the barrier that publishes the iterate)
   }
 
   // time averages: of the state and, from the fluxes of the last iterate, of

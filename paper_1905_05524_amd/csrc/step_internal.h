@@ -17,6 +17,16 @@ __device__ inline double uniform(double v) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// A value with the rounding of the operation that gave it: the compiler may not
+// contract that operation into a sum that takes the value.  Where kernels share
+// their arithmetic but not their data paths (one sums in registers what another
+// passes through LDS) the products either meet their sums in explicit fused
+// operations or pass through here, so that results agree bit for bit.
+__device__ inline double rounded(double v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // A wavefront-uniform table read through scalar loads (opaque, so that the
 // entries are loaded where they are used instead of being held).
 typedef const __attribute__((address_space(4))) double* ctab;
@@ -49,7 +59,15 @@ struct EO {
       double S = M[0] * o[0];
 #pragma unroll
       for (int m = 1; m < h; ++m) S = fma(M[m], o[m], S);
-      out[mid] = S;
+      out[mid] = h == 1 ? rounded(S) : S;   // a bare product at n = 3
+    }
+    if constexpr (h == 1) {
+      double U = B[0][0] * e[0];
+      if constexpr (n % 2) U = fma(C[0], mv, U);
+      else U = rounded(U);
+      out[0] = fma(A[0][0], o[0], U);
+      out[n - 1] = fma(A[0][0], o[0], -U);
+      return;
     }
 #pragma unroll
     for (int i = 0; i < h; ++i) {
