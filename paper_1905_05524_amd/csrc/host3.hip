@@ -1,6 +1,8 @@
 // Host side of the three-dimensional C ABI: validation, handle lifetime,
 // workspace layout and dispatch of the kernels in step3.hip.
+#include <algorithm>
 #include <cmath>
+#include <memory>
 #include <new>
 
 #include "adg3_internal.h"
@@ -71,13 +73,19 @@ int adg3_init_mesh(const adg_params* prm, const adg3_mesh_desc* mesh, adg3_mesh*
   m->iters = prm->picard_iters > 0 ? prm->picard_iters : m->n;
   m->ph = make_phys(*prm);
   build_basis(m->n, m->basis);
-  // basis tables, then the background: zeros without gravity
-  std::vector<double> tab(m->basis.gtab);
-  tab.resize(tab.size() + 2 * (size_t)mesh->nz * (m->n + 2), 0.0);
-  const size_t tb = sizeof(double) * tab.size();
-  if (hipMalloc(&m->d_gtab, tb) != hipSuccess) { delete m; return fail(ADG_ENOMEM, "device allocation failed"); }
+  // Basis tables, then the background.  Without gravity it is zeros: they go up
+  // with the tables while they are few (a fill of its own is a launch of 10 us),
+  // else they are cleared before the upload, whose wait covers the fill.
+  const size_t nt = m->basis.gtab.size(), nb = 2 * (size_t)mesh->nz * (m->n + 2);
+  const size_t tb = sizeof(double) * nt, bb = sizeof(double) * nb;
+  const bool zeros = !m->prm.gravity && nb <= 16384;
+  std::unique_ptr<double[]> up(new (std::nothrow) double[nt + (zeros ? nb : 0)]());
+  if (!up) { delete m; return fail(ADG_ENOMEM, "out of host memory"); }
+  std::copy(m->basis.gtab.begin(), m->basis.gtab.end(), up.get());
+  if (hipMalloc(&m->d_gtab, tb + bb) != hipSuccess) { delete m; return fail(ADG_ENOMEM, "device allocation failed"); }
   m->d_bg = m->d_gtab + m->basis.gtab.size();
-  if (hipMemcpy(m->d_gtab, tab.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
+  if ((!m->prm.gravity && !zeros && hipMemset(m->d_bg, 0, bb) != hipSuccess) ||
+      hipMemcpy(m->d_gtab, up.get(), tb + (zeros ? bb : 0), hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(m->d_gtab);
     delete m;
     return fail(ADG_EHIP, "upload failed");

@@ -48,3 +48,20 @@ def test_step_after_handles_with_gravity(N):
     m.set_state(Q, t=0.0, dt=dt)
     m.step()
     P.assert_step(m.Q.cpu().numpy(), O.step3(phys, mesh, Q, 0.0, dt), Q, V=5)
+
+
+@pytest.mark.parametrize("nz", [1638, 1639])
+def test_columns_around_the_size_of_the_upload(nz):
+    """N = 2, 10 doubles per layer: up to 16,384 zeros are sent, more are cleared on
+    the device."""
+    for _ in range(2):
+        adg.Mesh3(dict(I.ATMO, N=2, picard_iters=1, mu=0.01, mms=0, cfl=0.5),
+                  dict(nx=1, ny=1, nz=nz, h=1.0, bc=[I.BC_PERIODIC] * 6))
+    phys, mesh = grid3(I.CFD)
+    mesh.update(nx=1, ny=1, nz=nz)
+    Q = I.random_state_cfd3(nz, 2, seed=4)
+    dt = 0.5 * O.dt3(phys, mesh, Q)
+    m = adg.Mesh3(phys, mesh)
+    m.set_state(Q, t=0.0, dt=dt)
+    m.step()
+    P.assert_step(m.Q.cpu().numpy(), O.step3(phys, mesh, Q, 0.0, dt), Q, V=5)
