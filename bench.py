@@ -743,7 +743,7 @@ def main():
                    "cells": C, "order": N, "dof": dof, "parallelism": "single GPU"},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_PEAK_TFLOPS,
-                     "traffic": measured_traffic(f"k_predictor<{N + 1}"),
+                     "traffic": measured_traffic(f"k_predict_rows<{N + 1}"),
                      "traffic_unit": "bytes per launch (FETCH_SIZE x2 + WRITE_SIZE x1, copy-calibrated)",
                      "kernel": f"k_predict_rows<{N + 1}>", "kernel_ms": pred_ms, "kernel_launches_timed": len(ev),
                      "flops_per_launch": pflops},

@@ -238,7 +238,8 @@ int adg_regrid_apply(adg_mesh* m, double* Q_new, void* workspace_new, double* cl
  * 2 or 4, all the same) four wavefronts per cell, for meshes too small to
  * fill the GPU with one.  Results do not depend on the shape, to the last bit.
  * Default: by order and cells (four wavefronts per cell up to 768 cells at
- * orders 5 and up and 384 below, then the packing measured fastest).
+ * orders 5 and up, 512 at orders 2 to 4 and 1,024 at order 1, then the packing
+ * measured fastest).
  * adg_autotune reports four wavefronts per cell as 0, 1. */
 int adg_set_launch(adg_mesh* m, int cells_per_wave, int waves_per_block);
 

@@ -223,7 +223,7 @@ int check_launch(const char* what);
 // Gauss-Legendre basis of n nodes and its device tables (computed in long
 // double, stored in double).
 void build_basis(int n, HostBasis& B);
-// persistent predictor of one order group (k_predictor's body on work items
+// persistent predictor of one order group (predict_rows on work items
 // from counter [2], nwaves resident wavefronts), and its resident
 // wavefronts per CU
 int launch_predictor_queue(const Group& g, unsigned* counter, int nwaves, hipStream_t s);

@@ -16,8 +16,8 @@
 // three variables, not four, go through the divergences.
 //
 // What bounds it (counters at 243 x 243 cells, n = 7): the vector units are
-// busy 72 % of the time (8,660 vector instructions per cell; 8,400 since the
-// background comes from a table), the LDS 63 %.
+// busy 70 % of the time (8,390 vector instructions per cell), the LDS 63 %; at
+// 81 x 81 cells, with a nearly empty third round of wavefronts, 54 and 49 %.
 // The kernel before it kept one node per lane and went through LDS for every
 // contraction of one time level at a time (26 writes and 30 reads per node
 // and level against 18 and 22 here, and 28 dependent LDS stages per sweep

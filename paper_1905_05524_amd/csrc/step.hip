@@ -407,11 +407,11 @@ static int corr_w(const Group& g, hipStream_t s) {
 }
 // Cells per wavefront of a launch without a shape of its own: as many as have
 // a lane for every node and every face node.  One cell for each wavefront
-// takes 50 us for 200 x 200 cells at every n up to 6 (1.2 ns a cell, the rate
-// of the wavefronts); with them packed, corrector and clock take 19 us at
-// n = 2, 23 at n = 3, 28 at n = 4 and 38 at n = 5, near the time of their
-// memory traffic, and no mesh of 81 to 3,600 cells gets slower.  At n = 6 and 7
-// (51 and 53 us) the traffic bounds one cell per wavefront already.
+// takes 47 to 48 us for 200 x 200 cells, with the clock, at every n up to 6 (1.2
+// ns a cell, the rate of the wavefronts); with them packed, 17 us at n = 2, 21 at
+// n = 3, 26 at n = 4 and 35 at n = 5, near the time of their memory traffic, and
+// no mesh of 81 to 3,600 cells gets slower.  At n = 6 and 7 (48 and 50 us) the
+// traffic bounds one cell per wavefront already.
 constexpr int corr_cells(int n) { return n == 2 ? 8 : n == 3 ? 5 : n == 4 ? 4 : n == 5 ? 2 : 1; }
 // cells per wavefront of a launch shape: 1, 2 or 4 (while CPW * n^2 <= 64)
 template <int n>
