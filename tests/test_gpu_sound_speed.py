@@ -30,3 +30,18 @@ def test_root_is_correctly_rounded():
     with np.errstate(all="ignore"):
         want = 0.5 / (9.0 * np.sqrt(2.0 * E))
     assert np.array_equal(got, want, equal_nan=True), [(E[k], got[k], want[k]) for k in np.flatnonzero(got != want)[:8]]
+
+
+def test_reciprocal_of_the_density_is_correctly_rounded():
+    """The viscous speed of a cell with (next to) no pressure: with gamma = 2,
+    Pr = 1 and mu = 1/2 it is 1/rho, and the candidate cfl h / (9 (2 (1/rho) 3))."""
+    rng = np.random.default_rng(2)
+    nx = 24000
+    phys = dict(I.CFD, gamma=2.0, Pr=1.0, N=1, picard_iters=1, mu=0.5, mms=0, cfl=0.5)
+    m = adg.Mesh3(phys, dict(nx=nx, ny=1, nz=1, h=1.0, bc=[I.BC_PERIODIC] * 6))
+    rho = np.ldexp(1.0 + rng.random(nx), rng.integers(-60, 61, nx))
+    m.Q.zero_()
+    m.Q[:, 0] = torch.as_tensor(rho, device="cuda").view(nx, 1, 1, 1)
+    m.Q[:, 4] = 2.0 ** -900
+    m.compute_dt()
+    assert np.array_equal(m.cell_dt().cpu().numpy(), 0.5 / (9.0 * (2.0 * (1.0 / rho) * 3.0)))
