@@ -9,6 +9,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from oracle import oracle as O
 from paper_1905_05524_amd import adg
 from paper_1905_05524_amd import inputs as I
 
@@ -83,3 +84,40 @@ def test_static_step_of_the_largest_mesh():
     m.step_static(Q, clock)
     m.step()
     assert torch.equal(Q, m.Q) and torch.equal(clock, m.clock)
+
+
+def test_minimum_across_a_regrid():
+    """3,025 cells refined to 27,225 and merged again: the section for the two
+    stages comes and goes with the workspace."""
+    phys = dict(I.CFD, N=1, picard_iters=0, mu=0.01, mms=0, cfl=0.5)
+    mesh = dict(nx=55, nz=55, max_level=1, x0=0.0, z0=0.0, Lx=1.0, Lz=1.0, bc=[I.BC_PERIODIC] * 4,
+                leaves=I.uniform_leaves(55, 55))
+    m = adg.Mesh(phys, mesh)
+    m.set_state(I.random_state_cfd(55 * 55, 1, seed=8), t=0.0)
+    for flag, cells in ((1, 27225), (-1, 3025)):
+        assert m.regrid(np.full(m.C, flag, dtype=np.int8)) == cells
+        m.Q[cells - 1, 3] *= 40.0
+        m.compute_dt()
+        want = O.dt(phys, dict(mesh, leaves=m.leaves()), m.Q.cpu().numpy())
+        assert abs(m.dt - want) <= 1e-12 * want, cells
+
+
+def test_two_stages_in_a_captured_step():
+    phys = dict(I.CFD, N=1, picard_iters=1, mu=0.01, mms=0, cfl=0.5)
+    mesh = dict(nx=30, ny=29, nz=29, h=1.0 / 32, bc=[I.BC_PERIODIC] * 6)
+    Q = I.random_state_cfd3(30 * 29 * 29, 1, seed=5)
+    eager, graph = adg.Mesh3(phys, mesh), adg.Mesh3(phys, mesh)
+    for m in (eager, graph):
+        m.set_state(Q, t=0.0)
+        m.compute_dt()
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        graph.step()
+    for _ in range(4):
+        g.replay()
+        eager.step()
+        torch.cuda.synchronize()
+        assert torch.equal(graph.Q, eager.Q) and torch.equal(graph.clock, eager.clock)
+        assert torch.equal(graph.cell_dt(), eager.cell_dt())
